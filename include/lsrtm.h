@@ -127,11 +127,17 @@ enum {
                                        are bitwise the same.  Two-phase steps with checkpoints
                                        for the whole plan only; 0 = off
                                        (default).  Re-plans when changed.       */
-    LSRTM_OPT_GRAPH_CACHE = 12      /* most pass graphs kept (least recently
+    LSRTM_OPT_GRAPH_CACHE = 12,     /* most pass graphs kept (least recently
                                        used replaced first; a pass graph is
                                        keyed by pass kind, launch group, data
                                        pointer and tile); 0 = 8 per launch
                                        group plus 8 (default)                   */
+    LSRTM_OPT_RESIDENT = 13         /* 2D: 1 = keep a shot's fields in registers
+                                       through many time steps per launch where
+                                       its window fits (default; padded depth
+                                       up to 384 nodes, two-phase steps), 0 =
+                                       one velocity and one pressure kernel per
+                                       step.  Both give identical results       */
 };
 
 /* Create a context for one grid on one HIP stream (hipStream_t, may be 0).

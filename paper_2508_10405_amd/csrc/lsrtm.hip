@@ -34,6 +34,7 @@
 
 #include "../../include/lsrtm.h"
 #include "kernels.h"
+#include "resident.h"
 
 using namespace lsrtm;
 
@@ -47,6 +48,7 @@ struct Window {
     int N[3];
     int ldz;
     long long sx, sy, npts;
+    long long segn;                // elements of one replay-buffer array of a step
     float* kdt = nullptr;
     float* sb = nullptr;
     float* bdt[3] = {nullptr, nullptr, nullptr};
@@ -62,6 +64,17 @@ struct ShotInfo {
     long long data_off;
     long long ckbytes;
     std::vector<int> rec_lin;
+};
+
+// One launch of the resident 2D kernels: the slabs of a run of slots.
+struct ResLaunch {
+    int cx = 1, nblocks = 0, maxnodes = 0;
+    size_t lds = 0;
+    ResBlock* blocks = nullptr;
+    int* rptr = nullptr;           // receivers by workgroup (recording kinds)
+    Rec* rec = nullptr;
+    int* nptr = nullptr;           // receiver nodes by workgroup (adjoint)
+    int4* node = nullptr;
 };
 
 struct Group {
@@ -94,13 +107,17 @@ struct Group {
     // d_slots but for seg), and whether the cache holds this group's replays
     Slot* d_rc = nullptr;
     bool rc_valid = false;
+    std::vector<ResLaunch> res[R_KINDS];   // resident launches, in slot order
+    std::vector<int> h_node_slot, h_node_idx, h_node_ptr;   // receiver nodes (host copy)
     long long max_npts = 0;
     long long bg_used = 0, sc_used = 0, img_used = 0;   // floats
+    long long segn = 0;            // elements of one replay-buffer array of a step, all slots
 };
 
 struct EvPair {
     hipEvent_t a, b;
     int cls;
+    int count = 1;                 // launches (resident: time steps) the sample stands for
 };
 
 }  // namespace
@@ -181,6 +198,16 @@ struct lsrtm_ctx {
     int opt_tile_v = -1;           // two-phase steps: tile of the velocity phases (-1: tile)
     int opt_tile_a = -1;           // two-phase steps: tile of the adjoint A phase (-1: tile)
     long long opt_rcache_mb = 0;   // HBM the replay cache may take (0: none)
+    int opt_res = 1;               // 2D: resident time stepping where the plan allows it
+    // resident time stepping
+    bool res_ok = false;           // the plan's windows fit
+    bool res_on = false;           // passes run on it (replay-cache layout too)
+    int res_bz = 0;
+    unsigned long long* res_ex = nullptr;   // exchange words
+    long long res_exn = 0;
+    int* res_ctl = nullptr;        // [0] gave up, [1 + i] arrivals of launch i of a group's pass
+    int res_ctln = 0, res_launch = 0;
+    unsigned res_tag = 0;
     // timing
     std::vector<EvPair> evpool;
     size_t evused = 0;
@@ -282,6 +309,9 @@ void free_acq(lsrtm_ctx* c) {
     c->psf_d = nullptr;
     c->cg_active = false;
     c->src_amp = nullptr;
+    c->res_ok = false;
+    c->res_ex = nullptr;
+    c->res_ctl = nullptr;
 }
 
 long long round_up(long long a, long long m) { return (a + m - 1) / m * m; }
@@ -341,6 +371,7 @@ EvPair* tpick(lsrtm_ctx* c, int cls) {
     }
     EvPair& e = c->evpool[c->evused];
     e.cls = cls;
+    e.count = 1;
     return &e;
 }
 
@@ -386,7 +417,7 @@ lsrtm_status pass_end(lsrtm_ctx* c) {
         float t = 0.f;
         HIPCHK(c, hipEventElapsedTime(&t, c->evpool[i].a, c->evpool[i].b));
         c->kms[c->evpool[i].cls] += t;
-        c->kcnt[c->evpool[i].cls] += 1;
+        c->kcnt[c->evpool[i].cls] += c->evpool[i].count;
     }
     c->evused = 0;
     return LSRTM_OK;
@@ -576,12 +607,115 @@ lsrtm_status check_flag(lsrtm_ctx* c) {
 }
 
 // ---------------------------------------------------------------------------
+// Resident 2D time stepping
+// ---------------------------------------------------------------------------
+// Clears what the launches of one group's pass share: the arrival counts and
+// the exchange words (tags grow through the pass from 1).
+lsrtm_status res_begin(lsrtm_ctx* c) {
+    c->res_launch = 0;
+    c->res_tag = 0;
+    CHK(fill(c, reinterpret_cast<float*>(c->res_ctl + 1), c->res_ctln - 1));
+    return fill(c, reinterpret_cast<float*>(c->res_ex), 2 * c->res_exn);
+}
+
+// Advances every slot of a group from step n0 to n1 (the adjoint from n1 - 1
+// back to n0).
+lsrtm_status res_run(lsrtm_ctx* c, Group& gr, int kind, const Slot* sl, int n0, int n1, int sstep0, int first,
+                     float* d, const float* y) {
+    static const int cls_of[R_KINDS] = {2, 2, 0, 0, 4};
+    bool lead = true;
+    for (const ResLaunch& L : gr.res[kind]) {
+        if (c->res_launch + 1 >= c->res_ctln) FAIL(c, LSRTM_EHIP, "more resident launches than planned");
+        ResArgs a;
+        a.slots = dev_slots(sl);
+        a.blocks = L.blocks;
+        a.C = c->C;
+        a.n0 = n0;
+        a.n1 = n1;
+        a.sstep0 = sstep0;
+        a.first = first;
+        a.npml = c->g.npml;
+        a.rptr = d ? L.rptr : nullptr;
+        a.rec = kind == R_ADJ ? gr.d_node_rec : L.rec;
+        a.d = d;
+        a.y = y;
+        a.nptr = L.nptr;
+        a.node = L.node;
+        a.maxnodes = L.maxnodes;
+        a.ex = c->res_ex;
+        a.tag0 = c->res_tag;
+        a.ctl = c->res_ctl + 1 + c->res_launch++;
+        a.abort_ = c->res_ctl;
+        c->res_tag += (unsigned)(n1 - n0) + 2;
+        // a sample stands for the steps of the whole group
+        c->tnow = true;
+        EvPair* ev = kind == R_BORN_RC ? nullptr : tpick(c, cls_of[kind]);
+        if (ev) ev->count = lead ? n1 - n0 : 0;
+        lead = false;
+        hipError_t e = hipErrorInvalidValue;
+        hipEvent_t e0 = ev ? ev->a : nullptr, e1 = ev ? ev->b : nullptr;
+        switch (c->res_bz) {
+        case 2: e = launch_resident_bz<2>(kind, L.cx, L.nblocks, L.lds, c->st, a, e0, e1); break;
+        case 3: e = launch_resident_bz<3>(kind, L.cx, L.nblocks, L.lds, c->st, a, e0, e1); break;
+        case 4: e = launch_resident_bz<4>(kind, L.cx, L.nblocks, L.lds, c->st, a, e0, e1); break;
+        case 5: e = launch_resident_bz<5>(kind, L.cx, L.nblocks, L.lds, c->st, a, e0, e1); break;
+        case 6: e = launch_resident_bz<6>(kind, L.cx, L.nblocks, L.lds, c->st, a, e0, e1); break;
+        }
+        if (e != hipSuccess) FAIL(c, LSRTM_EHIP, "resident launch (kind %d): %s", kind, hipGetErrorString(e));
+        if (ev) c->evused++;
+    }
+    return LSRTM_OK;
+}
+
+lsrtm_status res_forward(lsrtm_ctx* c, Group& gr, int mode, float* d, bool write_ck) {
+    CHK(fill(c, c->pool, gr.bg_used));
+    if (mode == 1) CHK(fill(c, c->pool + c->bg_region, gr.sc_used));
+    CHK(res_begin(c));
+    const int nt = c->g.nt, jc = c->nseg - c->rc_m;
+    const bool use_rc = mode == 1 && !write_ck && c->rc_m > 0 && gr.rc_valid;
+    for (int n = 0; n < nt;) {
+        const int j = n / c->k;
+        int end = nt;
+        if (write_ck && n > 0) CHK(ckpt(c, gr, j, true, gr.d_slots));
+        if (write_ck) end = std::min(nt, (j + 1) * c->k);
+        if (use_rc && j >= jc) {
+            end = std::min(nt, (j + 1) * c->k);
+            CHK(res_run(c, gr, R_BORN_RC, gr.d_rc + (long long)(j - jc) * gr.ns, n, end, 0, 0, d, nullptr));
+        } else {
+            if (use_rc) end = std::min(nt, jc * c->k);
+            CHK(res_run(c, gr, mode == 1 ? R_BORN : R_BG, gr.d_slots, n, end, 0, 0, mode != 2 ? d : nullptr, nullptr));
+        }
+        n = end;
+    }
+    return LSRTM_OK;
+}
+
+// The reverse steps of a group's migration (the caller clears the fields,
+// injects the data of the last step and reduces the images).
+lsrtm_status res_adjoint(lsrtm_ctx* c, Group& gr, const float* d) {
+    CHK(res_begin(c));
+    const int nt = c->g.nt, jc = c->nseg - c->rc_m;
+    for (int j = c->nseg - 1; j >= 0; --j) {
+        const int n0 = j * c->k, n1 = std::min(n0 + c->k, nt);
+        const Slot* sl = j >= jc ? gr.d_rc + (long long)(j - jc) * gr.ns : gr.d_slots;
+        if (j < jc || !gr.rc_valid) {
+            if (j == 0) CHK(fill(c, c->pool, gr.bg_used));
+            else CHK(ckpt(c, gr, j, false, gr.d_slots));
+            CHK(res_run(c, gr, R_SEG, sl, n0, n1, 0, 0, nullptr, nullptr));
+        }
+        CHK(res_run(c, gr, R_ADJ, sl, n0, n1, 0, n1 == nt, nullptr, c->data_len > 0 ? d : nullptr));
+    }
+    return LSRTM_OK;
+}
+
+// ---------------------------------------------------------------------------
 // Passes of one launch group
 // ---------------------------------------------------------------------------
 // mode 0: forward (record p), 1: born (record dp), 2: forward without data.
 // With the fused schedule the step reads the buffers of parity n % 2 and
 // writes the other ones.
 lsrtm_status group_forward(lsrtm_ctx* c, Group& gr, int mode, float* d, bool write_ck) {
+    if (c->res_on) return res_forward(c, gr, mode, d, write_ck);
     CHK(build_tiles(c, gr, c->tile));
     CHK(fill(c, c->pool, gr.bg_used));
     if (mode == 1) CHK(fill(c, c->pool + c->bg_region, gr.sc_used));
@@ -633,10 +767,11 @@ lsrtm_status group_adjoint(lsrtm_ctx* c, Group& gr, const float* d) {
     };
     tstep(c, nt - 1);
     CHK(inject(nt - 1));
+    if (c->res_on) CHK(res_adjoint(c, gr, d));
     // segments j >= jc replay into the replay cache, and only when it does
     // not hold this group's replays yet
     const int jc = c->nseg - c->rc_m;
-    for (int j = c->nseg - 1; j >= 0; --j) {
+    for (int j = c->res_on ? -1 : c->nseg - 1; j >= 0; --j) {
         const int n0 = j * c->k, n1 = std::min(n0 + c->k, nt);
         const Slot* rcd = j >= jc ? gr.d_rc + (long long)(j - jc) * gr.ns : nullptr;
         tstep(c, n0);
@@ -730,7 +865,8 @@ lsrtm_status run_group_impl(lsrtm_ctx* c, Group& gr, int gi, int pass, float* d,
     // a migration pass that fills the replay cache and one that reads it are
     // different graphs, and so are Born passes with and without it
     const int rcv = (pass == P_ADJ || pass == P_BORN) && gr.rc_valid ? 1 : 0;
-    const auto key = std::make_tuple((pass * 2 + (write_ck ? 1 : 0)) * 2 + rcv, gi, (const void*)d, c->tile);
+    const auto key = std::make_tuple(((pass * 2 + (write_ck ? 1 : 0)) * 2 + rcv) * 2 + (c->res_on ? 1 : 0), gi,
+                                     (const void*)d, c->tile);
     auto it = c->graphs.find(key);
     hipGraphExec_t exec = nullptr;
     if (it == c->graphs.end()) {
@@ -807,12 +943,49 @@ lsrtm_status ensure_ckpts(lsrtm_ctx* c) {
 lsrtm_status autotune(lsrtm_ctx* c, int nsteps, bool groups, double* out);
 lsrtm_status plan(lsrtm_ctx* c);
 
+// Resident launches of a process run one call at a time: two of them sharing
+// the GPU would each hold workgroups that the other one waits for.
+std::mutex g_res_mu;
+
+// The two schedules keep the replay cache in layouts of their own.
+void set_resident(lsrtm_ctx* c, bool on) {
+    if (c->res_on == on) return;
+    for (auto& gr : c->groups) gr.rc_valid = false;
+    c->res_on = on;
+}
+
+// Runs the passes of one call (body) on the resident kernels where the plan
+// allows it, and again on the streaming kernels if a launch gave up waiting
+// for room on the GPU.
+template <typename F>
+lsrtm_status run_passes(lsrtm_ctx* c, F body) {
+    if (!c->res_ok || !c->opt_res) {
+        set_resident(c, false);
+        return body();
+    }
+    {
+        std::lock_guard<std::mutex> lock(g_res_mu);
+        set_resident(c, true);
+        CHK(fill(c, reinterpret_cast<float*>(c->res_ctl), 1));
+        const lsrtm_status s = body();
+        int gave_up = 0;
+        HIPCHK(c, hipMemcpyAsync(&gave_up, c->res_ctl, sizeof(int), hipMemcpyDeviceToHost, c->st));
+        HIPCHK(c, hipStreamSynchronize(c->st));
+        if (!gave_up) return s;
+    }
+    background_changed(c);
+    set_resident(c, false);
+    return body();
+}
+
 lsrtm_status check_ready(lsrtm_ctx* c) {
     if (!c) return LSRTM_EINVAL;
     if (!c->have_model) FAIL(c, LSRTM_ESTATE, "set_model has not been called");
     if (!c->have_acq) FAIL(c, LSRTM_ESTATE, "set_acquisition has not been called");
     if (c->opt_tile >= 0) {
         c->tile = c->opt_tile;
+    } else if (!c->tuned && c->res_ok && c->opt_res) {
+        c->tile = default_tile(c->ndim);   // serves the pseudo-Hessian pass only
     } else if (!c->tuned) {
         c->tile = default_tile(c->ndim);
         CHK(autotune(c, 4, false, nullptr));
@@ -859,6 +1032,190 @@ lsrtm_status prep_model_windows(lsrtm_ctx* c) {
     }
     HIPCHK(c, hipStreamSynchronize(c->st));
     background_changed(c);
+    return LSRTM_OK;
+}
+
+// Slabs of an axis of nx padded columns: (first column, in the strips).  The
+// slabs that reach a strip are as wide as their body allows.
+void res_slabs(int nx, int npml, int cx, int cxe, std::vector<std::pair<int, bool>>& out) {
+    out.clear();
+    for (int x = 0; x < nx;) {
+        const bool inner = x >= npml && x + RES_WAVES * cx <= nx - npml - 1;
+        out.push_back({x, !inner});
+        x += RES_WAVES * (inner ? cx : cxe);
+    }
+}
+
+template <typename T>
+lsrtm_status upload(lsrtm_ctx* c, T** p, const std::vector<T>& v) {
+    CHK(dalloc_t(c, p, std::max<size_t>(1, v.size()), true));
+    if (!v.empty()) HIPCHK(c, hipMemcpy(*p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice));
+    return LSRTM_OK;
+}
+
+// Rows per lane of the resident kernels for the plan's windows; 0 if they do
+// not fit (deeper than 64 lanes of the most rows, or strips wider than the
+// lanes that may hold them).
+int res_rows(const lsrtm_ctx* c) {
+    if (c->ndim != 2 || c->fused) return 0;
+    int nz = 0;
+    for (const Window& W : c->wins) nz = std::max(nz, W.N[0]);
+    const int bz = std::max(RES_BZ_MIN, (nz + 63) / 64), npml = c->g.npml;
+    if (bz > RES_BZ_MAX) return 0;
+    for (const Window& W : c->wins) {
+        const int lanes = (W.N[0] + bz - 1) / bz, low = (npml + bz - 1) / bz, top = std::max(0, W.N[0] - npml - 1) / bz;
+        if (std::min(low, lanes) + std::max(0, lanes - std::max(top, low)) > RES_ZSLOTS) return 0;
+    }
+    return bz;
+}
+
+// Estimated microseconds of one resident step: what a step costs whatever the
+// slab's width, and per node of a thread.
+double res_step_us(int kind, int nodes) {
+    static const double per[R_KINDS] = {0.20, 0.22, 0.40, 0.30, 0.30};
+    return 2.5 + per[kind] * nodes;
+}
+
+// Launches of the resident kernels for every group and kind: consecutive
+// slots whose slabs fill the GPU together, one workgroup per CU, the slab
+// width of every launch chosen for the least estimated time.
+lsrtm_status plan_resident(lsrtm_ctx* c) {
+    c->res_ok = false;
+    if (!c->res_bz) return LSRTM_OK;
+    const int bz = c->res_bz, npml = c->g.npml;
+    int dev = 0, ncu = 0;
+    HIPCHK(c, hipGetDevice(&dev));
+    HIPCHK(c, hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
+    constexpr size_t kLds = 160 * 1024 - 64;
+    long long exn = 0;
+    size_t rounds = 1;
+    std::vector<std::pair<int, bool>> sl;
+    for (auto& gr : c->groups) {
+        // receivers and receiver nodes by slot and column
+        std::vector<std::vector<int>> rcols(gr.ns), ncols(gr.ns);
+        for (int s = 0; s < gr.ns; ++s) {
+            rcols[s].assign(gr.h_slots[s].n[1], 0);
+            ncols[s].assign(gr.h_slots[s].n[1], 0);
+        }
+        for (const Rec& R : gr.h_rec) rcols[R.slot][R.idx / gr.h_slots[R.slot].ldz] += 1;
+        for (int i = 0; i < gr.nnode; ++i)
+            ncols[gr.h_node_slot[i]][gr.h_node_idx[i] / gr.h_slots[gr.h_node_slot[i]].ldz] += 1;
+        for (int kind = 0; kind < R_KINDS; ++kind) {
+            gr.res[kind].clear();
+            // workgroups of a slot, and most receivers of one, for every width
+            const auto& cols = kind == R_ADJ ? ncols : rcols;
+            const bool lists = kind != R_SEG;
+            std::vector<int> nb[RES_CX_MAX + 1], mn[RES_CX_MAX + 1];
+            for (int cx = 1; cx <= RES_CX_MAX; ++cx)
+                for (int s = 0; s < gr.ns; ++s) {
+                    const int nx = gr.h_slots[s].n[1], cxe = res_cx_edge(cx);
+                    res_slabs(nx, npml, cx, cxe, sl);
+                    int most = 0;
+                    for (auto& b : sl) {
+                        int m = 0;
+                        for (int x = b.first; x < std::min(nx, b.first + RES_WAVES * (b.second ? cxe : cx)); ++x)
+                            m += lists ? cols[s][x] : 0;
+                        most = std::max(most, m);
+                    }
+                    nb[cx].push_back((int)sl.size());
+                    mn[cx].push_back(most);
+                }
+            // best[i]: least time of slots i ..; take[i], width[i]: its first launch
+            std::vector<double> best(gr.ns + 1, 1e30);
+            std::vector<int> take(gr.ns + 1, 0), width(gr.ns + 1, 0);
+            best[gr.ns] = 0.0;
+            for (int i = gr.ns - 1; i >= 0; --i)
+                for (int cx = 1; cx <= RES_CX_MAX; ++cx) {
+                    int blocks = 0, most = 0;
+                    for (int e = i; e < gr.ns; ++e) {
+                        blocks += nb[cx][e];
+                        most = std::max(most, mn[cx][e]);
+                        if (blocks > ncu || res_lds_bytes(kind, bz, cx, most) > kLds) break;
+                        const double t = res_step_us(kind, bz * cx) + best[e + 1];
+                        if (t < best[i]) {
+                            best[i] = t;
+                            take[i] = e + 1 - i;
+                            width[i] = cx;
+                        }
+                    }
+                }
+            if (best[0] >= 1e30) return LSRTM_OK;
+            for (int i = 0; i < gr.ns; i += take[i]) {
+                ResLaunch L;
+                L.cx = width[i];
+                const int cxe = res_cx_edge(L.cx), row = bz * 64;
+                std::vector<ResBlock> blocks;
+                std::vector<int> first(gr.ns + 1, 0);
+                std::vector<std::vector<Rec>> per;
+                std::vector<std::vector<int4>> nodes;
+                std::vector<std::vector<int>> of(gr.ns);   // workgroup of every column
+                for (int s = i; s < i + take[i]; ++s) {
+                    const int nx = gr.h_slots[s].n[1];
+                    res_slabs(nx, npml, L.cx, cxe, sl);
+                    of[s].resize(nx);
+                    for (size_t b = 0; b < sl.size(); ++b) {
+                        const int x1 = b + 1 < sl.size() ? sl[b + 1].first : nx;
+                        for (int x = sl[b].first; x < x1; ++x) of[s][x] = (int)blocks.size();
+                        blocks.push_back({s, sl[b].first,
+                                          (b > 0 ? 1 : 0) | (b + 1 < sl.size() ? 2 : 0) | (sl[b].second ? 4 : 0), 0});
+                    }
+                }
+                L.nblocks = (int)blocks.size();
+                int most = 0;
+                if (kind == R_BG || kind == R_BORN || kind == R_BORN_RC) {
+                    per.resize(blocks.size());
+                    for (const Rec& R : gr.h_rec) {
+                        if (R.slot < i || R.slot >= i + take[i]) continue;
+                        const int ldz = gr.h_slots[R.slot].ldz, x = R.idx / ldz, z = R.idx % ldz;
+                        const int b = of[R.slot][x];
+                        Rec T = R;
+                        T.idx = (x - blocks[b].x0 + HW) * row + (z % bz) * 64 + z / bz;
+                        per[b].push_back(T);
+                    }
+                    std::vector<int> ptr(1, 0);
+                    std::vector<Rec> all;
+                    for (auto& v : per) {
+                        most = std::max(most, (int)v.size());
+                        all.insert(all.end(), v.begin(), v.end());
+                        ptr.push_back((int)all.size());
+                    }
+                    CHK(upload(c, &L.rptr, ptr));
+                    CHK(upload(c, &L.rec, all));
+                }
+                if (kind == R_ADJ) {
+                    nodes.resize(blocks.size());
+                    for (int u = 0; u < gr.nnode; ++u) {
+                        const int s = gr.h_node_slot[u];
+                        if (s < i || s >= i + take[i]) continue;
+                        const int ldz = gr.h_slots[s].ldz, x = gr.h_node_idx[u] / ldz, z = gr.h_node_idx[u] % ldz;
+                        const int b = of[s][x], cw = (blocks[b].nb & 4) ? cxe : L.cx, j = x - blocks[b].x0;
+                        const int owner = (j / cw) * 64 + z / bz, bit = (j % cw) * bz + z % bz;
+                        nodes[b].push_back(make_int4(owner << 8 | bit, gr.h_node_ptr[u], gr.h_node_ptr[u + 1], 0));
+                    }
+                    std::vector<int> ptr(1, 0);
+                    std::vector<int4> all;
+                    for (auto& v : nodes) {
+                        std::sort(v.begin(), v.end(), [](const int4& a, const int4& b) { return a.x < b.x; });
+                        all.insert(all.end(), v.begin(), v.end());
+                        ptr.push_back((int)all.size());
+                        L.maxnodes = most = std::max(most, (int)v.size());
+                    }
+                    CHK(upload(c, &L.nptr, ptr));
+                    CHK(upload(c, &L.node, all));
+                }
+                CHK(upload(c, &L.blocks, blocks));
+                L.lds = res_lds_bytes(kind, bz, L.cx, most);
+                exn = std::max(exn, L.nblocks * res_ex_words(bz, kind == R_BORN ? 2 : 1));
+                gr.res[kind].push_back(L);
+            }
+            rounds = std::max(rounds, gr.res[kind].size());
+        }
+    }
+    c->res_ctln = (int)((2 * c->nseg + 4) * rounds + 1);
+    c->res_exn = exn;
+    CHK(dalloc_t(c, &c->res_ex, exn, true));
+    CHK(dalloc_t(c, &c->res_ctl, c->res_ctln, true));
+    c->res_ok = true;
     return LSRTM_OK;
 }
 
@@ -952,11 +1309,16 @@ lsrtm_status plan(lsrtm_ctx* c) {
         sh.ckbytes = round_up(ck, 256);
     }
 
+    c->fused = nd == 2 && c->opt_fused;
+    // the resident kernels store a column's replay rows in whole waves
+    c->res_bz = res_rows(c);
+    for (auto& W : c->wins)
+        W.segn = c->res_bz ? res_segn(W.npts, W.N[1], c->res_bz) : W.npts;
+
     // ---- memory plan --------------------------------------------------------
     size_t fr = 0, tot = 0;
     HIPCHK(c, hipMemGetInfo(&fr, &tot));
     const long long budget = c->opt_budget_mb > 0 ? c->opt_budget_mb * 1024LL * 1024LL : (long long)(0.9 * fr);
-    c->fused = nd == 2 && c->opt_fused;
     const int nbg = 1 + 3 * nd + (c->fused ? 1 + 2 * nd : 0);   // p, v, psi, phi [, p', v', psi']
     const int nsc = 1 + 3 * nd + (c->fused ? 1 + 3 * nd : 0);   // q, w, xi, eta [, q', w', xi', eta']
     const int nt = c->g.nt;
@@ -981,16 +1343,20 @@ lsrtm_status plan(lsrtm_ctx* c) {
         ckg = mode == 1;
         G = G0;
         for (;;) {
-            long long grp_pts = 0;
+            long long grp_pts = 0, grp_seg = 0;
             {
                 int s = 0;
                 for (int gs : group_sizes(nshot, G)) {
-                    long long cur = 0;
-                    for (int e = 0; e < gs; ++e, ++s) cur += c->wins[c->shots[s].win].npts;
+                    long long cur = 0, seg = 0;
+                    for (int e = 0; e < gs; ++e, ++s) {
+                        cur += c->wins[c->shots[s].win].npts;
+                        seg += c->wins[c->shots[s].win].segn;
+                    }
                     grp_pts = std::max(grp_pts, cur);
+                    grp_seg = std::max(grp_seg, seg);
                 }
             }
-            const long long seg_step = grp_pts * (nd + 1) * 4;
+            const long long seg_step = grp_seg * (nd + 1) * 4;
             const double ck_mem = ckg ? (double)G * max_ck : (double)ck_per_shot_sum;
             if (c->g.ckpt_every > 0) {
                 k = std::min(c->g.ckpt_every, nt);
@@ -1015,18 +1381,22 @@ lsrtm_status plan(lsrtm_ctx* c) {
     // planner chose may shrink, down to half, when the cache then holds more
     // steps; results do not depend on the interval.
     if (c->opt_rcache_mb > 0 && !c->fused && !ckg && c->g.ckpt_every <= 0) {
-        long long grp_pts = 0, all_pts = 0;
+        long long grp_pts = 0, grp_seg = 0, all_seg = 0;
         {
             int s = 0;
             for (int gs : group_sizes(nshot, G)) {
-                long long cur = 0;
-                for (int e = 0; e < gs; ++e, ++s) cur += c->wins[c->shots[s].win].npts;
+                long long cur = 0, seg = 0;
+                for (int e = 0; e < gs; ++e, ++s) {
+                    cur += c->wins[c->shots[s].win].npts;
+                    seg += c->wins[c->shots[s].win].segn;
+                }
                 grp_pts = std::max(grp_pts, cur);
-                all_pts += cur;
+                grp_seg = std::max(grp_seg, seg);
+                all_seg += seg;
             }
         }
-        const long long seg_step = grp_pts * (nd + 1) * 4;   // replay buffer bytes per step
-        const long long step_all = all_pts * (nd + 1) * 4;   // cache bytes per step, all groups
+        const long long seg_step = grp_seg * (nd + 1) * 4;   // replay buffer bytes per step
+        const long long step_all = all_seg * (nd + 1) * 4;   // cache bytes per step, all groups
         auto need_of = [&](int kk) -> long long {
             const int ns = (nt + kk - 1) / kk;
             return fixed + grp_pts * (nbg + nsc + 2) * 4LL + (long long)kk * seg_step +
@@ -1088,7 +1458,10 @@ lsrtm_status plan(lsrtm_ctx* c) {
         gr.ns = gs;
         s0 += gs;
         long long pts = 0;
-        for (int s = gr.s0; s < gr.s0 + gr.ns; ++s) pts += c->wins[c->shots[s].win].npts;
+        for (int s = gr.s0; s < gr.s0 + gr.ns; ++s) {
+            pts += c->wins[c->shots[s].win].npts;
+            gr.segn += c->wins[c->shots[s].win].segn;
+        }
         gr.bg_used = pts * nbg;
         gr.sc_used = pts * nsc;
         gr.img_used = pts * 2;
@@ -1098,10 +1471,7 @@ lsrtm_status plan(lsrtm_ctx* c) {
         c->groups.push_back(gr);
     }
     long long seg_floats = 0;
-    for (auto& gr : c->groups) {
-        long long pts = gr.bg_used / nbg;
-        seg_floats = std::max(seg_floats, (long long)c->k * (nd + 1) * pts);
-    }
+    for (auto& gr : c->groups) seg_floats = std::max(seg_floats, (long long)c->k * (nd + 1) * gr.segn);
     CHK(dalloc_t(c, &c->pool, c->bg_region + c->sc_region + c->img_region, true));
     CHK(dalloc_t(c, &c->segbuf, seg_floats, true));
     // Replay cache: the replays of the last rc_m segments of every group are
@@ -1110,7 +1480,7 @@ lsrtm_status plan(lsrtm_ctx* c) {
     // 2D Born passes.  Two-phase steps with checkpoints held for the whole
     // plan only.
     long long rc_seg = 0;          // floats of one cached segment over all groups
-    for (auto& gr : c->groups) rc_seg += (long long)c->k * (nd + 1) * (gr.bg_used / nbg);
+    for (auto& gr : c->groups) rc_seg += (long long)c->k * (nd + 1) * gr.segn;
     if (c->opt_rcache_mb > 0 && !c->fused && !c->ck_group && rc_seg > 0) {
         const long long cap = std::min(c->opt_rcache_mb * 1024LL * 1024LL, budget - need);
         c->rc_m = (int)std::max(0LL, std::min((long long)c->nseg, cap / (rc_seg * 4)));
@@ -1220,7 +1590,7 @@ lsrtm_status plan(lsrtm_ctx* c) {
             obg += (long long)nbg * W.npts;
             osc += (long long)nsc * W.npts;
             oimg += 2LL * W.npts;
-            oseg += (long long)c->k * (nd + 1) * W.npts;
+            oseg += (long long)c->k * (nd + 1) * W.segn;
             gr.max_npts = std::max(gr.max_npts, W.npts);
             gr.h_slots.push_back(S);
             for (int r = 0; r < sh.nrec; ++r) {
@@ -1240,7 +1610,7 @@ lsrtm_status plan(lsrtm_ctx* c) {
         if (c->rc_m > 0) {
             // cached segment m of this group: its slots' replay buffers at the
             // offsets they have in segbuf, inside block m of the group's range
-            const long long gseg = (long long)c->k * (nd + 1) * (gr.bg_used / nbg);
+            const long long gseg = (long long)c->k * (nd + 1) * gr.segn;
             std::vector<Slot> rc;
             for (int m = 0; m < c->rc_m; ++m)
                 for (const Slot& S0 : gr.h_slots) {
@@ -1293,6 +1663,9 @@ lsrtm_status plan(lsrtm_ctx* c) {
         }
         nptr.push_back((int)nrec.size());
         gr.nnode = (int)nslot.size();
+        gr.h_node_slot = nslot;
+        gr.h_node_idx = nidx;
+        gr.h_node_ptr = nptr;
         CHK(dalloc_t(c, &gr.d_node_slot, std::max<size_t>(1, nslot.size()), true));
         CHK(dalloc_t(c, &gr.d_node_idx, std::max<size_t>(1, nidx.size()), true));
         CHK(dalloc_t(c, &gr.d_node_ptr, nptr.size(), true));
@@ -1304,6 +1677,7 @@ lsrtm_status plan(lsrtm_ctx* c) {
         }
         HIPCHK(c, hipMemcpy(gr.d_node_ptr, nptr.data(), nptr.size() * sizeof(int), hipMemcpyHostToDevice));
     }
+    CHK(plan_resident(c));
     c->have_acq = true;
     CHK(prep_model_windows(c));
     return LSRTM_OK;
@@ -1621,6 +1995,7 @@ lsrtm_status lsrtm_set_option(lsrtm_ctx* c, int key, long long v) {
         return LSRTM_OK;
     }
     case LSRTM_OPT_GRAPH: c->opt_graph = v != 0; return LSRTM_OK;
+    case LSRTM_OPT_RESIDENT: c->opt_res = v != 0; return LSRTM_OK;
     case LSRTM_OPT_TIMING: c->opt_timing = v != 0; return LSRTM_OK;
     case LSRTM_OPT_MEM_BUDGET_MB:
         if (v < 0 || v > kMaxMB) FAIL(c, LSRTM_EINVAL, "memory budget must be in [0, %lld] MB", kMaxMB);
@@ -1771,13 +2146,15 @@ lsrtm_status lsrtm_stats(lsrtm_ctx* c, double* out, int nout) {
 lsrtm_status lsrtm_forward(lsrtm_ctx* c, float* d) {
     CHK(check_ready(c));
     if (!d && c->data_len > 0) FAIL(c, LSRTM_EINVAL, "d is NULL");
-    CHK(pass_begin(c));
-    for (size_t gi = 0; gi < c->groups.size(); ++gi)
-        CHK(run_group(c, c->groups[gi], (int)gi, P_FWD, d, !c->ck_group));
-    CHK(pass_end(c));
-    CHK(check_flag(c));
-    c->ckpt_valid = !c->ck_group;
-    return LSRTM_OK;
+    return run_passes(c, [&]() -> lsrtm_status {
+        CHK(pass_begin(c));
+        for (size_t gi = 0; gi < c->groups.size(); ++gi)
+            CHK(run_group(c, c->groups[gi], (int)gi, P_FWD, d, !c->ck_group));
+        CHK(pass_end(c));
+        CHK(check_flag(c));
+        c->ckpt_valid = !c->ck_group;
+        return LSRTM_OK;
+    });
 }
 
 static lsrtm_status born_impl(lsrtm_ctx* c, const float* dm, float* d) {
@@ -1799,13 +2176,15 @@ static lsrtm_status born_impl(lsrtm_ctx* c, const float* dm, float* d) {
         a.dlnk = W.dlnk;
         HIPCHK(c, launch_dm_prep(a, c->st));
     }
-    const bool write_ck = !c->ckpt_valid && !c->ck_group;
-    for (size_t gi = 0; gi < c->groups.size(); ++gi) CHK(run_group(c, c->groups[gi], (int)gi, P_BORN, d, write_ck));
-    if (write_ck) {
-        CHK(check_flag(c));
-        c->ckpt_valid = true;
-    }
-    return LSRTM_OK;
+    return run_passes(c, [&]() -> lsrtm_status {
+        const bool write_ck = !c->ckpt_valid && !c->ck_group;
+        for (size_t gi = 0; gi < c->groups.size(); ++gi) CHK(run_group(c, c->groups[gi], (int)gi, P_BORN, d, write_ck));
+        if (write_ck) {
+            CHK(check_flag(c));
+            c->ckpt_valid = true;
+        }
+        return LSRTM_OK;
+    });
 }
 
 lsrtm_status lsrtm_born(lsrtm_ctx* c, const float* dm, float* d) {
@@ -1818,13 +2197,16 @@ lsrtm_status lsrtm_born(lsrtm_ctx* c, const float* dm, float* d) {
 }
 
 static lsrtm_status adjoint_impl(lsrtm_ctx* c, const float* d, float* img, int accumulate) {
-    if (!c->ck_group) CHK(ensure_ckpts(c));
-    HIPCHK(c, launch_fill_f64(c->acc64, 2 * c->gpts, c->st));
-    for (size_t gi = 0; gi < c->groups.size(); ++gi) {
-        if (c->ck_group) CHK(run_group(c, c->groups[gi], (int)gi, P_FWDCK, nullptr, true));
-        CHK(run_group(c, c->groups[gi], (int)gi, P_ADJ, const_cast<float*>(d), false));
-    }
-    if (c->ck_group) CHK(check_flag(c));
+    CHK(run_passes(c, [&]() -> lsrtm_status {
+        if (!c->ck_group) CHK(ensure_ckpts(c));
+        HIPCHK(c, launch_fill_f64(c->acc64, 2 * c->gpts, c->st));
+        for (size_t gi = 0; gi < c->groups.size(); ++gi) {
+            if (c->ck_group) CHK(run_group(c, c->groups[gi], (int)gi, P_FWDCK, nullptr, true));
+            CHK(run_group(c, c->groups[gi], (int)gi, P_ADJ, const_cast<float*>(d), false));
+        }
+        if (c->ck_group) CHK(check_flag(c));
+        return LSRTM_OK;
+    }));
     HIPCHK(c, launch_image_store(c->acc64, img, 2 * c->gpts, accumulate, c->st));
     return LSRTM_OK;
 }

@@ -1,0 +1,418 @@
+// Device code shared by the resident 2D kernels (kern2r_fwd.hip, kern2r_adj.hip).
+//
+// Layout of a slab: wave w of a workgroup owns columns w CX .. w CX + CX - 1
+// of its slab; lane l owns rows l BZ .. l BZ + BZ - 1 of each, so a wave spans
+// the whole z extent.  z-neighbours outside the lane come from the next lanes
+// (DPP shifts, zero beyond the wave as the operators define it); x-neighbours
+// from an LDS copy of the slab with the halo columns, [column][row k][lane].
+#pragma once
+#include "resident.h"
+
+namespace lsrtm {
+
+using u64 = unsigned long long;
+
+// The value that lane - 1 / lane + 1 holds; 0 in the first / last lane.
+__device__ __forceinline__ float lane_below(float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x138, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float lane_above(float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x130, 0xf, 0xf, true));
+}
+
+// The staggered differences of the streaming kernels (d_half, d_node) on a
+// window w[i]: both are sum_m c_m (w[i + 4 + m] - w[i + 3 - m]), the window of
+// the half-node derivative starting three nodes below, of the node one four.
+__device__ __forceinline__ float d_win(const float* w, const float* ck) {
+    float r = ck[0] * (w[4] - w[3]);
+    r = fmaf(ck[1], w[5] - w[2], r);
+    r = fmaf(ck[2], w[6] - w[1], r);
+    r = fmaf(ck[3], w[7] - w[0], r);
+    return r;
+}
+
+// e[4 + o] = the column's value o rows above the lane's first row, o = -4 .. BZ + 3.
+template <int BZ>
+__device__ __forceinline__ void col_ext(const float (&f)[BZ], float (&e)[BZ + 8]) {
+#pragma unroll
+    for (int k = 0; k < BZ; ++k) e[4 + k] = f[k];
+#pragma unroll
+    for (int o = 1; o <= 4; ++o) e[4 - o] = lane_below(e[4 - o + BZ]);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) e[4 + BZ + j] = lane_above(e[4 + j]);
+}
+
+// The z-derivative of a column: rows o above / below the lane's own come from
+// the lanes next to it.  HALF = 1: at half nodes (three below, four above),
+// 0: at nodes (four below, three above); the differences of d_win.  Each
+// shifted value is used right after it is formed, so that the shift becomes
+// an operand modifier of the subtraction.
+template <int BZ, int HALF>
+__device__ __forceinline__ void d_col(const float (&f)[BZ], const float* ck, float (&r)[BZ]) {
+    float d[BZ][4];              // d[k][m] = value at k + HALF + m minus value at k + HALF - 1 - m
+    if constexpr (BZ >= 4) {
+#pragma unroll
+        for (int k = 0; k < BZ; ++k)
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                const int u = k + HALF + m, l = k + HALF - 1 - m;
+                if (u < BZ && l >= 0) d[k][m] = f[u] - f[l];
+            }
+#pragma unroll
+        for (int o = 1; o <= 4; ++o) {
+            const float s = lane_below(f[BZ - o]);      // value at -o
+#pragma unroll
+            for (int k = 0; k < BZ; ++k)
+#pragma unroll
+                for (int m = 0; m < 4; ++m)
+                    if (k + HALF - 1 - m == -o && k + HALF + m < BZ) d[k][m] = f[k + HALF + m] - s;
+        }
+#pragma unroll
+        for (int o = 0; o < 4; ++o) {
+            const float s = lane_above(f[o]);           // value at BZ + o
+#pragma unroll
+            for (int k = 0; k < BZ; ++k)
+#pragma unroll
+                for (int m = 0; m < 4; ++m)
+                    if (k + HALF + m == BZ + o && k + HALF - 1 - m >= 0) d[k][m] = s - f[k + HALF - 1 - m];
+        }
+#pragma unroll
+        for (int k = 0; k < BZ; ++k)
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                const int u = k + HALF + m, l = k + HALF - 1 - m;
+                if (u >= BZ && l < 0) d[k][m] = lane_above(f[u - BZ]) - lane_below(f[l + BZ]);
+            }
+#pragma unroll
+        for (int k = 0; k < BZ; ++k) {
+            float v = ck[0] * d[k][0];
+            v = fmaf(ck[1], d[k][1], v);
+            v = fmaf(ck[2], d[k][2], v);
+            r[k] = fmaf(ck[3], d[k][3], v);
+        }
+    } else {
+        float e[BZ + 8];
+        col_ext<BZ>(f, e);
+#pragma unroll
+        for (int k = 0; k < BZ; ++k) r[k] = d_win(e + k + HALF, ck);
+    }
+}
+
+// Keeps the computation of x where it is written: values that are needed in a
+// later phase only would otherwise be computed there, and their operands (the
+// windows of a whole phase) held in registers until then.
+__device__ __forceinline__ void pin(float& x) { asm volatile("" : "+v"(x)); }
+
+__device__ __forceinline__ float uniform(float x) {
+    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
+}
+
+// Where a workgroup stands in its shot's grid, and what a thread owns.
+template <typename G>
+struct ByteOf {
+    using T = gchar;
+};
+template <>
+struct ByteOf<const gfloat> {
+    using T = const gchar;
+};
+template <typename G>
+using Byte = typename ByteOf<G>::T;
+
+template <int BZ, int CX, bool XP>
+struct Place {
+    static constexpr int CW = RES_WAVES * CX;        // slab width
+    static constexpr int LC = CW + 2 * HW;           // columns of an LDS copy: HW halo columns on either side
+    static constexpr int ROW = BZ * 64;              // elements per column
+    int lane, w, j0, x, nz, nx, nv;                  // j0: first own column in the slab, nv: valid rows
+    unsigned ldz;
+    long long segn;                                  // elements of one replay-buffer array of a step
+    bool zp;                                         // the lane holds rows of a z strip
+    int zslot;
+    __device__ __forceinline__ Place(const DSlot& S, const ResBlock& B, int npml) {
+        lane = threadIdx.x & 63;
+        w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        j0 = w * CX;
+        x = B.x0 + j0;
+        nz = S.n[0];
+        nx = S.n[1];
+        ldz = (unsigned)S.ldz;
+        segn = res_segn(S.npts, nx, BZ);
+        nv = nz - lane * BZ;
+        // lanes with rows < npml, then lanes with rows >= nz - npml - 1
+        const int low = (npml + BZ - 1) / BZ, top = max(0, nz - npml - 1) / BZ;
+        zp = npml > 0 && nv > 0 && (lane < low || lane >= top);
+        zslot = lane < low ? lane : lane - max(top, low) + low;
+    }
+    // a slab without strip columns lies inside the grid
+    __device__ __forceinline__ bool col(int c) const { return !XP || x + c < nx; }
+    __device__ __forceinline__ bool ok(int c, int k) const { return col(c) && k < nv; }
+    // Addresses: a base that is uniform over the wave and one lane offset.
+    // Standard layout of a shot's arrays:
+    template <typename G>
+    __device__ __forceinline__ G& at(G* f, int c, int k) const {
+        return *reinterpret_cast<G*>(reinterpret_cast<Byte<G>*>(f + ((long long)(x + c) * ldz + k)) + (unsigned)(lane * (4 * BZ)));
+    }
+    // Replay buffer of a step: [column][row k][lane], so that a wave's accesses
+    // are whole lines and lie a constant apart (lanes past the grid hold zeros).
+    template <typename G>
+    __device__ __forceinline__ G& seg(G* f, int c, int k) const {
+        return *reinterpret_cast<G*>(reinterpret_cast<Byte<G>*>(f + (long long)x * ROW) + (unsigned)(lane * 4) + (c * BZ + k) * 256);
+    }
+    __device__ __forceinline__ float seg_load(const gfloat* f, int c, int k) const {
+        if (XP && !col(c)) return 0.f;
+        return __builtin_nontemporal_load(&seg(f, c, k));
+    }
+    // whole lines, the zeros past the grid included: stores of the 224 bytes of
+    // 56 lanes ran at two thirds of the rate
+    __device__ __forceinline__ void seg_store(gfloat* f, int c, int k, float v) const {
+        if (col(c)) __builtin_nontemporal_store(v, &seg(f, c, k));
+    }
+    __device__ __forceinline__ int lds(int c, int k) const { return (j0 + c) * ROW + k * 64 + lane; }
+    // after the time loop: nothing of the addresses is kept in registers
+    // through it
+    __device__ __forceinline__ void forget() {
+        asm volatile("" : "+v"(lane), "+v"(nv));
+        asm volatile("" : "+s"(x), "+s"(ldz));
+    }
+    // a shot's value at the nearest node inside the grid: loads that no branch
+    // separates
+    template <typename G>
+    __device__ __forceinline__ float near(G* f, int c, int k) const {
+        const int z = min(lane * BZ + k, nz - 1), g = XP ? min(x + c, nx - 1) : x + c;
+        return *reinterpret_cast<G*>(reinterpret_cast<Byte<G>*>(f + (long long)g * ldz) + (unsigned)(z * 4));
+    }
+    __device__ __forceinline__ void get(const gfloat* f, float (&v)[CX][BZ]) const {
+#pragma unroll
+        for (int c = 0; c < CX; ++c)
+#pragma unroll
+            for (int k = 0; k < BZ; ++k) v[c][k] = near(f, c, k);
+#pragma unroll
+        for (int c = 0; c < CX; ++c)
+#pragma unroll
+            for (int k = 0; k < BZ; ++k) v[c][k] = ok(c, k) ? v[c][k] : 0.f;
+    }
+    // the upper neighbours along an axis (0: z, 1: x), zero outside the grid
+    __device__ __forceinline__ void next(const gfloat* f, int axis, float (&v)[CX][BZ]) const {
+#pragma unroll
+        for (int c = 0; c < CX; ++c)
+#pragma unroll
+            for (int k = 0; k < BZ; ++k) {
+                const int z = min(lane * BZ + k + (axis == 0 ? 1 : 0), nz - 1), g = min(x + c + (axis == 1 ? 1 : 0), nx - 1);
+                v[c][k] = *reinterpret_cast<const gfloat*>(reinterpret_cast<const gchar*>(f + (long long)g * ldz) + (unsigned)(z * 4));
+            }
+#pragma unroll
+        for (int c = 0; c < CX; ++c)
+#pragma unroll
+            for (int k = 0; k < BZ; ++k) v[c][k] = ok(c, k) ? v[c][k] : 0.f;
+    }
+    __device__ __forceinline__ void put(gfloat* f, const float (&v)[CX][BZ]) const {
+#pragma unroll
+        for (int c = 0; c < CX; ++c) {
+#pragma unroll
+            for (int k = 0; k < BZ; ++k)
+                if (ok(c, k)) at(f, c, k) = v[c][k];
+        }
+    }
+    // CPML memory of the z axis between global memory and its LDS slots; zero
+    // on a lane's rows outside the strips (global memory holds anything there)
+    __device__ __forceinline__ void get_z(const gfloat* f, float* zm, int npml) const {
+        if (!zp) return;
+#pragma unroll
+        for (int c = 0; c < CX; ++c) {
+#pragma unroll
+            for (int k = 0; k < BZ; ++k) {
+                const float m = near(f, c, k);
+                zm[(c * BZ + k) * RES_ZSLOTS] = ok(c, k) && in_pml(lane * BZ + k, nz, npml) ? m : 0.f;
+            }
+        }
+    }
+    __device__ __forceinline__ void put_z(gfloat* f, const float* zm, int npml) const {
+        if (!zp) return;
+#pragma unroll
+        for (int c = 0; c < CX; ++c) {
+#pragma unroll
+            for (int k = 0; k < BZ; ++k)
+                if (ok(c, k) && in_pml(lane * BZ + k, nz, npml)) at(f, c, k) = zm[(c * BZ + k) * RES_ZSLOTS];
+        }
+    }
+    __device__ __forceinline__ void get_x(const gfloat* f, float (&v)[CX][BZ], int npml) const {
+#pragma unroll
+        for (int c = 0; c < CX; ++c) {
+#pragma unroll
+            for (int k = 0; k < BZ; ++k) {
+                const float m = near(f, c, k);
+                v[c][k] = ok(c, k) && in_pml(x + c, nx, npml) ? m : 0.f;
+            }
+        }
+    }
+    __device__ __forceinline__ void put_x(gfloat* f, const float (&v)[CX][BZ], int npml) const {
+#pragma unroll
+        for (int c = 0; c < CX; ++c) {
+#pragma unroll
+            for (int k = 0; k < BZ; ++k)
+                if (ok(c, k) && in_pml(x + c, nx, npml)) at(f, c, k) = v[c][k];
+        }
+    }
+};
+
+// Every workgroup of the launch is resident, or none of them starts: a
+// workgroup counts itself in and waits for the others; the first one to wait
+// too long (another process or stream holds part of the GPU) turns the count
+// negative, after which every workgroup leaves.  Past this point every wait
+// is for a workgroup that is running.
+__device__ __forceinline__ bool res_admit(const ResArgs& a, int* shared) {
+    if (threadIdx.x == 0) {
+        int ok = 0;
+        if (__hip_atomic_load(a.abort_, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) {
+            const int total = (int)gridDim.x;
+            int v = __hip_atomic_fetch_add(a.ctl, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
+            const long long t0 = wall_clock64();
+            while (v >= 0 && v < total) {
+                if (wall_clock64() - t0 > RES_ADMIT_TICKS &&
+                    __hip_atomic_compare_exchange_strong(a.ctl, &v, -(1 << 30), __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                         __HIP_MEMORY_SCOPE_AGENT)) {
+                    v = -1;
+                    break;
+                }
+                __builtin_amdgcn_s_sleep(2);
+                v = __hip_atomic_load(a.ctl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            ok = v >= 0;
+            if (!ok) __hip_atomic_store(a.abort_, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        *shared = ok;
+    }
+    __syncthreads();
+    const bool ok = *shared != 0;
+    __syncthreads();
+    return ok;
+}
+
+// Exchange of boundary columns.  A published value is one 64-bit word, the
+// float and the tag of its step, stored and loaded whole at device scope, so a
+// reader needs no flag and no fence: it loads the words until every tag
+// matches.  Steps alternate between two buffers: a slab can be at most one
+// exchange ahead of its neighbour, because it needs the neighbour's columns
+// to go on.
+template <int BZ, int NF>
+struct Exchange {
+    u64* ex;                     // of this launch
+    long long per;               // words per workgroup
+    int me, nb;
+    int* abort_;
+    bool in;                     // the lane holds rows of the grid (the others neither publish nor wait)
+    bool dead = false;
+    __device__ __forceinline__ Exchange(const ResArgs& a, int b, int nb_, bool in_)
+        : ex(a.ex), per(res_ex_words(BZ, NF)), me(b), nb(nb_), abort_(a.abort_), in(in_) {}
+    // A column's words: a base that is uniform over the wave, and the lane.
+    __device__ __forceinline__ u64* words(int b, int phase, int par, int side, int f, int col) const {
+        return ex + b * per + ((((((phase * 2 + par) * 2 + side) * NF + f) * RES_EXCOLS) + col) * BZ) * 64;
+    }
+    static __device__ __forceinline__ u64* lane_word(u64* base, int k) {
+        return reinterpret_cast<u64*>(reinterpret_cast<char*>(base + k * 64) + ((threadIdx.x & 63u) << 3));
+    }
+    __device__ __forceinline__ void publish(int phase, int par, int side, int f, int col, const float (&v)[BZ],
+                                            unsigned tag) const {
+        u64* const p = words(me, phase, par, side, f, col);
+        if (!in) return;
+#pragma unroll
+        for (int k = 0; k < BZ; ++k) {
+            unsigned bits;           // a copy: the value itself is not tied to the word's register pair
+            asm volatile("v_mov_b32 %0, %1" : "=v"(bits) : "v"(v[k]));
+            __hip_atomic_store(lane_word(p, k), ((u64)tag << 32) | bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    // Columns col .. col + N - 1 of a neighbour's published side into LDS
+    // (column i, row k at dst[i * BZ * 64 + k * 64]).
+    template <int N>
+    __device__ __forceinline__ void fetch(int from, int phase, int par, int side, int f, int col, float* dst,
+                                          unsigned tag) {
+        u64* const p = words(from, phase, par, side, f, col);
+        if (!in) return;
+        u64 v[N * BZ];
+        long long t0 = 0;
+        for (int it = 1;; ++it) {
+            bool ready = true;
+#pragma unroll
+            for (int k = 0; k < N * BZ; ++k)
+                v[k] = __hip_atomic_load(lane_word(p, k), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+            for (int k = 0; k < N * BZ; ++k) ready = ready && (unsigned)(v[k] >> 32) == tag;
+            if (__all(ready) || dead) break;
+            if ((it & 255) == 0) {
+                const long long now = wall_clock64();
+                if (t0 == 0) t0 = now;
+                if (now - t0 > RES_WAIT_TICKS ||
+                    __hip_atomic_load(abort_, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
+                    // give up: run on without waiting, so that every wave ends
+                    __hip_atomic_store(abort_, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    dead = true;
+                    break;
+                }
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < N * BZ; ++k) dst[k * 64] = __uint_as_float((unsigned)v[k]);
+    }
+    // The halo columns of an LDS copy (HL of them to the left), two to a wave:
+    // the left ones by waves 0 and 1, the right ones by waves 6 and 7.
+    template <int HL, int CW>
+    __device__ __forceinline__ void halo(int w, int phase, int par, int f, float* lds, unsigned tag) {
+        constexpr int HR = RES_HALO - HL, ROW = BZ * 64;
+        float* const l = lds + (threadIdx.x & 63);
+        if (nb & 1) {
+            if (w == 0) fetch<2>(me - 1, phase, par, 1, f, 0, l + (HW - HL) * ROW, tag);
+            if (w == 1) fetch<HL - 2>(me - 1, phase, par, 1, f, 2, l + (HW - HL + 2) * ROW, tag);
+        }
+        if (nb & 2) {
+            if (w == 6) fetch<2>(me + 1, phase, par, 0, f, 0, l + (HW + CW) * ROW, tag);
+            if (w == 7) fetch<HR - 2>(me + 1, phase, par, 0, f, 2, l + (HW + CW + 2) * ROW, tag);
+        }
+    }
+};
+
+// The waves that publish and fetch columns (the outer two on either side) run
+// at a higher priority than the inner wave on their SIMD: they publish early,
+// and the words travel while the inner waves compute.
+__device__ __forceinline__ void res_priority(int w) {
+    if (w < 2 || w >= RES_WAVES - 2) __builtin_amdgcn_s_setprio(2);
+}
+
+// CPML update of a derivative column in the z strips: g += psi with
+// psi = b psi + a g (a lane's rows outside the strips have a = 0, psi = 0).
+template <int BZ>
+__device__ __forceinline__ void pml_z(bool zp, const float (&a)[BZ], const float (&b)[BZ], float* zm, float (&g)[BZ]) {
+    if (!zp) return;
+#pragma unroll
+    for (int k = 0; k < BZ; ++k) {
+        const float ps = fmaf(b[k], zm[k * RES_ZSLOTS], a[k] * g[k]);
+        zm[k * RES_ZSLOTS] = ps;
+        g[k] = g[k] + ps;
+    }
+}
+
+// One coefficient table's rows of the lane.
+template <int BZ>
+__device__ __forceinline__ void zrow(const float* t, float (&v)[BZ]) {
+#pragma unroll
+    for (int k = 0; k < BZ; ++k) v[k] = t[k * 64];
+}
+
+// A receiver of the workgroup, kept in LDS.
+struct LdsRec {
+    long long out;
+    int idx, stride;
+};
+
+// The z axis' coefficient tables (half-node a, b; node a, b) as [4][BZ][64].
+template <int BZ>
+__device__ __forceinline__ void load_ztab(const DSlot& S, float* zt) {
+    const int nz = S.n[0];
+    for (int e = threadIdx.x; e < 4 * BZ * 64; e += RES_NT) {
+        const int t = e / (BZ * 64), k = (e / 64) % BZ, z = (e & 63) * BZ + k;
+        zt[e] = z < nz ? elem(S.cpml[0], (unsigned)(t * nz + z)) : 0.f;
+    }
+}
+
+}  // namespace lsrtm

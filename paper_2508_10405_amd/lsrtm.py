@@ -31,7 +31,7 @@ HEADER = os.path.join(os.path.dirname(_HERE), "include", "lsrtm.h")
 OK, EINVAL, ENOMEM, EHIP, EUNSTABLE, ENONFINITE, ESTATE = 0, -1, -2, -3, -4, -5, -6
 CKPT = {"f32": 0, "f16": 1, "bf16": 2}
 OPT_SHOTS_PER_LAUNCH, OPT_TILE, OPT_GRAPH, OPT_TIMING, OPT_MEM_BUDGET_MB, OPT_CKPT_PER_GROUP, OPT_FUSED, \
-    OPT_PROGRESS, OPT_TILE_V, OPT_TILE_ADJ_A, OPT_REPLAY_CACHE_MB, OPT_GRAPH_CACHE = 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12
+    OPT_PROGRESS, OPT_TILE_V, OPT_TILE_ADJ_A, OPT_REPLAY_CACHE_MB, OPT_GRAPH_CACHE, OPT_RESIDENT = 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13
 NKERNEL = 8
 KERNEL_NAMES = ("born_v", "born_p", "bg_v", "bg_p", "adj_a", "adj_b", "ckpt", "rec")
 

@@ -1,0 +1,87 @@
+"""Resident 2D time stepping (many steps per launch, fields in registers)
+against the streaming kernels: both do the same operations per node, so data,
+images and CGNR iterates agree bit for bit.  Sizes sit at the edges of the
+rows per lane (64 lanes of 2 .. 6 rows), of the slabs (8 waves of 1 .. 3
+columns) and of the exchanged columns; shot counts make the plan pick narrow,
+wide and mixed launches."""
+import numpy as np
+import pytest
+
+from gpu_common import require_gpu, to_dev
+from paper_2508_10405_amd import lsrtm, synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(torch, w, resident, **opts):
+    ctx = lsrtm.context_for(w, tile=1, **opts)
+    ctx.set_option(lsrtm.OPT_RESIDENT, resident)
+    dm = to_dev(torch, w.dm)
+    out = []
+    for _ in range(2):           # the second round reads checkpoints, graphs and cached replays
+        out.append(ctx.forward())
+        out.append(ctx.born(dm))
+        out.append(ctx.adjoint(out[-1]))
+    x, mis = ctx.cgnr(out[1], 2)
+    out += [x, torch.tensor(mis)]
+    ctx.close()
+    return out
+
+
+# (padded nz, padded nx, npml, shots, steps, interval, options)
+CASES = [
+    (28, 7, 3, 2, 20, 7, {}),                    # slabs narrower than a wave's halo
+    (65, 40, 8, 3, 31, 0, {}),                   # two rows per lane, one past 64
+    (128, 64, 6, 40, 24, 10, {}),                # exactly 64 lanes of two rows
+    (129, 130, 13, 3, 40, 16, {"graph": False}),
+    (192, 97, 20, 50, 24, 9, {"ckpt_dtype": "bf16"}),
+    (193, 89, 20, 2, 33, 11, {"ckpt_dtype": "f16"}),
+    (256, 203, 20, 24, 24, 8, {"replay_cache_mb": 600}),
+    (257, 120, 20, 3, 24, 8, {"replay_cache_mb": 4000}),
+    (320, 161, 13, 24, 20, 7, {"ckpt_per_group": True, "shots_per_launch": 5}),
+    (321, 100, 0, 2, 16, 5, {}),                 # no absorbing strips
+    (384, 75, 20, 30, 16, 6, {"shots_per_launch": 7, "replay_cache_mb": 4000}),
+]
+
+
+@pytest.mark.parametrize("nz,nx,npml,nshot,nt,k,opts", CASES)
+def test_bitwise_equal_to_streaming(nz, nx, npml, nshot, nt, k, opts):
+    torch = require_gpu()
+    w = synth.small((nz - 2 * npml, nx - 2 * npml), nt=nt, npml=npml, seed=nz + nx, nshot=nshot, uneven=nshot > 2)
+    a = _run(torch, w, 0, ckpt_every=k, **opts)
+    b = _run(torch, w, 1, ckpt_every=k, **opts)
+    for i, (x, y) in enumerate(zip(a, b)):
+        assert torch.equal(x, y), (i, float((x - y).abs().max()))
+
+
+def test_switching_schedules_on_one_context():
+    """The replay cache is kept in a layout per schedule: switching between
+    them on one context refills it."""
+    torch = require_gpu()
+    w = synth.small((100, 120), nt=40, npml=10, seed=5, nshot=4)
+    ctx = lsrtm.context_for(w, tile=1, ckpt_every=9, replay_cache_mb=2000)
+    dm = to_dev(torch, w.dm)
+    ref = None
+    for resident in (1, 0, 0, 1, 1, 0):
+        ctx.set_option(lsrtm.OPT_RESIDENT, resident)
+        d = ctx.born(dm)
+        got = (d, ctx.adjoint(d), ctx.born(dm))
+        if ref is None:
+            ref = got
+        assert all(torch.equal(x, y) for x, y in zip(got, ref)), resident
+    ctx.close()
+
+
+def test_many_receivers_on_one_slab():
+    """More receivers than threads on a slab, several on one node, and
+    receivers on the first and last node of each axis."""
+    torch = require_gpu()
+    w = synth.small((60, 60), nt=30, npml=6, seed=9, nshot=2)
+    rng = np.random.default_rng(3)
+    full = np.stack(np.meshgrid(np.arange(60), np.arange(20, 36), indexing="ij"), -1).reshape(-1, 2)
+    dup = full[rng.integers(0, len(full), 200)]
+    edge = np.array([[0, 0], [59, 0], [0, 59], [59, 59]])
+    w.rec = [np.concatenate([full, dup, edge]), full[::7]]
+    a, b = _run(torch, w, 0, ckpt_every=8), _run(torch, w, 1, ckpt_every=8)
+    for i, (x, y) in enumerate(zip(a, b)):
+        assert torch.equal(x, y), i
