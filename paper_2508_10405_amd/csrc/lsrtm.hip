@@ -440,11 +440,36 @@ void tile_shape(int ndim, int id, int* bz, int* bx, int* by) {
     }
 }
 
+// Planes of a 3D march of a group: the shape's own number, or fewer where that
+// many would leave the GPU idle.  A launch takes about the planes of one march
+// (a plane is a chain of loads and two barriers) plus the four that filling the
+// y-queues costs, times the rounds in which its blocks find room (three blocks
+// of 256 threads on each of 256 CUs).  Two shots of 60 x 84 x 68 nodes: 66
+// blocks of 32 planes took 39 us per launch; large grids keep their shape's
+// planes, whose queues are refilled least often.
+int march_planes(const Group& gr, int bz, int bx, int by) {
+    constexpr long long room = 768;
+    int best = by;
+    long long least = LLONG_MAX;
+    for (int l = by; l >= 1; l /= 2) {
+        long long blocks = 0;
+        for (const Slot& S : gr.h_slots)
+            blocks += (long long)((S.n[0] + bz - 1) / bz) * ((S.n[1] + bx - 1) / bx) * ((S.n[2] + l - 1) / l);
+        const long long cost = (blocks + room - 1) / room * (l + 4);
+        if (cost < least) {
+            least = cost;
+            best = l;
+        }
+    }
+    return best;
+}
+
 // Tile table of a group: (slot, z0, x0, w) of every tile of every slot; in
 // 3D w = y0 | y1 << 16, the planes y0 .. y1 - 1 of the tile's march.
 void tile_list(const lsrtm_ctx* c, const Group& gr, int tile, std::vector<int4>& t) {
     int bz, bx, by;
     tile_shape(c->ndim, tile, &bz, &bx, &by);
+    if (c->ndim == 3) by = march_planes(gr, bz, bx, by);
     t.clear();
     for (int s = 0; s < gr.ns; ++s) {
         const Slot& S = gr.h_slots[s];
