@@ -128,6 +128,22 @@ struct PsfArgs {
     const float* psf;      // PSF images [2 (scatterer parameter q)][2 (response p)][N]
 };
 hipError_t launch_psf_apply(const PsfArgs& a, const float* x, float* y, int transpose, hipStream_t st);
+// 2D products: tables of the axes' pieces and the packed corner windows.
+struct Psf2Args {
+    int n[2], K[2];        // grid, lattice corners (z, x)
+    int s, W, mono;
+    long long N;
+    const int* tab;        // as in PsfArgs
+    int off[2];
+    const float* psf;
+    float* pack;           // [corner][2 W + 1][2 W + 1][blocks]
+    const int4 *tz, *tx;   // pieces of H^T: (start, length, lower corner, upper corner)
+    const int4 *fz, *fx;   // pieces of H: (start, length, first corner, last corner)
+    int ntz, ntx, nfz, nfx;
+    size_t lds_t, lds_f;   // bytes of x per parameter
+};
+hipError_t launch_psf_pack(const Psf2Args& a, hipStream_t st);
+hipError_t launch_psf2_apply(const Psf2Args& a, const float* x, float* y, int transpose, hipStream_t st);
 hipError_t launch_psf_spikes(const PsfArgs& a, int q, float* dm, hipStream_t st);
 
 // Nonstationary Wiener deblurring (wiener.hip): FFT plans and buffers kept

@@ -182,6 +182,12 @@ struct lsrtm_ctx {
     // PSF Hessian (image domain)
     int* psf_tab = nullptr;        // corner/weight tables of psf_spacing
     int psf_spacing = 0;
+    Psf2Args psf2{};               // 2D products at psf_spacing
+    bool psf2_ok = false;
+    int4* psf_pieces = nullptr;
+    size_t psf_npieces = 0;
+    float* psf_pack = nullptr;
+    long long psf_npack = 0;
     float* psf_dm = nullptr;       // [2][gpts] scatterer model
     float* psf_d = nullptr;        // data of the scatterer model
     float* psf_v[4] = {nullptr, nullptr, nullptr, nullptr};   // image-domain CG: r, z, p, w
@@ -2405,6 +2411,100 @@ lsrtm_status lsrtm_cgnr_state(lsrtm_ctx* c, int get, float* r, float* z, float* 
     return LSRTM_OK;
 }
 
+// Pieces of the axes for the 2D products, and the buffer of packed windows.
+// H^T: the cells of the lattice (the points between two corners; the first and
+// last cell reach to the grid's edges) in pieces of at most 32 rows and of as
+// many columns as give a block of 256 threads two rows each.  H: halves of the
+// corners' intervals from a spacing of 16 on, because a half leaves out a fifth
+// of the taps per axis, else pieces of 10 points, which fill a wave; at most 16.
+static lsrtm_status psf2_setup(lsrtm_ctx* c, const PsfArgs& pa, int s) {
+    c->psf2_ok = false;
+    if (c->ndim != 2 || s < 4) return LSRTM_OK;
+    Psf2Args& a = c->psf2;
+    const int W = pa.W;
+    a.s = s;
+    a.W = W;
+    a.N = pa.N;
+    a.tab = c->psf_tab;
+    std::vector<int4> t[2], f[2];
+    int most_t[2] = {0, 0}, most_f[2] = {0, 0};
+    for (int ax = 0; ax < 2; ++ax) {
+        const int n = pa.n[ax], K = (n - W + s - 1) / s;
+        a.n[ax] = n;
+        a.K[ax] = K;
+        a.off[ax] = pa.off[ax];
+        const int cells = std::max(1, K - 1);
+        const int cap = ax == 0 ? 32 : 2 * NTHREADS / std::max(2, most_t[0] + (most_t[0] & 1));
+        auto cut = [&](std::vector<int4>& v, int lo, int hi, int cap_, int k0, int k1, int& most) {
+            const int m = (hi - lo + cap_ - 1) / cap_;
+            for (int i = 0; i < m; ++i) {
+                const int b0 = lo + (int)((long long)(hi - lo) * i / m), b1 = lo + (int)((long long)(hi - lo) * (i + 1) / m);
+                v.push_back(make_int4(b0, b1 - b0, k0, k1));
+                most = std::max(most, b1 - b0);
+            }
+        };
+        for (int k = 0; k < cells; ++k) {
+            const int lo = k == 0 ? 0 : W + k * s, hi = k == cells - 1 ? n : W + (k + 1) * s;
+            cut(t[ax], lo, hi, cap, k, std::min(k + 1, K - 1), most_t[ax]);
+        }
+        std::vector<int> edge(1, 0);
+        if (s >= 16) {
+            for (int k = 0; k < K; ++k)
+                for (int e : {W + k * s, W + k * s + s / 2})
+                    if (e > edge.back() && e < n) edge.push_back(e);
+        } else {
+            for (int e = 10; e < n; e += 10) edge.push_back(e);
+        }
+        edge.push_back(n);
+        for (size_t i = 0; i + 1 < edge.size(); ++i) cut(f[ax], edge[i], edge[i + 1], 16, 0, 0, most_f[ax]);
+        for (int4& p : f[ax]) {
+            // corners k with a served point in [start - W, start + length - 1 + W]
+            const int j0 = p.x - W, j1 = p.x + p.y - 1 + W;
+            int k0 = 0, k1 = K - 1;
+            while (k0 < K - 1 && W + (k0 + 1) * s - 1 < j0) ++k0;
+            while (k1 > 0 && W + (k1 - 1) * s + 1 > j1) --k1;
+            p.z = k0;
+            p.w = k1;
+        }
+    }
+    a.lds_t = (size_t)(most_t[0] + 2 * W + 1) * (most_t[1] + 2 * W) * sizeof(float);
+    a.lds_f = (size_t)(most_f[0] + 2 * W + 1) * (most_f[1] + 2 * W) * sizeof(float);
+    if (2 * std::max(a.lds_t + 4096, 3 * a.lds_f) > 150 * 1024) return LSRTM_OK;
+    std::vector<int4> all;
+    for (auto* v : {&t[0], &t[1], &f[0], &f[1]}) all.insert(all.end(), v->begin(), v->end());
+    const long long npack = (long long)a.K[0] * a.K[1] * (2 * W + 1) * (2 * W + 1) * 4;
+    for (void** p : {(void**)&c->psf_pieces, (void**)&c->psf_pack}) {
+        const bool big = p == (void**)&c->psf_pack ? npack > c->psf_npack : all.size() > c->psf_npieces;
+        if (!big) continue;
+        if (*p) {
+            (void)hipFree(*p);
+            c->allocs.erase(std::find(c->allocs.begin(), c->allocs.end(), *p));
+            *p = nullptr;
+        }
+        if (p == (void**)&c->psf_pack) {
+            c->psf_npack = 0;
+            CHK(dalloc_t(c, &c->psf_pack, npack, false));
+            c->psf_npack = npack;
+        } else {
+            c->psf_npieces = 0;
+            CHK(dalloc_t(c, &c->psf_pieces, all.size(), false));
+            c->psf_npieces = all.size();
+        }
+    }
+    HIPCHK(c, hipMemcpy(c->psf_pieces, all.data(), all.size() * sizeof(int4), hipMemcpyHostToDevice));
+    a.pack = c->psf_pack;
+    a.tz = c->psf_pieces;
+    a.tx = a.tz + t[0].size();
+    a.fz = a.tx + t[1].size();
+    a.fx = a.fz + f[0].size();
+    a.ntz = (int)t[0].size();
+    a.ntx = (int)t[1].size();
+    a.nfz = (int)f[0].size();
+    a.nfx = (int)f[1].size();
+    c->psf2_ok = true;
+    return LSRTM_OK;
+}
+
 // Corner/weight tables of the interpolated PSF Hessian for a lattice spacing
 // (appendix C): scatterers at W, W + s, ... on every axis, W = (s - 1) / 2;
 // coordinate j lies between corners c0 <= c1 with weight (j - c0) / s,
@@ -2452,8 +2552,31 @@ static lsrtm_status psf_setup(lsrtm_ctx* c, const float* psf, int spacing, int m
             memcpy(&t[2], &wf, sizeof(float));
         }
     }
+    // kernels of earlier calls may still read the tables
+    HIPCHK(c, hipStreamSynchronize(c->st));
     HIPCHK(c, hipMemcpy(c->psf_tab, tab.data(), tab.size() * sizeof(int), hipMemcpyHostToDevice));
+    CHK(psf2_setup(c, *a, spacing));
     c->psf_spacing = spacing;
+    return LSRTM_OK;
+}
+
+// y = H x or H^T x.  In 2D on the packed windows of psf, which the caller packs
+// first (psf2_pack).
+static lsrtm_status psf_product(lsrtm_ctx* c, const PsfArgs& a, const float* x, float* y, int transpose) {
+    if (!c->psf2_ok) {
+        HIPCHK(c, launch_psf_apply(a, x, y, transpose, c->st));
+        return LSRTM_OK;
+    }
+    c->psf2.mono = a.mono;
+    HIPCHK(c, launch_psf2_apply(c->psf2, x, y, transpose, c->st));
+    return LSRTM_OK;
+}
+
+static lsrtm_status psf2_pack(lsrtm_ctx* c, const PsfArgs& a) {
+    if (!c->psf2_ok) return LSRTM_OK;
+    c->psf2.mono = a.mono;
+    c->psf2.psf = a.psf;
+    HIPCHK(c, launch_psf_pack(c->psf2, c->st));
     return LSRTM_OK;
 }
 
@@ -2481,7 +2604,8 @@ lsrtm_status lsrtm_psf_apply(lsrtm_ctx* c, const float* psf, int spacing, int mo
     if (x == y) FAIL(c, LSRTM_EINVAL, "x and y must not alias");
     PsfArgs a;
     CHK(psf_setup(c, psf, spacing, mono, &a));
-    HIPCHK(c, launch_psf_apply(a, x, y, transpose, c->st));
+    CHK(psf2_pack(c, a));
+    CHK(psf_product(c, a, x, y, transpose));
     return LSRTM_OK;
 }
 
@@ -2496,10 +2620,11 @@ lsrtm_status lsrtm_psf_cgnr(lsrtm_ctx* c, const float* psf, int spacing, int mon
     for (int k = 0; k < 4; ++k)
         if (!c->psf_v[k]) CHK(dalloc_t(c, &c->psf_v[k], 2 * c->gpts, false));
     float *r = c->psf_v[0], *z = c->psf_v[1], *p = c->psf_v[2], *w = c->psf_v[3];
+    CHK(psf2_pack(c, a));
     // CGNR on H^T H x = H^T m_rtm (section 3, eq. migdeconobj), x0 = 0
     HIPCHK(c, launch_copy(m_rtm, r, M, c->st));
     HIPCHK(c, launch_fill(x, M, 0.f, c->st));
-    HIPCHK(c, launch_psf_apply(a, r, z, 1, c->st));
+    CHK(psf_product(c, a, r, z, 1));
     HIPCHK(c, launch_copy(z, p, M, c->st));
     double zz, r0;
     CHK(dot_impl(c, z, z, M, &zz));
@@ -2508,14 +2633,14 @@ lsrtm_status lsrtm_psf_cgnr(lsrtm_ctx* c, const float* psf, int spacing, int mon
     if (misfit) misfit[0] = 1.0;
     for (int it = 0; it < niter; ++it) {
         if (zz > 0.0 && r0 > 0.0) {
-            HIPCHK(c, launch_psf_apply(a, p, w, 0, c->st));
+            CHK(psf_product(c, a, p, w, 0));
             double ww;
             CHK(dot_impl(c, w, w, M, &ww));
             if (ww > 0.0) {
                 const double alpha = zz / ww;
                 HIPCHK(c, launch_axpy(alpha, p, x, M, c->st));
                 HIPCHK(c, launch_axpy(-alpha, w, r, M, c->st));
-                HIPCHK(c, launch_psf_apply(a, r, z, 1, c->st));
+                CHK(psf_product(c, a, r, z, 1));
                 double zz1;
                 CHK(dot_impl(c, z, z, M, &zz1));
                 const double beta = zz1 / zz;

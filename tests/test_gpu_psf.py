@@ -11,7 +11,7 @@ import numpy as np
 import pytest
 
 from oracle import lsrtm_oracle as O
-from paper_2508_10405_amd import synth
+from paper_2508_10405_amd import lsrtm, synth
 from gpu_common import f64, oracle_problem, rel, require_gpu, to_dev
 
 pytestmark = pytest.mark.gpu
@@ -133,4 +133,55 @@ def test_psf_errors(torch):
         ctx.psf_apply(psf, 40, x)              # W = 19: no scatterer inside 12 nodes
     with pytest.raises(lsrtm.LsrtmError):
         ctx.psf_apply(psf, 0, x)
+    ctx.close()
+
+
+@pytest.mark.parametrize("mono", [False, True])
+@pytest.mark.parametrize("n,spacing", [((40, 52), 4), ((33, 47), 5), ((61, 40), 15), ((50, 83), 16), ((90, 70), 21),
+                                       ((95, 101), 22), ((23, 120), 41), ((120, 23), 23), ((7, 9), 6)])
+def test_psf_products_by_corner(torch, n, spacing, mono):
+    """The 2D products that sum corner by corner, at spacings on either side of
+    their rules and grids whose first and last cells are cut, against the
+    definition in FP64 (sums of up to (2 W + 1)^2 * 8 terms in FP32: 1e-6)."""
+    nz, nx = n
+    W = (spacing - 1) // 2
+    g = torch.Generator(device="cuda").manual_seed(spacing)
+    ctx = lsrtm.Context(n, (10.0, 10.0), 10, 1e-3)
+    ctx.set_model(torch.full((nx, nz), 7.5, device="cuda"), torch.full((nx, nz), 15.0, device="cuda"))
+    psf = torch.randn((2, 2, nx, nz), generator=g, device="cuda")
+    nb = 1 if mono else 2
+    x = torch.randn((nx, nz) if mono else (2, nx, nz), generator=g, device="cuda")
+    P = psf.double().cpu().numpy()[1:, 1:] if mono else psf.double().cpu().numpy()
+    xd = x.double().cpu().numpy().reshape(nb, nx, nz)
+
+    def axis(m):
+        lat = np.arange(W, m, spacing)
+        j = np.arange(m)
+        k = np.clip((j - W) // spacing, 0, max(len(lat) - 2, 0))
+        c0, c1 = lat[k], lat[np.minimum(k + 1, len(lat) - 1)]
+        w = np.clip((j - c0) / spacing, 0.0, 1.0).astype(np.float32).astype(np.float64) * (c1 > c0)
+        return (c0, 1.0 - w), (c1, w)
+    ax, az = axis(nx), axis(nz)
+    fwd, adj = np.zeros((nb, nx, nz)), np.zeros((nb, nx, nz))
+    jx, jz = np.arange(nx)[:, None], np.arange(nz)[None, :]
+    for ox in range(-W, W + 1):
+        for oz in range(-W, W + 1):
+            tx, tz = jx + ox, jz + oz
+            ok = (tx >= 0) & (tx < nx) & (tz >= 0) & (tz < nz)
+            txc, tzc = np.clip(tx, 0, nx - 1), np.clip(tz, 0, nz - 1)
+            for q in range(nb):
+                for p in range(nb):
+                    h = 0.0
+                    for cx, wx in ax:
+                        for cz, wz in az:
+                            sx, sz = cx[:, None] + ox, cz[None, :] + oz
+                            inn = (sx >= 0) & (sx < nx) & (sz >= 0) & (sz < nz)
+                            h = h + wx[:, None] * wz[None, :] * np.where(
+                                inn, P[q, p][np.clip(sx, 0, nx - 1), np.clip(sz, 0, nz - 1)], 0.0)
+                    h = np.where(ok, h, 0.0)
+                    np.add.at(fwd[p], (txc, tzc), h * xd[q])
+                    adj[q] += h * xd[p][txc, tzc]
+    for ref, tr in ((fwd, False), (adj, True)):
+        y = ctx.psf_apply(psf, spacing, x, transpose=tr, mono=mono).double().cpu().numpy().reshape(nb, nx, nz)
+        assert np.linalg.norm(y - ref) <= 1e-6 * np.linalg.norm(ref), (tr, np.linalg.norm(y - ref) / np.linalg.norm(ref))
     ctx.close()
