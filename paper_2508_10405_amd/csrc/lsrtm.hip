@@ -1095,7 +1095,7 @@ int res_rows(const lsrtm_ctx* c) {
     if (bz > RES_BZ_MAX) return 0;
     for (const Window& W : c->wins) {
         const int lanes = (W.N[0] + bz - 1) / bz, low = (npml + bz - 1) / bz, top = std::max(0, W.N[0] - npml - 1) / bz;
-        if (std::min(low, lanes) + std::max(0, lanes - std::max(top, low)) > RES_ZSLOTS) return 0;
+        if (std::min(low, lanes) + std::max(0, lanes - std::max(top, low)) > RES_ZSLOTS - 1) return 0;
     }
     return bz;
 }
@@ -1117,7 +1117,6 @@ lsrtm_status plan_resident(lsrtm_ctx* c) {
     int dev = 0, ncu = 0;
     HIPCHK(c, hipGetDevice(&dev));
     HIPCHK(c, hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-    constexpr size_t kLds = 160 * 1024 - 64;
     long long exn = 0;
     size_t rounds = 1;
     std::vector<std::pair<int, bool>> sl;
@@ -1161,7 +1160,7 @@ lsrtm_status plan_resident(lsrtm_ctx* c) {
                     for (int e = i; e < gr.ns; ++e) {
                         blocks += nb[cx][e];
                         most = std::max(most, mn[cx][e]);
-                        if (blocks > ncu || res_lds_bytes(kind, bz, cx, most) > kLds) break;
+                        if (blocks > ncu || res_lds_bytes(kind, bz, cx, most) > RES_LDS) break;
                         const double t = res_step_us(kind, bz * cx) + best[e + 1];
                         if (t < best[i]) {
                             best[i] = t;

@@ -14,9 +14,9 @@
 // step then is instruction issue (two waves per SIMD), the latency of two
 // exchanges of boundary columns, and for the replay and adjoint steps the
 // buffer's traffic.  Measured on 120 shots of 280 x 777 padded nodes, a Born
-// pass of 600 steps went from 219 to 109 ms, a migration pass of 500 steps from
-// 298 to 183 ms; on one shot of 140 x 240, 1000 steps, from 8.7 to 5.1 ms and
-// from 17.5 to 8.8 ms, where it is the launches that no longer count.
+// pass of 600 steps went from 219 to 107 ms, a migration pass of 500 steps from
+// 298 to 151 ms; on one shot of 140 x 240, 1000 steps, from 8.7 to 4.3 ms and
+// from 17.6 to 7.6 ms, where it is the launches that no longer count.
 #pragma once
 #include "common.h"
 
@@ -25,7 +25,7 @@ namespace lsrtm {
 constexpr int RES_WAVES = 8;
 constexpr int RES_NT = 64 * RES_WAVES;
 constexpr int RES_HALO = 2 * HW - 1;         // columns of other slabs that a derivative reads
-constexpr int RES_ZSLOTS = 32;               // lanes that may hold rows of the z strips
+constexpr int RES_ZSLOTS = 32;               // LDS slots: lanes that hold rows of the z strips, and one for the others
 constexpr int RES_EXCOLS = 5;                // columns published per side (the adjoint's product takes one more)
 
 enum ResKind {
@@ -85,13 +85,32 @@ constexpr long long res_ex_words(int bz, int nf) { return 2LL * 2 * 2 * nf * RES
 // Columns per wave of a strip slab whose launch's interior slabs have cx: the
 // strips' x memories take the registers of a column.
 constexpr int res_cx_edge(int cx) { return cx > 1 ? cx - 1 : cx; }
-// Dynamic LDS bytes of a workgroup.
-// most: receivers (adjoint: receiver nodes) of the workgroup that has most.
-constexpr size_t res_lds_bytes(int kind, int bz, int cx, int most) {
-    const size_t cw = RES_WAVES * cx, row = (size_t)bz * 64, copy = (cw + 2 * HW) * row;
+// The z strips' memories in registers: where a thread's nodes leave them.
+constexpr bool res_zreg(int kind, int bz, int cx) { return kind <= R_SEG || bz * cx <= (kind == R_BORN ? 6 : 10); }
+// LDS floats of the copies of p and v_x (each with its halo), and of the z
+// strips' tables and memories.
+constexpr size_t res_copy_floats(int bz, int cx) { return (size_t)(RES_WAVES * cx + 2 * HW) * bz * 64; }
+constexpr size_t res_strip_floats(int kind, int bz, int cx) {
     const size_t nf = kind == R_BORN ? 2 : 1;
-    const size_t copies = kind == R_ADJ ? 2 * copy + (cw + 1) * row : (kind == R_BORN ? 1 : 2) * nf * copy;
-    return 4 * (copies + 4 * row + 2 * nf * cw * bz * RES_ZSLOTS + (kind == R_ADJ ? 2 : 4) * (size_t)most);
+    return 4 * (size_t)bz * 64 + (res_zreg(kind, bz, cx) ? 0 : 2 * nf * RES_WAVES * cx * bz * RES_ZSLOTS);
+}
+// The Born step keeps one copy that serves p and v_x in turn (two more
+// barriers) where two do not fit.
+constexpr size_t RES_LDS = 160 * 1024 - 64;
+constexpr bool res_alias(int kind, int bz, int cx) {
+    return kind == R_BORN && 4 * (4 * res_copy_floats(bz, cx) + res_strip_floats(kind, bz, cx)) > RES_LDS - 4096;
+}
+// Dynamic LDS bytes of a workgroup whose interior slabs have cx columns per
+// wave; most: receivers (adjoint: receiver nodes) of the workgroup that has most.
+constexpr size_t res_lds_of(int kind, int bz, int cx, int most) {
+    const size_t copy = res_copy_floats(bz, cx), nf = kind == R_BORN ? 2 : 1;
+    const size_t copies = kind == R_ADJ ? 2 * copy + (size_t)(RES_WAVES * cx + 1) * bz * 64
+                                        : (res_alias(kind, bz, cx) ? 1 : 2) * nf * copy;
+    return 4 * (copies + res_strip_floats(kind, bz, cx) + (kind == R_ADJ ? 2 : 4) * (size_t)most);
+}
+constexpr size_t res_lds_bytes(int kind, int bz, int cx, int most) {
+    const size_t a = res_lds_of(kind, bz, cx, most), b = res_lds_of(kind, bz, res_cx_edge(cx), most);
+    return a > b ? a : b;
 }
 // Instantiated shapes: rows per lane (64 bz >= padded nz) and columns per wave.
 constexpr int RES_BZ_MIN = 2, RES_BZ_MAX = 6, RES_CX_MAX = 3;

@@ -23,11 +23,16 @@ __device__ __forceinline__ void adj_body(const ResArgs& a, const ResBlock& B, fl
     float* const lx = lg + LC * ROW;                 // column j at (j + 1) * ROW
     float* const zt = lx + (CW + 1) * ROW;
     float* const zm = zt + 4 * ROW + (w * CX * BZ) * zs + pl.zslot;
-    constexpr int zmem = RES_WAVES * CX * BZ * zs;
+    constexpr bool ZREG = res_zreg(R_ADJ, BZ, CX);
+    constexpr int zmem = ZREG ? 0 : RES_WAVES * CX * BZ * zs;
+    ZMem<BZ, CX, ZREG> chi, phi;                     // chi_z, phi~_z
+    chi.l = zm;
+    phi.l = zm + zmem;
     float* const inj = zt + 4 * ROW + 2 * zmem;
     const float *zah = zt + lane, *zbh = zah + ROW, *zan = zbh + ROW, *zbn = zan + ROW;
-    for (int e = threadIdx.x; e < (2 * LC + CW + 1) * ROW; e += RES_NT) lds[e] = 0.f;
-    load_ztab<BZ>(S, zt);
+    for (int e = threadIdx.x; e < (2 * LC + CW + 1 + 4) * ROW + 2 * zmem; e += RES_NT) lds[e] = 0.f;
+    __syncthreads();
+    load_ztab<BZ, true>(S, zt);
     __syncthreads();
 
     float Q[CX][BZ], uz[CX][BZ], ux[CX][BZ], gk[CX][BZ], gr[CX][BZ];
@@ -39,8 +44,8 @@ __device__ __forceinline__ void adj_body(const ResArgs& a, const ResBlock& B, fl
     pl.get(S.gk, gk);
     pl.get(S.gr, gr);
     pl.get(S.kdt, kd);
-    pl.get_z(S.xi[0], zm, a.npml);
-    pl.get_z(S.eta[0], zm + zmem, a.npml);
+    chi.load(pl, S.xi[0], a.npml);
+    phi.load(pl, S.eta[0], a.npml);
     if constexpr (XP) {
         pl.get_x(S.xi[1], mc, a.npml);
         pl.get_x(S.eta[1], mf, a.npml);
@@ -186,12 +191,11 @@ __device__ __forceinline__ void adj_body(const ResArgs& a, const ResBlock& B, fl
             float e[BZ], dd[BZ];
 #pragma unroll
             for (int k = 0; k < BZ; ++k) e[k] = Q[c][k];
-            if (pl.zp) {
-                float *chi = zm + c * BZ * zs, *phi = chi + zmem;
+            {
 #pragma unroll
                 for (int k = 0; k < BZ; ++k) {
-                    e[k] = e[k] + tn[k] * (phi[k * zs] + e[k]);
-                    if (!skip) chi[k * zs] = th[k] != 0.f ? tb[k] * (chi[k * zs] + uz[c][k]) : 0.f;
+                    e[k] = e[k] + tn[k] * (phi.get(c, k) + e[k]);
+                    if (!skip) chi.set(c, k, tb[k] * (chi.get(c, k) + uz[c][k]));
                 }
             }
             d_col<BZ, 1>(e, a.C.c[0], dd);
@@ -203,7 +207,7 @@ __device__ __forceinline__ void adj_body(const ResArgs& a, const ResBlock& B, fl
                 pin(gk[c][k]);
             }
         }
-        X.template halo<HE, CW>(w, 0, par, 0, le, tag);
+        X.template halo<HE, CW, 1>(w, 0, par, 0, le, 0, tag);
         __syncthreads();
         if (n < a.n1 - 1) load_z(n);
         // ---- phase A, x
@@ -252,12 +256,11 @@ __device__ __forceinline__ void adj_body(const ResArgs& a, const ResBlock& B, fl
                 g[k] = uz[c][k];
                 x[k] = -sz[c][k] * uz[c][k];
             }
-            if (pl.zp) {
-                float *chi = zm + c * BZ * zs, *phi = chi + zmem;
+            {
 #pragma unroll
                 for (int k = 0; k < BZ; ++k) {
-                    g[k] = g[k] + th[k] * (chi[k * zs] + g[k]);
-                    phi[k * zs] = tn[k] != 0.f ? tb[k] * (phi[k * zs] + Q[c][k]) : 0.f;
+                    g[k] = g[k] + th[k] * (chi.get(c, k) + g[k]);
+                    phi.set(c, k, tb[k] * (phi.get(c, k) + Q[c][k]));
                 }
             }
             d_col<BZ, 0>(g, a.C.c[0], dz[c]);
@@ -272,8 +275,8 @@ __device__ __forceinline__ void adj_body(const ResArgs& a, const ResBlock& B, fl
                 pin(sz[c][k]);
             }
         }
-        X.template halo<HG, CW>(w, 1, par, 0, lg, tag);
-        if (w == 1 && (B.nb & 1)) X.template fetch<1>(X.me - 1, 1, par, 1, 0, HG, lx + lane, tag);
+        X.template halo<HG, CW, 1>(w, 1, par, 0, lg, 0, tag);
+        if (w == 2 && (B.nb & 1)) X.template fetch<1>(X.me - 1, 1, par, 1, 0, HG, lx + lane, 0, tag);
         __syncthreads();
         if (n > a.n0) load_seg(n - 1);
         // ---- phase B, x
@@ -317,8 +320,8 @@ __device__ __forceinline__ void adj_body(const ResArgs& a, const ResBlock& B, fl
     pl.put(S.w[1], ux);
     pl.put(S.gk, gk);
     pl.put(S.gr, gr);
-    pl.put_z(S.xi[0], zm, a.npml);
-    pl.put_z(S.eta[0], zm + zmem, a.npml);
+    chi.store(pl, S.xi[0], a.npml);
+    phi.store(pl, S.eta[0], a.npml);
     if constexpr (XP) {
         pl.put_x(S.xi[1], mc, a.npml);
         pl.put_x(S.eta[1], mf, a.npml);

@@ -142,7 +142,7 @@ struct Place {
         // lanes with rows < npml, then lanes with rows >= nz - npml - 1
         const int low = (npml + BZ - 1) / BZ, top = max(0, nz - npml - 1) / BZ;
         zp = npml > 0 && nv > 0 && (lane < low || lane >= top);
-        zslot = lane < low ? lane : lane - max(top, low) + low;
+        zslot = !zp ? RES_ZSLOTS - 1 : lane < low ? lane : lane - max(top, low) + low;
     }
     // a slab without strip columns lies inside the grid
     __device__ __forceinline__ bool col(int c) const { return !XP || x + c < nx; }
@@ -212,28 +212,6 @@ struct Place {
 #pragma unroll
             for (int k = 0; k < BZ; ++k)
                 if (ok(c, k)) at(f, c, k) = v[c][k];
-        }
-    }
-    // CPML memory of the z axis between global memory and its LDS slots; zero
-    // on a lane's rows outside the strips (global memory holds anything there)
-    __device__ __forceinline__ void get_z(const gfloat* f, float* zm, int npml) const {
-        if (!zp) return;
-#pragma unroll
-        for (int c = 0; c < CX; ++c) {
-#pragma unroll
-            for (int k = 0; k < BZ; ++k) {
-                const float m = near(f, c, k);
-                zm[(c * BZ + k) * RES_ZSLOTS] = ok(c, k) && in_pml(lane * BZ + k, nz, npml) ? m : 0.f;
-            }
-        }
-    }
-    __device__ __forceinline__ void put_z(gfloat* f, const float* zm, int npml) const {
-        if (!zp) return;
-#pragma unroll
-        for (int c = 0; c < CX; ++c) {
-#pragma unroll
-            for (int k = 0; k < BZ; ++k)
-                if (ok(c, k) && in_pml(lane * BZ + k, nz, npml)) at(f, c, k) = zm[(c * BZ + k) * RES_ZSLOTS];
         }
     }
     __device__ __forceinline__ void get_x(const gfloat* f, float (&v)[CX][BZ], int npml) const {
@@ -323,23 +301,28 @@ struct Exchange {
             __hip_atomic_store(lane_word(p, k), ((u64)tag << 32) | bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
-    // Columns col .. col + N - 1 of a neighbour's published side into LDS
-    // (column i, row k at dst[i * BZ * 64 + k * 64]).
-    template <int N>
+    // Columns col .. col + N - 1 of a neighbour's published side, fields f ..
+    // f + F - 1, into LDS (field g, column i, row k at dst[g * stride + i * BZ *
+    // 64 + k * 64]); all words are loaded before any is waited for.
+    template <int N, int F = 1>
     __device__ __forceinline__ void fetch(int from, int phase, int par, int side, int f, int col, float* dst,
-                                          unsigned tag) {
-        u64* const p = words(from, phase, par, side, f, col);
-        if (!in) return;
-        u64 v[N * BZ];
+                                          int stride, unsigned tag) {
+        u64 v[F][N * BZ];
         long long t0 = 0;
         for (int it = 1;; ++it) {
-            bool ready = true;
+            unsigned differ = 0;
 #pragma unroll
-            for (int k = 0; k < N * BZ; ++k)
-                v[k] = __hip_atomic_load(lane_word(p, k), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (int g = 0; g < F; ++g) {
+                u64* const p = words(from, phase, par, side, f + g, col);
 #pragma unroll
-            for (int k = 0; k < N * BZ; ++k) ready = ready && (unsigned)(v[k] >> 32) == tag;
-            if (__all(ready) || dead) break;
+                for (int k = 0; k < N * BZ; ++k)
+                    v[g][k] = __hip_atomic_load(lane_word(p, k), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+#pragma unroll
+            for (int g = 0; g < F; ++g)
+#pragma unroll
+                for (int k = 0; k < N * BZ; ++k) differ |= (unsigned)(v[g][k] >> 32) ^ tag;
+            if (__all(differ == 0 || !in) || dead) break;
             if ((it & 255) == 0) {
                 const long long now = wall_clock64();
                 if (t0 == 0) t0 = now;
@@ -352,22 +335,35 @@ struct Exchange {
                 }
             }
         }
+        if (in)
 #pragma unroll
-        for (int k = 0; k < N * BZ; ++k) dst[k * 64] = __uint_as_float((unsigned)v[k]);
+            for (int g = 0; g < F; ++g)
+#pragma unroll
+                for (int k = 0; k < N * BZ; ++k) dst[g * stride + k * 64] = __uint_as_float((unsigned)v[g][k]);
     }
     // The halo columns of an LDS copy (HL of them to the left), two to a wave:
     // the left ones by waves 0 and 1, the right ones by waves 6 and 7.
-    template <int HL, int CW>
-    __device__ __forceinline__ void halo(int w, int phase, int par, int f, float* lds, unsigned tag) {
+    template <int HL, int CW, int F>
+    __device__ __forceinline__ void halo(int w, int phase, int par, int f, float* lds, int stride, unsigned tag) {
         constexpr int HR = RES_HALO - HL, ROW = BZ * 64;
         float* const l = lds + (threadIdx.x & 63);
         if (nb & 1) {
-            if (w == 0) fetch<2>(me - 1, phase, par, 1, f, 0, l + (HW - HL) * ROW, tag);
-            if (w == 1) fetch<HL - 2>(me - 1, phase, par, 1, f, 2, l + (HW - HL + 2) * ROW, tag);
+            if (w == 0) fetch<2, F>(me - 1, phase, par, 1, f, 0, l + (HW - HL) * ROW, stride, tag);
+            if (w == 1) fetch<HL - 2, F>(me - 1, phase, par, 1, f, 2, l + (HW - HL + 2) * ROW, stride, tag);
         }
         if (nb & 2) {
-            if (w == 6) fetch<2>(me + 1, phase, par, 0, f, 0, l + (HW + CW) * ROW, tag);
-            if (w == 7) fetch<HR - 2>(me + 1, phase, par, 0, f, 2, l + (HW + CW + 2) * ROW, tag);
+            if (w == 6) fetch<2, F>(me + 1, phase, par, 0, f, 0, l + (HW + CW) * ROW, stride, tag);
+            if (w == 7) fetch<HR - 2, F>(me + 1, phase, par, 0, f, 2, l + (HW + CW + 2) * ROW, stride, tag);
+        }
+    }
+    // every field of an exchange: together where registers allow, else one by one
+    template <int HL, int CW, bool TOGETHER>
+    __device__ __forceinline__ void halos(int w, int phase, int par, float* lds, int stride, unsigned tag) {
+        if constexpr (TOGETHER) {
+            halo<HL, CW, NF>(w, phase, par, 0, lds, stride, tag);
+        } else {
+#pragma unroll
+            for (int f = 0; f < NF; ++f) halo<HL, CW, 1>(w, phase, par, f, lds + f * stride, 0, tag);
         }
     }
 };
@@ -379,18 +375,52 @@ __device__ __forceinline__ void res_priority(int w) {
     if (w < 2 || w >= RES_WAVES - 2) __builtin_amdgcn_s_setprio(2);
 }
 
-// CPML update of a derivative column in the z strips: g += psi with
-// psi = b psi + a g (a lane's rows outside the strips have a = 0, psi = 0).
-template <int BZ>
-__device__ __forceinline__ void pml_z(bool zp, const float (&a)[BZ], const float (&b)[BZ], float* zm, float (&g)[BZ]) {
-    if (!zp) return;
-#pragma unroll
-    for (int k = 0; k < BZ; ++k) {
-        const float ps = fmaf(b[k], zm[k * RES_ZSLOTS], a[k] * g[k]);
-        zm[k * RES_ZSLOTS] = ps;
-        g[k] = g[k] + ps;
+// CPML memories of the z strips: in registers where they are to spare, or in
+// LDS slots of the lanes that hold strip rows (the other lanes share one slot of
+// zeros).  Every lane does the arithmetic, with zero coefficients outside the
+// strips: a branch around it put the wave's outstanding memory accesses in front
+// of it (a replay step of 7 shots of 280 x 777 took 8.6 us with the branch, 5.6
+// without).
+template <int BZ, int CX, bool REG>
+struct ZMem {
+    float r[REG ? CX : 1][REG ? BZ : 1];
+    float* l;                    // the lane's slots
+    __device__ __forceinline__ float get(int c, int k) const { return REG ? r[REG ? c : 0][REG ? k : 0] : l[(c * BZ + k) * RES_ZSLOTS]; }
+    __device__ __forceinline__ void set(int c, int k, float v) {
+        if (REG) r[REG ? c : 0][REG ? k : 0] = v;
+        else l[(c * BZ + k) * RES_ZSLOTS] = v;
     }
-}
+    // g += psi with psi = b psi + a g (a lane's rows outside the strips have
+    // a = 0, psi = 0)
+    __device__ __forceinline__ void step(const float (&a)[BZ], const float (&b)[BZ], int c, float (&g)[BZ]) {
+#pragma unroll
+        for (int k = 0; k < BZ; ++k) {
+            const float ps = fmaf(b[k], get(c, k), a[k] * g[k]);
+            set(c, k, ps);
+            g[k] = g[k] + ps;
+        }
+    }
+    template <typename P>
+    __device__ __forceinline__ void load(const P& pl, const gfloat* f, int npml) {
+#pragma unroll
+        for (int c = 0; c < CX; ++c)
+#pragma unroll
+            for (int k = 0; k < BZ; ++k) {
+                // zero outside the strips (global memory holds anything there)
+                const float m = pl.near(f, c, k);
+                set(c, k, pl.ok(c, k) && in_pml(pl.lane * BZ + k, pl.nz, npml) ? m : 0.f);
+            }
+    }
+    template <typename P>
+    __device__ __forceinline__ void store(const P& pl, gfloat* f, int npml) const {
+        if (!pl.zp) return;
+#pragma unroll
+        for (int c = 0; c < CX; ++c)
+#pragma unroll
+            for (int k = 0; k < BZ; ++k)
+                if (pl.ok(c, k) && in_pml(pl.lane * BZ + k, pl.nz, npml)) pl.at(f, c, k) = get(c, k);
+    }
+};
 
 // One coefficient table's rows of the lane.
 template <int BZ>
@@ -406,12 +436,16 @@ struct LdsRec {
 };
 
 // The z axis' coefficient tables (half-node a, b; node a, b) as [4][BZ][64].
-template <int BZ>
+// ADJ: b = 0 outside the strips, where the adjoint has no memory (its memories
+// take in the field itself, not a times it).
+template <int BZ, bool ADJ = false>
 __device__ __forceinline__ void load_ztab(const DSlot& S, float* zt) {
     const int nz = S.n[0];
     for (int e = threadIdx.x; e < 4 * BZ * 64; e += RES_NT) {
         const int t = e / (BZ * 64), k = (e / 64) % BZ, z = (e & 63) * BZ + k;
-        zt[e] = z < nz ? elem(S.cpml[0], (unsigned)(t * nz + z)) : 0.f;
+        float v = z < nz ? elem(S.cpml[0], (unsigned)(t * nz + z)) : 0.f;
+        if (ADJ && (t & 1) && z < nz && elem(S.cpml[0], (unsigned)((t - 1) * nz + z)) == 0.f) v = 0.f;
+        zt[e] = v;
     }
 }
 

@@ -13,8 +13,9 @@ __device__ __forceinline__ void fwd_body(const ResArgs& a, const ResBlock& B, fl
     constexpr bool BG = KIND != R_BORN_RC, SC = KIND == R_BORN || KIND == R_BORN_RC, RC = KIND == R_BORN_RC;
     constexpr bool SEGW = KIND == R_SEG;
     constexpr int NF = (BG ? 1 : 0) + (SC ? 1 : 0), IS = BG ? 1 : 0;   // IS: index of the scattered field
-    constexpr bool ALIAS = KIND == R_BORN;           // one LDS copy serves p and v_x in turn
-    constexpr bool TIGHT = KIND >= R_BORN && BZ * CX > 10;   // keep the scheduler from running out of registers
+    constexpr bool ALIAS = res_alias(KIND, BZ, CX);  // one LDS copy serves p and v_x in turn
+    constexpr bool ZREG = res_zreg(KIND, BZ, CX);
+    constexpr bool TIGHT = KIND >= R_BORN && BZ * CX > (KIND == R_BORN ? 6 : 10);   // keep the scheduler from running out of registers
     constexpr int CW = P::CW, LC = P::LC, ROW = P::ROW, HP = HW - 1, HV = HW;
     const DSlot& S = a.slots[B.slot];
     P pl(S, B, a.npml);
@@ -25,9 +26,13 @@ __device__ __forceinline__ void fwd_body(const ResArgs& a, const ResBlock& B, fl
     float* const lv = ALIAS ? lds : lds + NF * LC * ROW;
     float* const zt = lds + (ALIAS ? 1 : 2) * NF * LC * ROW;
     float* const zm = zt + 4 * ROW + (w * CX * BZ) * zs + pl.zslot;
-    constexpr int zmem = RES_WAVES * CX * BZ * zs;       // one memory of the workgroup
+    constexpr int zmem = ZREG ? 0 : RES_WAVES * CX * BZ * zs;   // one memory of the workgroup
+    ZMem<BZ, CX, ZREG> mz[2 * NF];                       // psi_z, phi_z (background), xi_z, eta_z
+#pragma unroll
+    for (int m = 0; m < 2 * NF; ++m) mz[m].l = zm + m * zmem;
     const float *zah = zt + lane, *zbh = zah + ROW, *zan = zbh + ROW, *zbn = zan + ROW;
-    for (int e = threadIdx.x; e < (ALIAS ? 1 : 2) * NF * LC * ROW; e += RES_NT) lds[e] = 0.f;
+    for (int e = threadIdx.x; e < (ALIAS ? 1 : 2) * NF * LC * ROW + 4 * ROW + 2 * NF * zmem; e += RES_NT) lds[e] = 0.f;
+    __syncthreads();
     load_ztab<BZ>(S, zt);
     __syncthreads();
 
@@ -41,8 +46,8 @@ __device__ __forceinline__ void fwd_body(const ResArgs& a, const ResBlock& B, fl
         pl.get(S.p, p);
         pl.get(S.v[0], vz);
         pl.get(S.v[1], vx);
-        pl.get_z(S.psi[0], zm, a.npml);
-        pl.get_z(S.phi[0], zm + zmem, a.npml);
+        mz[0].load(pl, S.psi[0], a.npml);
+        mz[1].load(pl, S.phi[0], a.npml);
         if constexpr (XP) {
             pl.get_x(S.psi[1], mv, a.npml);
             pl.get_x(S.phi[1], mp, a.npml);
@@ -53,8 +58,8 @@ __device__ __forceinline__ void fwd_body(const ResArgs& a, const ResBlock& B, fl
         pl.get(S.w[0], wz);
         pl.get(S.w[1], wx);
         pl.get(S.dlnk, lk);
-        pl.get_z(S.xi[0], zm + 2 * IS * zmem, a.npml);
-        pl.get_z(S.eta[0], zm + (2 * IS + 1) * zmem, a.npml);
+        mz[2 * IS].load(pl, S.xi[0], a.npml);
+        mz[2 * IS + 1].load(pl, S.eta[0], a.npml);
         if constexpr (XP) {
             pl.get_x(S.xi[1], nv_, a.npml);
             pl.get_x(S.eta[1], np, a.npml);
@@ -170,7 +175,7 @@ __device__ __forceinline__ void fwd_body(const ResArgs& a, const ResBlock& B, fl
             float g[BZ], dv[BZ];
             if constexpr (BG) {
                 d_col<BZ, 1>(p[c], a.C.c[0], g);
-                pml_z<BZ>(pl.zp, ta, tb, zm + c * BZ * zs, g);
+                mz[0].step(ta, tb, c, g);
 #pragma unroll
                 for (int k = 0; k < BZ; ++k) {
                     dv[k] = -bz[c][k] * g[k];
@@ -184,7 +189,7 @@ __device__ __forceinline__ void fwd_body(const ResArgs& a, const ResBlock& B, fl
             }
             if constexpr (SC) {
                 d_col<BZ, 1>(q[c], a.C.c[0], g);
-                pml_z<BZ>(pl.zp, ta, tb, zm + 2 * IS * zmem + c * BZ * zs, g);
+                mz[2 * IS].step(ta, tb, c, g);
 #pragma unroll
                 for (int k = 0; k < BZ; ++k) {
                     wz[c][k] = (wz[c][k] - bz[c][k] * g[k]) - rz[c][k] * dv[k];
@@ -192,8 +197,7 @@ __device__ __forceinline__ void fwd_body(const ResArgs& a, const ResBlock& B, fl
                 }
             }
         }
-#pragma unroll
-        for (int f = 0; f < NF; ++f) X.template halo<HP, CW>(w, 0, par, f, lp + f * LC * ROW, tag);
+        X.template halos<HP, CW, !TIGHT>(w, 0, par, lp, LC * ROW, tag);
         __syncthreads();
         // loads from the replay cache start right after a fetch, so that the
         // next fetch does not wait behind them
@@ -255,19 +259,18 @@ __device__ __forceinline__ void fwd_body(const ResArgs& a, const ResBlock& B, fl
             if (TIGHT) __builtin_amdgcn_sched_barrier(0);
             if constexpr (BG) {
                 d_col<BZ, 0>(vz[c], a.C.c[0], ez[c]);
-                pml_z<BZ>(pl.zp, ta, tb, zm + zmem + c * BZ * zs, ez[c]);
+                mz[1].step(ta, tb, c, ez[c]);
 #pragma unroll
                 for (int k = 0; k < BZ; ++k) pin(ez[c][k]);
             }
             if constexpr (SC) {
                 d_col<BZ, 0>(wz[c], a.C.c[0], fz[c]);
-                pml_z<BZ>(pl.zp, ta, tb, zm + (2 * IS + 1) * zmem + c * BZ * zs, fz[c]);
+                mz[2 * IS + 1].step(ta, tb, c, fz[c]);
 #pragma unroll
                 for (int k = 0; k < BZ; ++k) pin(fz[c][k]);
             }
         }
-#pragma unroll
-        for (int f = 0; f < NF; ++f) X.template halo<HV, CW>(w, 1, par, f, lv + f * LC * ROW, tag);
+        X.template halos<HV, CW, !TIGHT>(w, 1, par, lv, LC * ROW, tag);
         __syncthreads();
         if constexpr (RC)
             if (n + 1 < a.n1) {
@@ -338,8 +341,8 @@ __device__ __forceinline__ void fwd_body(const ResArgs& a, const ResBlock& B, fl
         pl.put(S.p, p);
         pl.put(S.v[0], vz);
         pl.put(S.v[1], vx);
-        pl.put_z(S.psi[0], zm, a.npml);
-        pl.put_z(S.phi[0], zm + zmem, a.npml);
+        mz[0].store(pl, S.psi[0], a.npml);
+        mz[1].store(pl, S.phi[0], a.npml);
         if constexpr (XP) {
             pl.put_x(S.psi[1], mv, a.npml);
             pl.put_x(S.phi[1], mp, a.npml);
@@ -349,8 +352,8 @@ __device__ __forceinline__ void fwd_body(const ResArgs& a, const ResBlock& B, fl
         pl.put(S.q, q);
         pl.put(S.w[0], wz);
         pl.put(S.w[1], wx);
-        pl.put_z(S.xi[0], zm + 2 * IS * zmem, a.npml);
-        pl.put_z(S.eta[0], zm + (2 * IS + 1) * zmem, a.npml);
+        mz[2 * IS].store(pl, S.xi[0], a.npml);
+        mz[2 * IS + 1].store(pl, S.eta[0], a.npml);
         if constexpr (XP) {
             pl.put_x(S.xi[1], nv_, a.npml);
             pl.put_x(S.eta[1], np, a.npml);
