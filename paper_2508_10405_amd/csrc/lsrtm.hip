@@ -29,6 +29,7 @@
 #include <list>
 #include <map>
 #include <mutex>
+#include <numeric>
 #include <string>
 #include <vector>
 
@@ -70,11 +71,10 @@ struct ShotInfo {
 struct ResLaunch {
     int cx = 1, nblocks = 0, maxnodes = 0;
     size_t lds = 0;
-    ResBlock* blocks = nullptr;
-    int* rptr = nullptr;           // receivers by workgroup (recording kinds)
-    Rec* rec = nullptr;
-    int* nptr = nullptr;           // receiver nodes by workgroup (adjoint)
-    int4* node = nullptr;
+    // tables, as offsets in the plan's block of them
+    size_t blocks = 0;
+    size_t rptr = 0, rec = 0;      // receivers by workgroup (recording kinds)
+    size_t nptr = 0, node = 0;     // receiver nodes by workgroup (adjoint)
 };
 
 struct Group {
@@ -209,6 +209,7 @@ struct lsrtm_ctx {
     bool res_ok = false;           // the plan's windows fit
     bool res_on = false;           // passes run on it (replay-cache layout too)
     int res_bz = 0;
+    char* res_tab = nullptr;       // tables of the resident launches
     unsigned long long* res_ex = nullptr;   // exchange words
     long long res_exn = 0;
     int* res_ctl = nullptr;        // [0] gave up, [1 + i] arrivals of launch i of a group's pass
@@ -316,6 +317,7 @@ void free_acq(lsrtm_ctx* c) {
     c->cg_active = false;
     c->src_amp = nullptr;
     c->res_ok = false;
+    c->res_tab = nullptr;
     c->res_ex = nullptr;
     c->res_ctl = nullptr;
 }
@@ -659,19 +661,19 @@ lsrtm_status res_run(lsrtm_ctx* c, Group& gr, int kind, const Slot* sl, int n0, 
         if (c->res_launch + 1 >= c->res_ctln) FAIL(c, LSRTM_EHIP, "more resident launches than planned");
         ResArgs a;
         a.slots = dev_slots(sl);
-        a.blocks = L.blocks;
+        a.blocks = reinterpret_cast<const ResBlock*>(c->res_tab + L.blocks);
         a.C = c->C;
         a.n0 = n0;
         a.n1 = n1;
         a.sstep0 = sstep0;
         a.first = first;
         a.npml = c->g.npml;
-        a.rptr = d ? L.rptr : nullptr;
-        a.rec = kind == R_ADJ ? gr.d_node_rec : L.rec;
+        a.rptr = d ? reinterpret_cast<const int*>(c->res_tab + L.rptr) : nullptr;
+        a.rec = kind == R_ADJ ? gr.d_node_rec : reinterpret_cast<const Rec*>(c->res_tab + L.rec);
         a.d = d;
         a.y = y;
-        a.nptr = L.nptr;
-        a.node = L.node;
+        a.nptr = reinterpret_cast<const int*>(c->res_tab + L.nptr);
+        a.node = reinterpret_cast<const int4*>(c->res_tab + L.node);
         a.maxnodes = L.maxnodes;
         a.ex = c->res_ex;
         a.tag0 = c->res_tag;
@@ -1077,11 +1079,13 @@ void res_slabs(int nx, int npml, int cx, int cxe, std::vector<std::pair<int, boo
     }
 }
 
+// Appends a table to a plan's block of tables; returns its offset.
 template <typename T>
-lsrtm_status upload(lsrtm_ctx* c, T** p, const std::vector<T>& v) {
-    CHK(dalloc_t(c, p, std::max<size_t>(1, v.size()), true));
-    if (!v.empty()) HIPCHK(c, hipMemcpy(*p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice));
-    return LSRTM_OK;
+size_t add_table(std::vector<char>& block, const std::vector<T>& v) {
+    const size_t at = (block.size() + 255) / 256 * 256;
+    block.resize(at + v.size() * sizeof(T));
+    if (!v.empty()) memcpy(block.data() + at, v.data(), v.size() * sizeof(T));
+    return at;
 }
 
 // Rows per lane of the resident kernels for the plan's windows; 0 if they do
@@ -1101,10 +1105,14 @@ int res_rows(const lsrtm_ctx* c) {
 }
 
 // Estimated microseconds of one resident step: what a step costs whatever the
-// slab's width, and per node of a thread.
+// slab's width (the exchanges' latency above all), and per node of a thread.
+// Measured at 5 rows per lane, slabs of 8 and 24 columns: 4.1 and 4.5 (background), 4.4
+// and 5.5 (replay), 6.3 and 9.3 (Born), 5.2 and 6.1 (Born on cached replays),
+// 5.0 and 8.1 (adjoint).
 double res_step_us(int kind, int nodes) {
-    static const double per[R_KINDS] = {0.20, 0.22, 0.40, 0.30, 0.30};
-    return 2.5 + per[kind] * nodes;
+    static const double base[R_KINDS] = {3.9, 3.9, 4.8, 4.8, 3.4};
+    static const double per[R_KINDS] = {0.04, 0.11, 0.30, 0.09, 0.31};
+    return base[kind] + per[kind] * nodes;
 }
 
 // Launches of the resident kernels for every group and kind: consecutive
@@ -1120,16 +1128,21 @@ lsrtm_status plan_resident(lsrtm_ctx* c) {
     long long exn = 0;
     size_t rounds = 1;
     std::vector<std::pair<int, bool>> sl;
+    std::vector<char> tab;
     for (auto& gr : c->groups) {
-        // receivers and receiver nodes by slot and column
+        // receivers and receiver nodes by slot, left of each column
         std::vector<std::vector<int>> rcols(gr.ns), ncols(gr.ns);
         for (int s = 0; s < gr.ns; ++s) {
-            rcols[s].assign(gr.h_slots[s].n[1], 0);
-            ncols[s].assign(gr.h_slots[s].n[1], 0);
+            rcols[s].assign(gr.h_slots[s].n[1] + 1, 0);
+            ncols[s].assign(gr.h_slots[s].n[1] + 1, 0);
         }
-        for (const Rec& R : gr.h_rec) rcols[R.slot][R.idx / gr.h_slots[R.slot].ldz] += 1;
+        for (const Rec& R : gr.h_rec) rcols[R.slot][R.idx / gr.h_slots[R.slot].ldz + 1] += 1;
         for (int i = 0; i < gr.nnode; ++i)
-            ncols[gr.h_node_slot[i]][gr.h_node_idx[i] / gr.h_slots[gr.h_node_slot[i]].ldz] += 1;
+            ncols[gr.h_node_slot[i]][gr.h_node_idx[i] / gr.h_slots[gr.h_node_slot[i]].ldz + 1] += 1;
+        for (int s = 0; s < gr.ns; ++s) {
+            std::partial_sum(rcols[s].begin(), rcols[s].end(), rcols[s].begin());
+            std::partial_sum(ncols[s].begin(), ncols[s].end(), ncols[s].begin());
+        }
         for (int kind = 0; kind < R_KINDS; ++kind) {
             gr.res[kind].clear();
             // workgroups of a slot, and most receivers of one, for every width
@@ -1141,11 +1154,9 @@ lsrtm_status plan_resident(lsrtm_ctx* c) {
                     const int nx = gr.h_slots[s].n[1], cxe = res_cx_edge(cx);
                     res_slabs(nx, npml, cx, cxe, sl);
                     int most = 0;
-                    for (auto& b : sl) {
-                        int m = 0;
-                        for (int x = b.first; x < std::min(nx, b.first + RES_WAVES * (b.second ? cxe : cx)); ++x)
-                            m += lists ? cols[s][x] : 0;
-                        most = std::max(most, m);
+                    for (size_t b = 0; lists && b < sl.size(); ++b) {
+                        const int x1 = b + 1 < sl.size() ? sl[b + 1].first : nx;
+                        most = std::max(most, cols[s][x1] - cols[s][sl[b].first]);
                     }
                     nb[cx].push_back((int)sl.size());
                     mn[cx].push_back(most);
@@ -1209,8 +1220,8 @@ lsrtm_status plan_resident(lsrtm_ctx* c) {
                         all.insert(all.end(), v.begin(), v.end());
                         ptr.push_back((int)all.size());
                     }
-                    CHK(upload(c, &L.rptr, ptr));
-                    CHK(upload(c, &L.rec, all));
+                    L.rptr = add_table(tab, ptr);
+                    L.rec = add_table(tab, all);
                 }
                 if (kind == R_ADJ) {
                     nodes.resize(blocks.size());
@@ -1230,10 +1241,10 @@ lsrtm_status plan_resident(lsrtm_ctx* c) {
                         ptr.push_back((int)all.size());
                         L.maxnodes = most = std::max(most, (int)v.size());
                     }
-                    CHK(upload(c, &L.nptr, ptr));
-                    CHK(upload(c, &L.node, all));
+                    L.nptr = add_table(tab, ptr);
+                    L.node = add_table(tab, all);
                 }
-                CHK(upload(c, &L.blocks, blocks));
+                L.blocks = add_table(tab, blocks);
                 L.lds = res_lds_bytes(kind, bz, L.cx, most);
                 exn = std::max(exn, L.nblocks * res_ex_words(bz, kind == R_BORN ? 2 : 1));
                 gr.res[kind].push_back(L);
@@ -1243,6 +1254,8 @@ lsrtm_status plan_resident(lsrtm_ctx* c) {
     }
     c->res_ctln = (int)((2 * c->nseg + 4) * rounds + 1);
     c->res_exn = exn;
+    CHK(dalloc_t(c, &c->res_tab, tab.size(), true));
+    HIPCHK(c, hipMemcpy(c->res_tab, tab.data(), tab.size(), hipMemcpyHostToDevice));
     CHK(dalloc_t(c, &c->res_ex, exn, true));
     CHK(dalloc_t(c, &c->res_ctl, c->res_ctln, true));
     c->res_ok = true;
@@ -1407,10 +1420,19 @@ lsrtm_status plan(lsrtm_ctx* c) {
     }
     if (!fits)
         FAIL(c, LSRTM_ENOMEM, "memory plan needs %.2f GB, budget %.2f GB", need / 1e9, budget / 1e9);
-    // With a replay cache (whole segments only), a checkpoint interval the
-    // planner chose may shrink, down to half, when the cache then holds more
-    // steps; results do not depend on the interval.
-    if (c->opt_rcache_mb > 0 && !c->fused && !ckg && c->g.ckpt_every <= 0) {
+    // An interval that the planner chose is the one of least memory.  From
+    // there it may change where that pays; results do not depend on it, except
+    // that 16-bit checkpoints round at other steps.
+    // With a replay cache (whole segments only) it may shrink, down to half,
+    // when the cache then holds more steps.
+    // A resident segment costs by its ends too (a checkpoint, two launches that
+    // read and write a shot's registers: 40 to 90 us), so resident plans take the
+    // longest one, up to a fifth of the march, that is within a thirtieth of the
+    // least memory, which is flat there (500 steps of 120 shots of 280 x 777: segments of
+    // 45 steps 8.7 GB and 151 ms, of 64 steps 9.0 GB and 143 ms), as long as the
+    // cache holds no less.
+    const bool lengthen = c->res_bz > 0 && c->g.ckpt_dtype == 0;
+    if ((c->opt_rcache_mb > 0 || lengthen) && !c->fused && !ckg && c->g.ckpt_every <= 0) {
         long long grp_pts = 0, grp_seg = 0, all_seg = 0;
         {
             int s = 0;
@@ -1449,6 +1471,11 @@ lsrtm_status plan(lsrtm_ctx* c) {
                 bk = kk;
             }
         }
+        for (int kk = std::max(bk + 1, (nt + 4) / 5); lengthen && kk > bk; --kk)
+            if (need_of(kk) <= need + need / 30 && held(kk) >= best) {
+                bk = kk;
+                break;
+            }
         if (bk != k) {
             k = bk;
             need = need_of(k);
