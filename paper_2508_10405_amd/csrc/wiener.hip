@@ -18,6 +18,10 @@
 // arrays), hipFFT transforms them, one workgroup per block forms the filtered
 // spectrum, hipFFT transforms back, and a gather kernel merges the 2^ndim
 // blocks over each node and restores the scale.
+//
+// 2D blocks of 16, 32 or 64 nodes take another route: a workgroup carries a
+// block from the images to its estimate in LDS (k_w_block), for all images of
+// a call at once, and only the estimates go through memory.
 #include "common.h"
 #include "kernels.h"
 #include <hipfft/hipfft.h>
@@ -41,8 +45,17 @@ struct WArgs {
 
 constexpr int NPART = 256;
 
+// Images that the LDS route takes per launch: its estimates then take less
+// memory than the spectra of one image do in the other.
+constexpr int WIMG = 4;
+constexpr int WPART = 64;            // partial maxima per image of that route
+
 struct WienerWork {
     int ndim = 0, n[3] = {0, 0, 0}, block = 0;
+    int images = 0;                  // images that est holds (LDS route)
+    float* est = nullptr;            // [images][nwin][bs] block estimates
+    float* part = nullptr;           // [WIMG][3][WPART] partial maxima
+    double2* root = nullptr;         // [block] exp(-2 pi i k / block)
     long long nwin = 0, bs = 0;
     hipfftComplex* buf = nullptr;    // [3][nwin][bs]: ref, blur, in spectra
     float* taper = nullptr;          // [block]
@@ -215,6 +228,299 @@ __global__ void k_w_merge(WArgs a, const hipfftComplex* __restrict__ bufA, float
     }
 }
 
+// ---------------------------------------------------------------------------
+// 2D blocks of B = 16, 32 or 64: one workgroup per block and image
+//
+// What bounds the general route at common sizes is its launches (seven per
+// image, 3 to 10 us each) and the spectra's way through memory (24 B per node
+// and transform for data of 4).  Here a block's three real images are
+// transformed in LDS, two columns of one image to a complex transform (never
+// two images, whose magnitudes can be far apart), filtered and transformed
+// back.  Two images of 240 x 737 take 28 us with blocks of 64 and 38 us with
+// blocks of 16 (the general route: 168 and 115).
+//
+// A transform of B = 8 T points runs in T lanes of one wave, 8 points each:
+// point n = t + T r, a radix-8 butterfly over r, twiddles w_B^(t k1), an
+// exchange through the group's LDS, a radix-T butterfly over t; the lane ends
+// with the frequencies (t + T i) + 8 k2.
+// The butterflies run in 64 bits, LDS holds 32: the call takes 28 us instead of 26
+// with 32-bit butterflies, and its error against 64 bits is 1.6e-7 instead
+// of 2.5e-7 (the general route: 2.3e-7; relative L2, blocks of 64).
+// ---------------------------------------------------------------------------
+template <int B>
+struct WShape {
+    static constexpr int T = B / 8;                  // lanes of a transform
+    static constexpr int H = B / 2 + 1;              // rows of a half spectrum
+    static constexpr int LS = B + B / 8;             // stride of a row: the exchange pads every 8
+    static constexpr int NT = B == 64 ? 512 : B == 32 ? 256 : 64;
+    static constexpr int NG = NT / T;                // transforms at once
+};
+
+__device__ __forceinline__ double2 to64(float2 a) { return {(double)a.x, (double)a.y}; }
+__device__ __forceinline__ float2 to32(double2 a) { return {(float)a.x, (float)a.y}; }
+__device__ __forceinline__ double2 cadd(double2 a, double2 b) { return {a.x + b.x, a.y + b.y}; }
+__device__ __forceinline__ double2 csub(double2 a, double2 b) { return {a.x - b.x, a.y - b.y}; }
+// times -i (forward) or i (inverse)
+template <bool INV>
+__device__ __forceinline__ double2 crot(double2 a) {
+    return INV ? make_double2(-a.y, a.x) : make_double2(a.y, -a.x);
+}
+template <bool INV>
+__device__ __forceinline__ double2 cmul(double2 a, double2 w) {   // w conjugated for the inverse
+    const double wy = INV ? -w.y : w.y;
+    return {fma(a.x, w.x, -a.y * wy), fma(a.x, wy, a.y * w.x)};
+}
+
+// Butterflies in place, natural order in and out.
+template <bool INV>
+__device__ __forceinline__ void fly2(double2* v) {
+    const double2 a = v[0];
+    v[0] = cadd(a, v[1]);
+    v[1] = csub(a, v[1]);
+}
+template <bool INV>
+__device__ __forceinline__ void fly4(double2* v) {
+    const double2 a = cadd(v[0], v[2]), b = csub(v[0], v[2]), c = cadd(v[1], v[3]), d = crot<INV>(csub(v[1], v[3]));
+    v[0] = cadd(a, c);
+    v[1] = cadd(b, d);
+    v[2] = csub(a, c);
+    v[3] = csub(b, d);
+}
+template <bool INV>
+__device__ __forceinline__ void fly8(double2* v) {
+    constexpr double r = 0.70710678118654752440;
+    double2 e[4] = {v[0], v[2], v[4], v[6]}, o[4] = {v[1], v[3], v[5], v[7]};
+    fly4<INV>(e);
+    fly4<INV>(o);
+    const double2 o1 = cmul<INV>(o[1], make_double2(r, -r)), o2 = crot<INV>(o[2]), o3 = cmul<INV>(o[3], make_double2(-r, -r));
+    v[0] = cadd(e[0], o[0]);
+    v[1] = cadd(e[1], o1);
+    v[2] = cadd(e[2], o2);
+    v[3] = cadd(e[3], o3);
+    v[4] = csub(e[0], o[0]);
+    v[5] = csub(e[1], o1);
+    v[6] = csub(e[2], o2);
+    v[7] = csub(e[3], o3);
+}
+
+// LDS accesses of the lanes of one wave, in program order.
+__device__ __forceinline__ void wave_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// v[r] = point t + T r in, v[i T + k2] = frequency (t + T i) + 8 k2 out; x is
+// the group's LDS row.
+template <int B, bool INV>
+__device__ __forceinline__ void transform(double2 (&v)[8], float2* x, int t, const double2 (&tw)[8]) {
+    constexpr int T = WShape<B>::T;
+    fly8<INV>(v);
+    wave_order();
+#pragma unroll
+    for (int k = 0; k < 8; ++k) x[t * 9 + k] = to32(k == 0 ? v[0] : cmul<INV>(v[k], tw[k]));
+    wave_order();
+#pragma unroll
+    for (int i = 0; i < 8 / T; ++i) {
+#pragma unroll
+        for (int u = 0; u < T; ++u) v[i * T + u] = to64(x[u * 9 + t + T * i]);
+        if constexpr (T == 8) fly8<INV>(v + i * T);
+        else if constexpr (T == 4) fly4<INV>(v + i * T);
+        else fly2<INV>(v + i * T);
+    }
+    wave_order();
+}
+
+// Largest of v over the workgroup.
+template <int NT>
+__device__ __forceinline__ float group_max(float v, float* red) {
+#pragma unroll
+    for (int s = 32; s > 0; s >>= 1) v = fmaxf(v, __shfl_xor(v, s));
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    v = red[0];
+#pragma unroll
+    for (int i = 1; i < NT / 64; ++i) v = fmaxf(v, red[i]);
+    return v;
+}
+
+// Largest |value| of image m of an image triple.
+__device__ __forceinline__ float wscale(const float* __restrict__ part, int m) {
+    float v = part[m * WPART + (threadIdx.x & 63)];
+#pragma unroll
+    for (int s = 32; s > 0; s >>= 1) v = fmaxf(v, __shfl_xor(v, s));
+    return v;
+}
+
+__global__ void k_w_part(const float* __restrict__ ref, const float* __restrict__ blur, const float* __restrict__ in,
+                         long long n, float* __restrict__ part) {
+    __shared__ float red[NTHREADS / 64];
+    const int k = blockIdx.y, img = blockIdx.z;
+    const float* const f = (k == 0 ? ref : k == 1 ? blur : in) + img * n;
+    float m = 0.f;
+    for (long long i = blockIdx.x * (long long)NTHREADS + threadIdx.x; i < n; i += (long long)WPART * NTHREADS)
+        m = fmaxf(m, fabsf(f[i]));
+    m = group_max<NTHREADS>(m, red);
+    if (threadIdx.x == 0) part[(img * 3 + k) * WPART + blockIdx.x] = m;
+}
+
+// IN: m_in is an image of its own (otherwise it is m_ref).
+template <int B, bool IN>
+__global__ void __launch_bounds__(WShape<B>::NT)
+k_w_block(WArgs a, double eps_rel, const float* __restrict__ ref, const float* __restrict__ blur,
+          const float* __restrict__ in, const double2* __restrict__ root, const float* __restrict__ part,
+          float* __restrict__ est) {
+    using W = WShape<B>;
+    constexpr int T = W::T, H = W::H, LS = W::LS, NT = W::NT, NG = W::NG, M = IN ? 3 : 2;
+    __shared__ __align__(16) float2 spec[M][H][LS];   // half spectra, rows of constant k_z
+    __shared__ float2 work[NG][LS];
+    __shared__ float red[NT / 64], taper[B];
+    const int t = threadIdx.x % T, gr = threadIdx.x / T;
+    const int oz = (int)(blockIdx.x % a.K[0]) * (B / 2) - B / 2, ox = (int)(blockIdx.x / a.K[0]) * (B / 2) - B / 2;
+    part += blockIdx.y * 3 * WPART;
+    est += ((long long)blockIdx.y * a.nwin + blockIdx.x) * (B * B);
+    float scale[M];
+#pragma unroll
+    for (int m = 0; m < M; ++m) scale[m] = wscale(part, m);
+    for (int i = threadIdx.x; i < B; i += NT) taper[i] = a.taper[i];
+    double2 tw[8], v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) tw[k] = root[t * k];
+    __syncthreads();
+    // along z: columns 2 j and 2 j + 1 of an image as one complex transform
+    for (int f = gr; f < M * (B / 2); f += NG) {
+        const int m = f / (B / 2), j = f % (B / 2), gx = ox + 2 * j;
+        const float sc = m == 0 ? scale[0] : m == 1 ? scale[1] : scale[M - 1];
+        const float* const img = (m == 0 ? ref : m == 1 ? blur : in) + blockIdx.y * a.N;
+        const float* const c0 = img + (long long)gx * a.n[0];
+        const bool x0 = (unsigned)gx < (unsigned)a.n[1], x1 = (unsigned)(gx + 1) < (unsigned)a.n[1];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            const int uz = t + T * r, gz = oz + uz;
+            const bool z = (unsigned)gz < (unsigned)a.n[0] && sc > 0.f;
+            v[r].x = z && x0 ? taper[uz] * taper[2 * j] * (c0[gz] / sc) : 0.f;
+            v[r].y = z && x1 ? taper[uz] * taper[2 * j + 1] * (c0[gz + a.n[0]] / sc) : 0.f;
+        }
+        float2* const x = work[gr];
+        transform<B, false>(v, x, t, tw);
+#pragma unroll
+        for (int i = 0; i < 8 / T; ++i)
+#pragma unroll
+            for (int k2 = 0; k2 < T; ++k2) x[(t + T * i) + 8 * k2] = to32(v[i * T + k2]);
+        wave_order();
+        for (int k = t; k < H; k += T) {
+            const float2 p = x[k], q = x[(B - k) % B];   // Z(k), Z(-k)
+            *reinterpret_cast<float4*>(&spec[m][k][2 * j]) =
+                make_float4(0.5f * (p.x + q.x), 0.5f * (p.y - q.y), 0.5f * (p.y + q.y), 0.5f * (q.x - p.x));
+        }
+        wave_order();
+    }
+    __syncthreads();
+    // along x, in place
+    for (int f = gr; f < M * H; f += NG) {
+        float2* const x = spec[f / H][f % H];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) v[r] = to64(x[t + T * r]);
+        transform<B, false>(v, x, t, tw);
+#pragma unroll
+        for (int i = 0; i < 8 / T; ++i)
+#pragma unroll
+            for (int k2 = 0; k2 < T; ++k2) x[(t + T * i) + 8 * k2] = to32(v[i * T + k2]);
+    }
+    __syncthreads();
+    // the filter, as in k_w_filter; a half spectrum has every magnitude
+    float mx = 0.f;
+    for (int u = threadIdx.x; u < H * B; u += NT) {
+        const float2 b = spec[1][u / B][u % B];
+        mx = fmaxf(mx, fmaxf(fabsf(b.x), fabsf(b.y)));
+    }
+    const float beta = group_max<NT>(mx, red);
+    if (!(beta > 0.f)) {
+        for (int u = threadIdx.x; u < B * B; u += NT) est[u] = 0.f;
+        return;
+    }
+    const float ib = 1.f / beta;
+    float pw = 0.f;
+    for (int u = threadIdx.x; u < H * B; u += NT) {
+        const float2 b = spec[1][u / B][u % B];
+        const float bx = b.x * ib, by = b.y * ib;
+        pw = fmaxf(pw, bx * bx + by * by);
+    }
+    const float eps = (float)(eps_rel * (double)group_max<NT>(pw, red));
+    const float inv_bs = 1.f / (float)(B * B);
+    for (int u = threadIdx.x; u < H * B; u += NT) {
+        const float2 b = spec[1][u / B][u % B], r = spec[0][u / B][u % B], c = spec[IN ? M - 1 : 0][u / B][u % B];
+        const float bx = b.x * ib, by = b.y * ib;
+        const float den = (bx * bx + by * by) + eps;
+        const float gx = ((bx * r.x + by * r.y) / den) * ib;
+        const float gy = ((bx * r.y - by * r.x) / den) * ib;
+        spec[0][u / B][u % B] = {(gx * c.x - gy * c.y) * inv_bs, (gx * c.y + gy * c.x) * inv_bs};
+    }
+    __syncthreads();
+    for (int f = gr; f < H; f += NG) {
+        float2* const x = spec[0][f];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) v[r] = to64(x[t + T * r]);
+        transform<B, true>(v, x, t, tw);
+#pragma unroll
+        for (int i = 0; i < 8 / T; ++i)
+#pragma unroll
+            for (int k2 = 0; k2 < T; ++k2) x[(t + T * i) + 8 * k2] = to32(v[i * T + k2]);
+    }
+    __syncthreads();
+    for (int j = gr; j < B / 2; j += NG) {
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            const int k = t + T * r;
+            const float4 s = *reinterpret_cast<const float4*>(&spec[0][k < H ? k : B - k][2 * j]);
+            // the rows 0 and B / 2 are their own conjugates: their values are real
+            const double sg = k == 0 || k == B / 2 ? 0.0 : k < H ? 1.0 : -1.0;
+            v[r] = {s.x - sg * s.w, sg * s.y + s.z};
+        }
+        transform<B, true>(v, work[gr], t, tw);
+#pragma unroll
+        for (int i = 0; i < 8 / T; ++i)
+#pragma unroll
+            for (int k2 = 0; k2 < T; ++k2) {
+                const int uz = (t + T * i) + 8 * k2;
+                est[2 * j * B + uz] = (float)v[i * T + k2].x;
+                est[(2 * j + 1) * B + uz] = (float)v[i * T + k2].y;
+            }
+    }
+}
+
+// One column of one image per workgroup: k_w_merge's sums, in its order.
+__global__ void k_w_merge2(WArgs a, int own_in, const float* __restrict__ part, const float* __restrict__ est,
+                           float* __restrict__ out) {
+    const int gx = blockIdx.x, h = a.B / 2;
+    part += blockIdx.y * 3 * WPART;
+    est += (long long)blockIdx.y * a.nwin * a.bs;
+    out += blockIdx.y * a.N + (long long)gx * a.n[0];
+    const float sr = wscale(part, 0), sb = wscale(part, 1), si = own_in ? wscale(part, 2) : sr;
+    const float back = sb > 0.f ? (sr / sb) * si : 0.f;
+    const int kx = gx / h, lx = gx - (kx - 1) * h;
+    for (int gz = threadIdx.x; gz < a.n[0]; gz += NTHREADS) {
+        const int kz = gz / h, lz = gz - (kz - 1) * h;
+        float num = 0.f, den = 0.f;
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            const int wz = kz + (m & 1), wx = kx + (m >> 1), uz = lz - (m & 1) * h, ux = lx - (m >> 1) * h;
+            if (wz >= a.K[0] || wx >= a.K[1]) continue;
+            num += est[((long long)wx * a.K[0] + wz) * a.bs + ux * a.B + uz];
+            den += a.taper[uz] * a.taper[ux];
+        }
+        out[gz] = den > 0.f ? (num / den) * back : 0.f;
+    }
+}
+
+template <int B>
+void launch_block(const WArgs& a, double eps_rel, const float* ref, const float* blur, const float* in, int nimg,
+                  const WienerWork* W, hipStream_t st) {
+    const dim3 grid((unsigned)a.nwin, nimg);
+    if (in == ref) k_w_block<B, false><<<grid, WShape<B>::NT, 0, st>>>(a, eps_rel, ref, blur, in, W->root, W->part, W->est);
+    else k_w_block<B, true><<<grid, WShape<B>::NT, 0, st>>>(a, eps_rel, ref, blur, in, W->root, W->part, W->est);
+}
+
 int grid_of(long long n) {
     long long b = (n + NTHREADS - 1) / NTHREADS;
     return (int)(b < 1 ? 1 : (b > 65536 ? 65536 : b));
@@ -229,6 +535,9 @@ void wiener_free(WienerWork* w) {
         (void)hipfftDestroy(w->inv);
     }
     if (w->buf) (void)hipFree(w->buf);
+    if (w->est) (void)hipFree(w->est);
+    if (w->part) (void)hipFree(w->part);
+    if (w->root) (void)hipFree(w->root);
     if (w->taper) (void)hipFree(w->taper);
     if (w->scale) (void)hipFree(w->scale);
     delete w;
@@ -240,6 +549,8 @@ const char* wiener_apply(WienerWork** work, int ndim, const int n[3], int block,
     if (block < 2 || (block & 1)) return "block must be even and >= 2";
     if (!(eps_rel >= 0.0)) return "eps_rel must be >= 0";
     WienerWork* W = *work;
+    // lanes of a wave per transform, whole waves per workgroup: 16, 32, 64
+    const bool in_lds = ndim == 2 && (block == 16 || block == 32 || block == 64);
     const bool same = W && W->ndim == ndim && W->block == block && W->n[0] == n[0] && W->n[1] == n[1] &&
                       W->n[2] == n[2];
     if (!same) {
@@ -247,7 +558,6 @@ const char* wiener_apply(WienerWork** work, int ndim, const int n[3], int block,
         W = new WienerWork();
         *work = W;
         W->ndim = ndim;
-        W->block = block;
         for (int a = 0; a < 3; ++a) W->n[a] = n[a];
         const int h = block / 2;
         W->nwin = 1;
@@ -256,9 +566,7 @@ const char* wiener_apply(WienerWork** work, int ndim, const int n[3], int block,
             W->nwin *= (n[a] - 1) / h + 2;
             W->bs *= block;
         }
-        if (hipMalloc(&W->buf, 3 * W->nwin * W->bs * sizeof(hipfftComplex)) != hipSuccess) return "out of memory";
         if (hipMalloc(&W->taper, block * sizeof(float)) != hipSuccess) return "out of memory";
-        if (hipMalloc(&W->scale, (3 * NPART + 3) * sizeof(float)) != hipSuccess) return "out of memory";
         std::vector<float> t(block);
         for (int u = 0; u < block; ++u) {
             const double s = std::sin(M_PI * (u + 0.5) / block);
@@ -266,19 +574,30 @@ const char* wiener_apply(WienerWork** work, int ndim, const int n[3], int block,
         }
         if (hipMemcpy(W->taper, t.data(), block * sizeof(float), hipMemcpyHostToDevice) != hipSuccess)
             return "taper upload failed";
-        int dims[3] = {block, block, block};
-        if (hipfftPlanMany(&W->fwd, ndim, dims, nullptr, 1, (int)W->bs, nullptr, 1, (int)W->bs, HIPFFT_C2C,
-                           (int)(3 * W->nwin)) != HIPFFT_SUCCESS)
-            return "hipfftPlanMany (forward) failed";
-        if (hipfftPlanMany(&W->inv, ndim, dims, nullptr, 1, (int)W->bs, nullptr, 1, (int)W->bs, HIPFFT_C2C,
-                           (int)W->nwin) != HIPFFT_SUCCESS) {
-            (void)hipfftDestroy(W->fwd);
-            return "hipfftPlanMany (inverse) failed";
+        if (in_lds) {
+            if (hipMalloc(&W->part, WIMG * 3 * WPART * sizeof(float)) != hipSuccess) return "out of memory";
+            if (hipMalloc(&W->root, block * sizeof(double2)) != hipSuccess) return "out of memory";
+            std::vector<double2> r(block);
+            for (int k = 0; k < block; ++k)
+                r[k] = {std::cos(2.0 * M_PI * k / block), -std::sin(2.0 * M_PI * k / block)};
+            if (hipMemcpy(W->root, r.data(), block * sizeof(double2), hipMemcpyHostToDevice) != hipSuccess)
+                return "twiddle upload failed";
+        } else {
+            if (hipMalloc(&W->buf, 3 * W->nwin * W->bs * sizeof(hipfftComplex)) != hipSuccess) return "out of memory";
+            if (hipMalloc(&W->scale, (3 * NPART + 3) * sizeof(float)) != hipSuccess) return "out of memory";
+            int dims[3] = {block, block, block};
+            if (hipfftPlanMany(&W->fwd, ndim, dims, nullptr, 1, (int)W->bs, nullptr, 1, (int)W->bs, HIPFFT_C2C,
+                               (int)(3 * W->nwin)) != HIPFFT_SUCCESS)
+                return "hipfftPlanMany (forward) failed";
+            if (hipfftPlanMany(&W->inv, ndim, dims, nullptr, 1, (int)W->bs, nullptr, 1, (int)W->bs, HIPFFT_C2C,
+                               (int)W->nwin) != HIPFFT_SUCCESS) {
+                (void)hipfftDestroy(W->fwd);
+                return "hipfftPlanMany (inverse) failed";
+            }
+            W->plans = true;
         }
-        W->plans = true;
+        W->block = block;            // complete: a later call may take it
     }
-    if (hipfftSetStream(W->fwd, st) != HIPFFT_SUCCESS || hipfftSetStream(W->inv, st) != HIPFFT_SUCCESS)
-        return "hipfftSetStream failed";
     WArgs a;
     for (int ax = 0; ax < 3; ++ax) {
         a.n[ax] = n[ax];
@@ -290,7 +609,30 @@ const char* wiener_apply(WienerWork** work, int ndim, const int n[3], int block,
     a.bs = W->bs;
     a.N = (long long)n[0] * n[1] * n[2];
     a.taper = W->taper;
+    if (in_lds) {
+        const int most = nimg < WIMG ? nimg : WIMG;
+        if (W->images < most) {
+            if (W->est) (void)hipFree(W->est);
+            W->est = nullptr;
+            W->images = 0;
+            if (hipMalloc(&W->est, most * W->nwin * W->bs * sizeof(float)) != hipSuccess) return "out of memory";
+            W->images = most;
+        }
+        for (int k = 0; k < nimg; k += WIMG) {
+            const int m = nimg - k < WIMG ? nimg - k : WIMG;
+            const float *r = ref + k * a.N, *b = blur + k * a.N, *x = in + k * a.N;
+            k_w_part<<<dim3(WPART, in == ref ? 2 : 3, m), NTHREADS, 0, st>>>(r, b, x, a.N, W->part);
+            if (block == 64) launch_block<64>(a, eps_rel, r, b, x, m, W, st);
+            else if (block == 32) launch_block<32>(a, eps_rel, r, b, x, m, W, st);
+            else launch_block<16>(a, eps_rel, r, b, x, m, W, st);
+            k_w_merge2<<<dim3(n[1], m), NTHREADS, 0, st>>>(a, in != ref, W->part, W->est, out + k * a.N);
+            if (hipGetLastError() != hipSuccess) return "block kernels failed";
+        }
+        return nullptr;
+    }
     a.scale = W->scale + 3 * NPART;
+    if (hipfftSetStream(W->fwd, st) != HIPFFT_SUCCESS || hipfftSetStream(W->inv, st) != HIPFFT_SUCCESS)
+        return "hipfftSetStream failed";
     for (int k = 0; k < nimg; ++k) {
         const long long off = k * a.N;
         k_w_maxabs<<<dim3(NPART, 3), NTHREADS, 0, st>>>(ref + off, blur + off, in + off, a.N, W->scale);

@@ -96,3 +96,27 @@ def test_wiener_errors(torch):
         with pytest.raises(lsrtm.LsrtmError):
             ctx.wiener(m, m, block=block, eps_rel=eps)
     ctx.close()
+
+
+@pytest.mark.parametrize("block", [16, 32, 64])
+def test_wiener_stacks(torch, block):
+    """A stack of more images than a launch takes, sizes that are no multiple
+    of the block, m_in given and left out: each image as by a call of its own,
+    and as the oracle has it (the operators' bar, as above)."""
+    from paper_2508_10405_amd import lsrtm
+    n, k = (71, 37), 5
+    rng = np.random.default_rng(block)
+    ctx = lsrtm.Context(n, (10.0, 10.0), 10, 1e-3)
+    ref, blur, x = (rng.standard_normal((k, 37, 71)) * 10.0 ** rng.uniform(-12, 3, (k, 1, 1)) for _ in range(3))
+    d = [to_dev(torch, v) for v in (ref, blur, x)]
+    for third in (None, 2):
+        out = ctx.wiener(d[0], d[1], None if third is None else d[third], block=block, eps_rel=1e-3)
+        for i in range(k):
+            own = ctx.wiener(*(v[i].contiguous() for v in d[:2]), None if third is None else d[third][i].contiguous(),
+                             block=block, eps_rel=1e-3)
+            assert torch.equal(own, out[i])
+            expect = O.wiener_deblur(ref[i], blur[i], ref[i] if third is None else x[i], block, 1e-3)
+            e = rel(out[i].cpu().numpy(), expect)
+            print("wiener stack", block, third, i, e, flush=True)
+            assert e <= TOL
+    ctx.close()
