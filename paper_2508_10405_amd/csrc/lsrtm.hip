@@ -214,7 +214,7 @@ struct lsrtm_ctx {
     long long res_exn = 0;
     int* res_ctl = nullptr;        // [0] gave up, [1 + i] arrivals of launch i of a group's pass
     int res_ctln = 0, res_launch = 0;
-    unsigned res_tag = 0;
+    int res_id = 0;                // launches since the exchange words were cleared
     // timing
     std::vector<EvPair> evpool;
     size_t evused = 0;
@@ -646,7 +646,7 @@ lsrtm_status check_flag(lsrtm_ctx* c) {
 // the exchange words (tags grow through the pass from 1).
 lsrtm_status res_begin(lsrtm_ctx* c) {
     c->res_launch = 0;
-    c->res_tag = 0;
+    c->res_id = 0;
     CHK(fill(c, reinterpret_cast<float*>(c->res_ctl + 1), c->res_ctln - 1));
     return fill(c, reinterpret_cast<float*>(c->res_ex), 2 * c->res_exn);
 }
@@ -676,10 +676,13 @@ lsrtm_status res_run(lsrtm_ctx* c, Group& gr, int kind, const Slot* sl, int n0, 
         a.node = reinterpret_cast<const int4*>(c->res_tab + L.node);
         a.maxnodes = L.maxnodes;
         a.ex = c->res_ex;
-        a.tag0 = c->res_tag;
+        if (++c->res_id >= RES_IDS) {
+            CHK(fill(c, reinterpret_cast<float*>(c->res_ex), 2 * c->res_exn));
+            c->res_id = 1;
+        }
+        a.id = c->res_id;
         a.ctl = c->res_ctl + 1 + c->res_launch++;
         a.abort_ = c->res_ctl;
-        c->res_tag += (unsigned)(n1 - n0) + 2;
         // a sample stands for the steps of the whole group
         c->tnow = true;
         EvPair* ev = kind == R_BORN_RC ? nullptr : tpick(c, cls_of[kind]);
@@ -1106,12 +1109,12 @@ int res_rows(const lsrtm_ctx* c) {
 
 // Estimated microseconds of one resident step: what a step costs whatever the
 // slab's width (the exchanges' latency above all), and per node of a thread.
-// Measured at 5 rows per lane, slabs of 8 and 24 columns: 4.1 and 4.5 (background), 4.4
-// and 5.5 (replay), 6.3 and 9.3 (Born), 5.2 and 6.1 (Born on cached replays),
-// 5.0 and 8.1 (adjoint).
+// Measured at 5 rows per lane, slabs of 8 and 24 columns: 3.2 and 3.8 (background),
+// 3.5 and 4.2 (replay), 4.6 and 7.4 (Born), 4.2 and 5.5 (Born on cached
+// replays), 4.4 and 6.9 (adjoint).
 double res_step_us(int kind, int nodes) {
-    static const double base[R_KINDS] = {3.9, 3.9, 4.8, 4.8, 3.4};
-    static const double per[R_KINDS] = {0.04, 0.11, 0.30, 0.09, 0.31};
+    static const double base[R_KINDS] = {3.0, 3.1, 3.3, 3.6, 3.1};
+    static const double per[R_KINDS] = {0.05, 0.07, 0.27, 0.13, 0.25};
     return base[kind] + per[kind] * nodes;
 }
 

@@ -14,9 +14,9 @@
 // step then is instruction issue (two waves per SIMD), the latency of two
 // exchanges of boundary columns, and for the replay and adjoint steps the
 // buffer's traffic.  Measured on 120 shots of 280 x 777 padded nodes, a Born
-// pass of 600 steps went from 219 to 107 ms, a migration pass of 500 steps from
-// 298 to 151 ms; on one shot of 140 x 240, 1000 steps, from 8.7 to 4.3 ms and
-// from 17.6 to 7.6 ms, where it is the launches that no longer count.
+// pass of 600 steps went from 219 to 84 ms, a migration pass of 500 steps from
+// 298 to 120 ms; on one shot of 140 x 240, 1000 steps, from 8.7 to 3.9 ms and
+// from 17.6 to 6.6 ms, where it is the launches that no longer count.
 #pragma once
 #include "common.h"
 
@@ -62,8 +62,8 @@ struct ResArgs {
     const int* nptr;             // adjoint: receiver nodes of a workgroup (CSR), and per node
     const int4* node;            // (owner thread << 8 | c BZ + k, first receiver, one past the last, 0)
     int maxnodes;                // most receiver nodes of a workgroup
-    unsigned long long* ex;      // exchange words [block][phase][parity][side][field][col][BZ][64]
-    unsigned tag0;               // tags of this launch are tag0 + 1 ...
+    unsigned long long* ex;      // exchange words [block][phase][parity][side][field][col][res_words][64]
+    unsigned id;                 // 1 .. RES_IDS - 1: of this launch, since the words were cleared
     int* ctl;                    // arrival count of this launch (0 before it)
     int* abort_;                 // set when a launch gives up
 };
@@ -80,8 +80,13 @@ __host__ __device__ constexpr long long res_segn(long long npts, int nx, int bz)
     return npts > (long long)nx * bz * 64 ? npts : (long long)nx * bz * 64;
 }
 
+// A column of a lane travels as res_words(bz) words of 64 bits: bz floats and
+// in the top 10 bits of each word a tag, which is the launch and every second
+// step's parity.
+constexpr int res_words(int bz) { return bz / 2 + 1; }
+constexpr int RES_IDS = 512;
 // Exchange words of one workgroup.
-constexpr long long res_ex_words(int bz, int nf) { return 2LL * 2 * 2 * nf * RES_EXCOLS * bz * 64; }
+constexpr long long res_ex_words(int bz, int nf) { return 2LL * 2 * 2 * nf * RES_EXCOLS * res_words(bz) * 64; }
 // Columns per wave of a strip slab whose launch's interior slabs have cx: the
 // strips' x memories take the registers of a column.
 constexpr int res_cx_edge(int cx) { return cx > 1 ? cx - 1 : cx; }
@@ -106,7 +111,7 @@ constexpr size_t res_lds_of(int kind, int bz, int cx, int most) {
     const size_t copy = res_copy_floats(bz, cx), nf = kind == R_BORN ? 2 : 1;
     const size_t copies = kind == R_ADJ ? 2 * copy + (size_t)(RES_WAVES * cx + 1) * bz * 64
                                         : (res_alias(kind, bz, cx) ? 1 : 2) * nf * copy;
-    return 4 * (copies + res_strip_floats(kind, bz, cx) + (kind == R_ADJ ? 2 : 4) * (size_t)most);
+    return 4 * (copies + res_strip_floats(kind, bz, cx) + (kind == R_ADJ ? 6 : 4) * (size_t)most + (kind == R_ADJ ? RES_NT + 1 : 0));
 }
 constexpr size_t res_lds_bytes(int kind, int bz, int cx, int most) {
     const size_t a = res_lds_of(kind, bz, cx, most), b = res_lds_of(kind, bz, res_cx_edge(cx), most);

@@ -78,11 +78,13 @@ __device__ __forceinline__ void adj_body(const ResArgs& a, const ResBlock& B, fl
             bxh[c] = axh[c] != 0.f ? uniform(elem(S.cpml[1], pl.nx + g)) : 0.f;
             bxn[c] = axn[c] != 0.f ? uniform(elem(S.cpml[1], 3 * pl.nx + g)) : 0.f;
         }
+    const gfloat* const seg0 = uniform(S.seg);
     Exchange<BZ, 1> X(a, 0, B.nb, pl.nv > 0);
     X.me = xcd_remap(blockIdx.x, gridDim.x);
-    // receiver nodes: bit c BZ + k of mask, data sums at inj[first ...] in that order
+    // receiver nodes: bit c BZ + k of mask, data sums at inj[first ...] in that
+    // order (one register: mask, and first above bit 18)
+    static_assert(CX * BZ <= 18, "a thread's nodes in 18 bits");
     unsigned mask = 0, wmask = 0;
-    int first = 0;
     const int q0 = a.y ? a.nptr[X.me] : 0, q1 = a.y ? a.nptr[X.me + 1] : 0;
     int* const own = reinterpret_cast<int*>(inj);    // owner thread << 8 | node of the thread
     for (int j = q0 + (int)threadIdx.x; j < q1; j += RES_NT) own[j - q0] = a.node[j].x;
@@ -90,13 +92,16 @@ __device__ __forceinline__ void adj_body(const ResArgs& a, const ResBlock& B, fl
     for (int j = 0; j < q1 - q0; ++j) {
         const int o = own[j];
         if ((o >> 8) == (int)threadIdx.x) {
-            if (!mask) first = j;
+            if (!mask) mask = (unsigned)j << 18;
             mask |= 1u << (o & 255);
         }
     }
     __syncthreads();
 #pragma unroll
     for (int b = 0; b < CX * BZ; ++b) wmask |= __any((mask >> b) & 1) ? 1u << b : 0u;
+    unsigned* const masks = reinterpret_cast<unsigned*>(inj + 6 * a.maxnodes) + threadIdx.x;
+    *masks = mask;
+    if (threadIdx.x == 0) masks[RES_NT] = 0;             // a zero, as an integer or a float
 
     auto share_e = [&](int par, unsigned tag) {      // e~_x = Q + aci (phi~ + Q)
 #pragma unroll
@@ -117,14 +122,14 @@ __device__ __forceinline__ void adj_body(const ResArgs& a, const ResBlock& B, fl
     // the last row of the grid: its row index in the lane, and the lane's share
     const int zlast = (pl.nz - 1) % BZ;
     const float flast = lane == (pl.nz - 1) / BZ ? 0.5f : 0.f;
-    unsigned tag = a.tag0 + 1;
+    unsigned tag = X.tag(0);
     share_e(0, tag);
     // q and the gradients of a step, from the replay buffer: each loaded half
     // a step before it is used, right after a fetch, so that the next fetch
     // does not wait behind it
     float sz[CX][BZ], sx[CX][BZ], sq[CX][BZ];
     auto load_seg = [&](int n) {
-        const gfloat* const f = S.seg + (long long)(a.sstep0 + n - a.n0) * 3 * pl.segn;
+        const gfloat* const f = seg0 + (long long)(a.sstep0 + n - a.n0) * 3 * pl.segn;
 #pragma unroll
         for (int c = 0; c < CX; ++c)
 #pragma unroll
@@ -134,7 +139,7 @@ __device__ __forceinline__ void adj_body(const ResArgs& a, const ResBlock& B, fl
             }
     };
     auto load_z = [&](int n) {
-        const gfloat* const f = S.seg + (long long)(a.sstep0 + n - a.n0) * 3 * pl.segn;
+        const gfloat* const f = seg0 + (long long)(a.sstep0 + n - a.n0) * 3 * pl.segn;
 #pragma unroll
         for (int c = 0; c < CX; ++c)
 #pragma unroll
@@ -153,18 +158,16 @@ __device__ __forceinline__ void adj_body(const ResArgs& a, const ResBlock& B, fl
         return s;
     };
     const bool mine = (int)threadIdx.x < q1 - q0;
+    LdsNode* const node = reinterpret_cast<LdsNode*>(inj + 2 * a.maxnodes) + threadIdx.x;
     bool single = false;
-    const float* yp = nullptr;
-    int ystride = 0;
     float pend = 0.f;
     if (mine) {
         const int4 u = a.node[q0 + (int)threadIdx.x];
         single = u.z - u.y == 1;
         if (single) {
             const Rec R = a.rec[u.y];
-            yp = a.y + R.out;
-            ystride = R.stride;
-            if (a.n1 > 1) pend = yp[(long long)(a.n1 - 2) * ystride];
+            *node = {R.out, R.stride, 0};
+            if (a.n1 > 1) pend = a.y[R.out + (long long)(a.n1 - 2) * R.stride];
         }
     }
 
@@ -172,14 +175,6 @@ __device__ __forceinline__ void adj_body(const ResArgs& a, const ResBlock& B, fl
     for (int n = a.n1 - 1; n >= a.n0; --n) {
         const int par = (a.n1 - 1 - n) & 1;
         const bool skip = a.first && n == a.n1 - 1;
-        // data of step n - 1 at the receiver nodes
-        if (a.y && n > 0) {
-            float* const to = inj + (n & 1) * a.maxnodes;
-            if (single) to[threadIdx.x] = 0.f + pend;
-            else if (mine) to[threadIdx.x] = node_sum(a.node[q0 + (int)threadIdx.x], n - 1);
-            for (int j = RES_NT + (int)threadIdx.x; j < q1 - q0; j += RES_NT) to[j] = node_sum(a.node[q0 + j], n - 1);
-            if (single && n > 1) pend = yp[(long long)(n - 2) * ystride];
-        }
         // ---- phase A, z
         float tn[BZ], th[BZ], tb[BZ];
         zrow<BZ>(zan, tn);
@@ -202,13 +197,30 @@ __device__ __forceinline__ void adj_body(const ResArgs& a, const ResBlock& B, fl
 #pragma unroll
             for (int k = 0; k < BZ; ++k) {
                 uz[c][k] = uz[c][k] + bz[c][k] * dd[k];
-                gk[c][k] = gk[c][k] + sq[c][k] * Q[c][k];
                 pin(uz[c][k]);
-                pin(gk[c][k]);
             }
         }
-        X.template halo<HE, CW, 1>(w, 0, par, 0, le, 0, tag);
+        // the replay buffer's values come last in a phase: the wait for them
+        // is one for the words published before it too
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int c = 0; c < CX; ++c)
+#pragma unroll
+            for (int k = 0; k < BZ; ++k) {
+                gk[c][k] = gk[c][k] + sq[c][k] * Q[c][k];
+                pin(gk[c][k]);
+            }
+        X.template halo<HE, CW, false>(w, 0, par, le, 0, tag);
         __syncthreads();
+        // data of step n - 1 at the receiver nodes: here the words published
+        // before the barrier no longer hold up the wait for them
+        if (w * 64 < q1 - q0 && n > 0) {
+            float* const to = inj + (n & 1) * a.maxnodes;
+            if (single) to[threadIdx.x] = 0.f + pend;
+            else if (mine) to[threadIdx.x] = node_sum(a.node[q0 + (int)threadIdx.x], n - 1);
+            for (int j = RES_NT + (int)threadIdx.x; j < q1 - q0; j += RES_NT) to[j] = node_sum(a.node[q0 + j], n - 1);
+            if (single && n > 1) pend = a.y[node->out + (long long)(n - 2) * node->stride];
+        }
         if (n < a.n1 - 1) load_z(n);
         // ---- phase A, x
 #pragma unroll
@@ -250,12 +262,9 @@ __device__ __forceinline__ void adj_body(const ResArgs& a, const ResBlock& B, fl
 #pragma unroll
         for (int c = 0; c < CX; ++c) {
             if (TIGHT) __builtin_amdgcn_sched_barrier(0);
-            float g[BZ], x[BZ];
+            float g[BZ];
 #pragma unroll
-            for (int k = 0; k < BZ; ++k) {
-                g[k] = uz[c][k];
-                x[k] = -sz[c][k] * uz[c][k];
-            }
+            for (int k = 0; k < BZ; ++k) g[k] = uz[c][k];
             {
 #pragma unroll
                 for (int k = 0; k < BZ; ++k) {
@@ -264,6 +273,15 @@ __device__ __forceinline__ void adj_body(const ResArgs& a, const ResBlock& B, fl
                 }
             }
             d_col<BZ, 0>(g, a.C.c[0], dz[c]);
+#pragma unroll
+            for (int k = 0; k < BZ; ++k) pin(dz[c][k]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int c = 0; c < CX; ++c) {
+            float x[BZ];
+#pragma unroll
+            for (int k = 0; k < BZ; ++k) x[k] = -sz[c][k] * uz[c][k];
             const float xb = lane_below(x[BZ - 1]);
 #pragma unroll
             for (int k = 0; k < BZ; ++k) {
@@ -271,11 +289,10 @@ __device__ __forceinline__ void adj_body(const ResArgs& a, const ResBlock& B, fl
                 // the last node of an axis takes the other half of its own
                 // product too (0.5 x is exact, so the fma rounds as the sum)
                 if (k == zlast) sz[c][k] = fmaf(flast, x[k], sz[c][k]);
-                pin(dz[c][k]);
                 pin(sz[c][k]);
             }
         }
-        X.template halo<HG, CW, 1>(w, 1, par, 0, lg, 0, tag);
+        X.template halo<HG, CW, false>(w, 1, par, lg, 0, tag);
         if (w == 2 && (B.nb & 1)) X.template fetch<1>(X.me - 1, 1, par, 1, 0, HG, lx + lane, 0, tag);
         __syncthreads();
         if (n > a.n0) load_seg(n - 1);
@@ -301,17 +318,26 @@ __device__ __forceinline__ void adj_body(const ResArgs& a, const ResBlock& B, fl
                 pin(Q[c][k]);
             }
         }
-        if (a.y && n > 0 && wmask) {
+        if (wmask && n > 0) {
+            // a row of nodes at a time, the nodes that are none taking the zero
+            const unsigned mask = *masks;
 #pragma unroll
-            for (int c = 0; c < CX; ++c)
+            for (int k = 0; k < BZ; ++k) {
+                unsigned row = 0;
 #pragma unroll
-                for (int k = 0; k < BZ; ++k) {
-                    const int b = c * BZ + k;
-                    if (wmask & (1u << b))
-                        if ((mask >> b) & 1) Q[c][k] = Q[c][k] - kd[c][k] * inj[(n & 1) * a.maxnodes + first + __popc(mask & ((1u << b) - 1))];
+                for (int c = 0; c < CX; ++c) row |= 1u << (c * BZ + k);
+                if (!(wmask & row)) continue;
+                float v[CX];
+#pragma unroll
+                for (int c = 0; c < CX; ++c) {
+                    const int b = c * BZ + k, at = (n & 1) * a.maxnodes + (int)(mask >> 18) + __popc(mask & ((1u << b) - 1));
+                    v[c] = inj[(mask >> b) & 1 ? at : 6 * a.maxnodes + RES_NT];
                 }
+#pragma unroll
+                for (int c = 0; c < CX; ++c) Q[c][k] = Q[c][k] - kd[c][k] * v[c];
+            }
         }
-        ++tag;
+        tag = X.tag(a.n1 - n);
         share_e(par ^ 1, tag);
     }
     pl.forget();

@@ -11,6 +11,7 @@
 namespace lsrtm {
 
 using u64 = unsigned long long;
+using gu64 = __attribute__((address_space(1))) u64;
 
 // The value that lane - 1 / lane + 1 holds; 0 in the first / last lane.
 __device__ __forceinline__ float lane_below(float x) {
@@ -105,6 +106,16 @@ __device__ __forceinline__ void pin(float& x) { asm volatile("" : "+v"(x)); }
 
 __device__ __forceinline__ float uniform(float x) {
     return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
+}
+// A descriptor's pointer, kept in scalar registers.  Read from the descriptor
+// inside the time loop it is a vector load (the kernel stores to memory), and the
+// wait for it is also one for every word just published: a background step of 7 shots
+// of 280 x 777 took 4.5 us with the source's amplitude read so, 4.1 without.
+template <typename G>
+__device__ __forceinline__ G* uniform(G* p) {
+    const u64 b = (u64)p;
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)b), hi = __builtin_amdgcn_readfirstlane((unsigned)(b >> 32));
+    return (G*)(((u64)hi << 32) | lo);
 }
 
 // Where a workgroup stands in its shot's grid, and what a thread owns.
@@ -267,38 +278,57 @@ __device__ __forceinline__ bool res_admit(const ResArgs& a, int* shared) {
     return ok;
 }
 
-// Exchange of boundary columns.  A published value is one 64-bit word, the
-// float and the tag of its step, stored and loaded whole at device scope, so a
-// reader needs no flag and no fence: it loads the words until every tag
-// matches.  Steps alternate between two buffers: a slab can be at most one
-// exchange ahead of its neighbour, because it needs the neighbour's columns
-// to go on.
+// Exchange of boundary columns.  A lane's rows of a column are published as
+// 64-bit words that each carry a tag in their top 10 bits, stored and loaded
+// whole at device scope, so a reader needs no flag and no fence: it loads the
+// words until every tag matches.  Steps alternate between two buffers: a slab
+// can be at most one exchange ahead of its neighbour, because it needs the
+// neighbour's columns to go on, so a word holds this step's values, those of
+// two steps ago, or an earlier launch's, and the launch's number with the
+// parity of (step / 2) tells them apart.
+//
+// What the exchange costs is its bytes, at device scope past the XCD's L2, and
+// the loads' latency (0.75 us when the words are there).  With a word per value
+// (40 B for 5 rows, now 24) and a Born step's two fields fetched one after the
+// other by the same waves, steps of 7 shots of 280 x 777 took 8.7 us (Born) and
+// 5.6 us (replay), now 7.4 and 4.2.
 template <int BZ, int NF>
 struct Exchange {
+    static constexpr int W = res_words(BZ), R = BZ - W;   // R values lie across the words' upper halves
+    static constexpr unsigned LOW = (1u << 22) - 1;       // value bits of an upper half
     u64* ex;                     // of this launch
     long long per;               // words per workgroup
     int me, nb;
+    unsigned id;
     int* abort_;
     bool in;                     // the lane holds rows of the grid (the others neither publish nor wait)
     bool dead = false;
     __device__ __forceinline__ Exchange(const ResArgs& a, int b, int nb_, bool in_)
-        : ex(a.ex), per(res_ex_words(BZ, NF)), me(b), nb(nb_), abort_(a.abort_), in(in_) {}
+        : ex(a.ex), per(res_ex_words(BZ, NF)), me(b), nb(nb_), id(a.id), abort_(a.abort_), in(in_) {}
+    // tag of the launch's i-th step
+    __device__ __forceinline__ unsigned tag(int i) const { return (id << 1 | ((unsigned)i >> 1 & 1)) << 22; }
     // A column's words: a base that is uniform over the wave, and the lane.
-    __device__ __forceinline__ u64* words(int b, int phase, int par, int side, int f, int col) const {
-        return ex + b * per + ((((((phase * 2 + par) * 2 + side) * NF + f) * RES_EXCOLS) + col) * BZ) * 64;
+    // (opaque, so that no 64-bit lane address is kept through the time loop)
+    __device__ __forceinline__ gu64* words(int b, int phase, int par, int side, int f, int col) const {
+        gu64* p = (gu64*)(ex + b * per + ((((((phase * 2 + par) * 2 + side) * NF + f) * RES_EXCOLS) + col) * W) * 64);
+        asm volatile("" : "+s"(p));
+        return p;
     }
-    static __device__ __forceinline__ u64* lane_word(u64* base, int k) {
-        return reinterpret_cast<u64*>(reinterpret_cast<char*>(base + k * 64) + ((threadIdx.x & 63u) << 3));
+    static __device__ __forceinline__ gu64* lane_word(gu64* base, int k) {
+        return (gu64*)((gchar*)(base + k * 64) + ((threadIdx.x & 63u) << 3));
     }
     __device__ __forceinline__ void publish(int phase, int par, int side, int f, int col, const float (&v)[BZ],
                                             unsigned tag) const {
-        u64* const p = words(me, phase, par, side, f, col);
+        gu64* const p = words(me, phase, par, side, f, col);
         if (!in) return;
+        const unsigned e0 = R > 0 ? __float_as_uint(v[R > 0 ? W : 0]) : 0, e1 = R > 1 ? __float_as_uint(v[R > 1 ? W + 1 : 0]) : 0;
 #pragma unroll
-        for (int k = 0; k < BZ; ++k) {
+        for (int k = 0; k < W; ++k) {
             unsigned bits;           // a copy: the value itself is not tied to the word's register pair
             asm volatile("v_mov_b32 %0, %1" : "=v"(bits) : "v"(v[k]));
-            __hip_atomic_store(lane_word(p, k), ((u64)tag << 32) | bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const unsigned up = k == 0 ? e0 : k == 1 ? __builtin_amdgcn_alignbit(e1, e0, 22) : k == 2 ? e1 >> 12 : 0;
+            __hip_atomic_store(lane_word(p, k), ((u64)((up & LOW) | tag) << 32) | bits, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
         }
     }
     // Columns col .. col + N - 1 of a neighbour's published side, fields f ..
@@ -307,22 +337,22 @@ struct Exchange {
     template <int N, int F = 1>
     __device__ __forceinline__ void fetch(int from, int phase, int par, int side, int f, int col, float* dst,
                                           int stride, unsigned tag) {
-        u64 v[F][N * BZ];
+        u64 v[F][N * W];
         long long t0 = 0;
         for (int it = 1;; ++it) {
             unsigned differ = 0;
 #pragma unroll
             for (int g = 0; g < F; ++g) {
-                u64* const p = words(from, phase, par, side, f + g, col);
+                gu64* const p = words(from, phase, par, side, f + g, col);
 #pragma unroll
-                for (int k = 0; k < N * BZ; ++k)
+                for (int k = 0; k < N * W; ++k)
                     v[g][k] = __hip_atomic_load(lane_word(p, k), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
 #pragma unroll
             for (int g = 0; g < F; ++g)
 #pragma unroll
-                for (int k = 0; k < N * BZ; ++k) differ |= (unsigned)(v[g][k] >> 32) ^ tag;
-            if (__all(differ == 0 || !in) || dead) break;
+                for (int k = 0; k < N * W; ++k) differ |= (unsigned)(v[g][k] >> 32) ^ tag;
+            if (__all(differ <= LOW || !in) || dead) break;
             if ((it & 255) == 0) {
                 const long long now = wall_clock64();
                 if (t0 == 0) t0 = now;
@@ -339,14 +369,30 @@ struct Exchange {
 #pragma unroll
             for (int g = 0; g < F; ++g)
 #pragma unroll
-                for (int k = 0; k < N * BZ; ++k) dst[g * stride + k * 64] = __uint_as_float((unsigned)v[g][k]);
+                for (int i = 0; i < N; ++i) {
+                    float* const d = dst + g * stride + i * BZ * 64;
+                    auto up = [&](int k) { return (unsigned)(v[g][i * W + k] >> 32); };
+#pragma unroll
+                    for (int k = 0; k < W; ++k) d[k * 64] = __uint_as_float((unsigned)v[g][i * W + k]);
+                    if constexpr (R > 0) d[W * 64] = __uint_as_float((up(0) & LOW) | up(1) << 22);
+                    if constexpr (R > 1) d[(W + 1) * 64] = __uint_as_float((up(1) >> 10 & 0xfff) | up(2) << 12);
+                }
     }
-    // The halo columns of an LDS copy (HL of them to the left), two to a wave:
-    // the left ones by waves 0 and 1, the right ones by waves 6 and 7.
-    template <int HL, int CW, int F>
-    __device__ __forceinline__ void halo(int w, int phase, int par, int f, float* lds, int stride, unsigned tag) {
-        constexpr int HR = RES_HALO - HL, ROW = BZ * 64;
-        float* const l = lds + (threadIdx.x & 63);
+    // The halo columns of an LDS copy (HL of them to the left), two or three to a
+    // wave: the left ones by waves 0 and 1, the right ones by waves 6 and 7,
+    // every field of the exchange at once; or, where registers do not allow that,
+    // the second field by the waves next to them (a wave that fetched one field
+    // after the other would wait for two round trips).
+    template <int HL, int CW, bool SPLIT>
+    __device__ __forceinline__ void halo(int w, int phase, int par, float* lds, int stride, unsigned tag) {
+        constexpr int HR = RES_HALO - HL, ROW = BZ * 64, F = SPLIT ? 1 : NF;
+        float* l = lds + (threadIdx.x & 63);
+        int f = 0;
+        if (SPLIT && w >= 2 && w < 6) {
+            w = w < 4 ? w - 2 : w + 2;
+            f = 1;
+            l += stride;
+        }
         if (nb & 1) {
             if (w == 0) fetch<2, F>(me - 1, phase, par, 1, f, 0, l + (HW - HL) * ROW, stride, tag);
             if (w == 1) fetch<HL - 2, F>(me - 1, phase, par, 1, f, 2, l + (HW - HL + 2) * ROW, stride, tag);
@@ -354,16 +400,6 @@ struct Exchange {
         if (nb & 2) {
             if (w == 6) fetch<2, F>(me + 1, phase, par, 0, f, 0, l + (HW + CW) * ROW, stride, tag);
             if (w == 7) fetch<HR - 2, F>(me + 1, phase, par, 0, f, 2, l + (HW + CW + 2) * ROW, stride, tag);
-        }
-    }
-    // every field of an exchange: together where registers allow, else one by one
-    template <int HL, int CW, bool TOGETHER>
-    __device__ __forceinline__ void halos(int w, int phase, int par, float* lds, int stride, unsigned tag) {
-        if constexpr (TOGETHER) {
-            halo<HL, CW, NF>(w, phase, par, 0, lds, stride, tag);
-        } else {
-#pragma unroll
-            for (int f = 0; f < NF; ++f) halo<HL, CW, 1>(w, phase, par, f, lds + f * stride, 0, tag);
         }
     }
 };
@@ -433,6 +469,11 @@ __device__ __forceinline__ void zrow(const float* t, float (&v)[BZ]) {
 struct LdsRec {
     long long out;
     int idx, stride;
+};
+// Where the data of a thread's receiver node are, if it has one receiver.
+struct LdsNode {
+    long long out;
+    int stride, pad;
 };
 
 // The z axis' coefficient tables (half-node a, b; node a, b) as [4][BZ][64].

@@ -107,13 +107,16 @@ __device__ __forceinline__ void fwd_body(const ResArgs& a, const ResBlock& B, fl
             axn[c] = uniform(on * elem(S.cpml[1], 2 * pl.nx + g));
             bxn[c] = uniform(on * elem(S.cpml[1], 3 * pl.nx + g));
         }
-    // the source node, if this thread owns it
+    gfloat* const seg0 = uniform(S.seg);
+    // the source node, if this thread owns it; its amplitude is loaded a step ahead
     int isrc = -1;
     if (BG && S.src >= 0) {
         const int sz = S.src % (int)pl.ldz, sxc = S.src / (int)pl.ldz - pl.x, k = sz - lane * BZ;
         if (sxc >= 0 && sxc < CX && k >= 0 && k < BZ) isrc = sxc * BZ + k;
     }
     const bool wsrc = __any(isrc >= 0);
+    const auto src_amp = uniform(S.src_amp);
+    float amp = wsrc ? elem(src_amp, a.n0) : 0.f;
 
     Exchange<BZ, NF> X(a, (int)blockIdx.x, B.nb, pl.nv > 0);
     X.me = xcd_remap(blockIdx.x, gridDim.x);
@@ -141,14 +144,14 @@ __device__ __forceinline__ void fwd_body(const ResArgs& a, const ResBlock& B, fl
             a.d[R.out + (long long)n * R.stride] = l[R.idx];
         }
     };
-    unsigned tag = a.tag0 + 1;
+    unsigned tag = X.tag(0);
     if constexpr (BG) share(0, 0, HP, 0, lp, p, tag);
     if constexpr (SC) share(0, 0, HP, IS, lp + IS * LC * ROW, q, tag);
 
     // background of the step, from the replay cache: the gradients a phase ahead
     float cgz[RC ? CX : 1][BZ], cgx[RC ? CX : 1][BZ];
     auto load_seg = [&](int n, int arr, auto& v) {
-        const gfloat* const f = S.seg + ((long long)(a.sstep0 + n - a.n0) * 3 + arr) * pl.segn;
+        const gfloat* const f = seg0 + ((long long)(a.sstep0 + n - a.n0) * 3 + arr) * pl.segn;
 #pragma unroll
         for (int c = 0; c < CX; ++c)
 #pragma unroll
@@ -162,8 +165,7 @@ __device__ __forceinline__ void fwd_body(const ResArgs& a, const ResBlock& B, fl
     res_priority(w);
     for (int n = a.n0; n < a.n1; ++n) {
         const int par = (n - a.n0) & 1;
-        gfloat* const seg = S.seg + (long long)(a.sstep0 + n - a.n0) * 3 * pl.segn;
-        const float amp = BG && S.src >= 0 ? elem(S.src_amp, n) : 0.f;
+        gfloat* const seg = seg0 + (long long)(a.sstep0 + n - a.n0) * 3 * pl.segn;
         float cq[RC ? CX : 1][BZ];
         // ---- velocity phase, z: own columns and lanes
         float ta[BZ], tb[BZ];
@@ -197,7 +199,7 @@ __device__ __forceinline__ void fwd_body(const ResArgs& a, const ResBlock& B, fl
                 }
             }
         }
-        X.template halos<HP, CW, !TIGHT>(w, 0, par, lp, LC * ROW, tag);
+        X.template halo<HP, CW, KIND == R_BORN && TIGHT>(w, 0, par, lp, LC * ROW, tag);
         __syncthreads();
         // loads from the replay cache start right after a fetch, so that the
         // next fetch does not wait behind them
@@ -270,7 +272,7 @@ __device__ __forceinline__ void fwd_body(const ResArgs& a, const ResBlock& B, fl
                 for (int k = 0; k < BZ; ++k) pin(fz[c][k]);
             }
         }
-        X.template halos<HV, CW, !TIGHT>(w, 1, par, lv, LC * ROW, tag);
+        X.template halo<HV, CW, KIND == R_BORN && TIGHT>(w, 1, par, lv, LC * ROW, tag);
         __syncthreads();
         if constexpr (RC)
             if (n + 1 < a.n1) {
@@ -328,9 +330,10 @@ __device__ __forceinline__ void fwd_body(const ResArgs& a, const ResBlock& B, fl
 #pragma unroll
                 for (int k = 0; k < BZ; ++k)
                     if (isrc == c * BZ + k) p[c][k] = p[c][k] + amp;
+            if (n + 1 < a.n1) amp = elem(src_amp, n + 1);
         }
         if (ALIAS) __syncthreads();
-        ++tag;
+        tag = X.tag(n - a.n0 + 1);
         if constexpr (BG) share(0, par ^ 1, HP, 0, lp, p, tag);
         if constexpr (SC) share(0, par ^ 1, HP, IS, lp + IS * LC * ROW, q, tag);
     }

@@ -85,3 +85,13 @@ def test_many_receivers_on_one_slab():
     a, b = _run(torch, w, 0, ckpt_every=8), _run(torch, w, 1, ckpt_every=8)
     for i, (x, y) in enumerate(zip(a, b)):
         assert torch.equal(x, y), i
+
+
+def test_more_launches_than_ids():
+    """Segments of one step: the launches of one migration (two a segment)
+    outnumber the ids that tell their exchanged words apart."""
+    torch = require_gpu()
+    w = synth.small((90, 60), nt=270, npml=6, seed=13, nshot=2)
+    a = _run(torch, w, 0, ckpt_every=1)
+    b = _run(torch, w, 1, ckpt_every=1)
+    assert all(torch.equal(x, y) for x, y in zip(a, b))
