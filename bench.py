@@ -56,6 +56,10 @@ BYTES_PER_PT = {
     3: {"born_v": 64, "born_p": 48, "bg_v": 44, "bg_p": 28, "adj_a": 44, "adj_b": 44},
     # fused 2D schedule: one kernel per step, reported under the velocity-phase class
     "2f": {"born_v": 64, "bg_v": 44, "adj_a": 64},
+    # resident 2D schedule: whole steps, reported under the first class of
+    # each; fields, model and CPML memories stay on the chip, and only the
+    # replay buffer (three values per node) is written or read
+    "2r": {"born_v": 0, "bg_v": 12, "adj_a": 12},
 }
 KERNEL_SYMBOL = {"born_v": "k2_v<*, true, false>", "born_p": "k2_p<*, true, false>",
                  "bg_v": "k2_v<*, false, true>", "bg_p": "k2_p<*, false, true>",
@@ -64,7 +68,8 @@ KERNEL_SYMBOL = {"born_v": "k2_v<*, true, false>", "born_p": "k2_p<*, true, fals
 # the step read once and written once), and the kernels that make up the
 # step in the two-phase schedule.  Every node of a CPML strip adds 16 B per
 # axis whose strip it lies in (two memories read and written).
-STEP_BYTES = {2: {"born": 68, "replay": 48, "adjoint": 64}, 3: {"born": 88, "replay": 64, "adjoint": 80}}
+STEP_BYTES = {2: {"born": 68, "replay": 48, "adjoint": 64}, 3: {"born": 88, "replay": 64, "adjoint": 80},
+              "2r": {"born": 0, "replay": 12, "adjoint": 12}}
 STEP_KERNELS = {"born": ("born_v", "born_p"), "replay": ("bg_v", "bg_p"), "adjoint": ("adj_a", "adj_b")}
 STRIP_BYTES = 16
 
@@ -412,15 +417,18 @@ def main():
     # minimum bytes per padded node (each array of one time step read and
     # written once) plus the CPML strip surcharge, over the summed average
     # durations of the step's kernels
+    resident = nd == 2 and not sz["fused"] and kcnt["bg_v"] > 0 and kcnt["bg_p"] == 0
+    if resident:
+        btab = BYTES_PER_PT["2r"]
     pts_per_launch = padded / sz["groups"]
-    strip_per_launch = STRIP_BYTES * strip_nodes(w) / sz["groups"]
+    strip_per_launch = 0 if resident else STRIP_BYTES * strip_nodes(w) / sz["groups"]
     ptag = tag + ("_fused" if (nd == 2 and sz["fused"]) else "")
     kernels = {}
     for k in lsrtm.KERNEL_NAMES:
         if kcnt[k] == 0:
             continue
         t = kms[k] / kcnt[k] * 1e-3
-        tr = read_traffic(ptag, k, pts_per_launch, nd) if k in btab else None
+        tr = read_traffic(ptag, k, pts_per_launch, nd) if k in btab and not resident else None
         gbs = btab[k] * pts_per_launch / t / 1e9 if k in btab else None
         kernels[k] = {"avg_ms": t * 1e3, "launches_timed": kcnt[k], "GBs": gbs,
                       "frac": gbs / HBM_PEAK_GBS if gbs else None,
@@ -429,12 +437,12 @@ def main():
     steps = {}
     fused = nd == 2 and sz["fused"]
     for name, ks in STEP_KERNELS.items():
-        ks = tuple(k for k in ks if k in btab) if fused else ks
+        ks = tuple(k for k in ks if k in btab) if fused or resident else ks
         if not ks or any(kcnt[k] == 0 for k in ks):
             continue
         t = sum(kms[k] / kcnt[k] for k in ks) * 1e-3
-        byt = STEP_BYTES[nd][name] * pts_per_launch + strip_per_launch
-        trs = [read_traffic(ptag, k, pts_per_launch, nd) for k in ks]
+        byt = STEP_BYTES["2r" if resident else nd][name] * pts_per_launch + strip_per_launch
+        trs = [None if resident else read_traffic(ptag, k, pts_per_launch, nd) for k in ks]
         steps[name] = {"kernels": list(ks), "step_ms": t * 1e3, "bytes_per_launch": byt,
                        "GBs": byt / t / 1e9, "frac": byt / t / 1e9 / HBM_PEAK_GBS,
                        "traffic": sum(trs) if all(trs) else None}
@@ -619,9 +627,9 @@ def main():
                    "tile_adj_a": list(lsrtm.tile_shape(nd, sz["tile_adj_a"])) if sz["tile_adj_a"] >= 0 else None,
                    "ckpt_dtype": ckdt,
                    "ckpt_per_group": bool(sz["ckpt_per_group"]),
-                   "schedule": "fused step" if sz["fused"] else "two-phase step",
+                   "schedule": "fused step" if sz["fused"] else "resident steps" if resident else "two-phase step",
                    "parallelism": "shots batched on 1 GPU"},
-        "roofline": {"bound": "hbm", "kernel": f"{dom} step ({' + '.join(ds['kernels'])})" if ds else None,
+        "roofline": {"bound": "issue and exchange latency" if resident else "hbm", "kernel": f"{dom} step ({' + '.join(ds['kernels'])})" if ds else None,
                      "achieved": ds.get("GBs"), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": ds.get("frac"), "traffic": ds.get("traffic"),
                      "bytes_per_launch": ds.get("bytes_per_launch"), "avg_launch_ms": ds.get("step_ms"),
@@ -631,7 +639,7 @@ def main():
                      "dominant_kernel": {"kernel": dk, "GBs": kernels[dk]["GBs"], "frac": kernels[dk]["frac"],
                                          "above_streaming_rate": kernels[dk]["above_streaming_rate"]},
                      "streaming_GBs": stream_gbs},
-        "steps": steps,
+        "time_steps": steps,
         "cpu_baseline": cpu,
         "cg_iter_s_batched": sec,
         "cg_iter_s_direct_launches": sec_direct,

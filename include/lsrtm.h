@@ -376,7 +376,9 @@ lsrtm_status lsrtm_set_option(lsrtm_ctx* ctx, int key, long long value);
  * launch, ms per time step, velocity-phase tile, adjoint-A tile).  With
  * LSRTM_TUNE_CACHE naming a file, results are read from and appended to it.
  * Invalidates stored checkpoints.  When no tile is set, the same tile tuning
- * (without group sizes and schedules) runs on the first pass by itself.
+ * (without group sizes and schedules) runs on the first pass by itself,
+ * unless the passes take the resident kernels (LSRTM_OPT_RESIDENT), which
+ * have no tiles.
  * Errors: EINVAL (NULL ctx, nsteps < 1), ESTATE (no model or acquisition),
  * ENOMEM, EHIP. */
 lsrtm_status lsrtm_autotune(lsrtm_ctx* ctx, int nsteps, int tune_groups, double* out);
@@ -406,8 +408,8 @@ lsrtm_status lsrtm_stats(lsrtm_ctx* ctx, double* out, int nout);
 
 /* Tile shape of a tile id: out[0] = BZ, out[1] = BX.  Returns LSRTM_EINVAL
  * for an unknown id.  HOST int [2].  In 3D an id also fixes the threads per
- * block and the planes a tile marches through (results are the same bits
- * for every id):
+ * block and the most planes a tile marches through (launches of few blocks
+ * take shorter marches; results are the same bits for every id):
  *   0: 64 x 4 (256 threads, 32 planes)   1: 64 x 8 (256, 32)
  *   2: 64 x 8 (256, 64)                  3: 32 x 8 (256, 64)
  *   4: 128 x 4 (256, 64)                 5: 64 x 4 (256, 64)

@@ -1190,8 +1190,6 @@ lsrtm_status plan_resident(lsrtm_ctx* c) {
                 const int cxe = res_cx_edge(L.cx), row = bz * 64;
                 std::vector<ResBlock> blocks;
                 std::vector<int> first(gr.ns + 1, 0);
-                std::vector<std::vector<Rec>> per;
-                std::vector<std::vector<int4>> nodes;
                 std::vector<std::vector<int>> of(gr.ns);   // workgroup of every column
                 for (int s = i; s < i + take[i]; ++s) {
                     const int nx = gr.h_slots[s].n[1];
@@ -1206,43 +1204,48 @@ lsrtm_status plan_resident(lsrtm_ctx* c) {
                 }
                 L.nblocks = (int)blocks.size();
                 int most = 0;
+                const auto from = [&](int s) {   // receivers are in slot order
+                    return std::lower_bound(gr.h_rec.begin(), gr.h_rec.end(), s,
+                                            [](const Rec& R, int v) { return R.slot < v; });
+                };
                 if (kind == R_BG || kind == R_BORN || kind == R_BORN_RC) {
-                    per.resize(blocks.size());
-                    for (const Rec& R : gr.h_rec) {
-                        if (R.slot < i || R.slot >= i + take[i]) continue;
-                        const int ldz = gr.h_slots[R.slot].ldz, x = R.idx / ldz, z = R.idx % ldz;
-                        const int b = of[R.slot][x];
-                        Rec T = R;
-                        T.idx = (x - blocks[b].x0 + HW) * row + (z % bz) * 64 + z / bz;
-                        per[b].push_back(T);
+                    const auto r0 = from(i), r1 = from(i + take[i]);
+                    std::vector<int> ptr(blocks.size() + 1, 0), at(r1 - r0);
+                    for (auto R = r0; R != r1; ++R) ptr[1 + (at[R - r0] = of[R->slot][R->idx / gr.h_slots[R->slot].ldz])] += 1;
+                    for (size_t b = 0; b < blocks.size(); ++b) {
+                        most = std::max(most, ptr[b + 1]);
+                        ptr[b + 1] += ptr[b];
                     }
-                    std::vector<int> ptr(1, 0);
-                    std::vector<Rec> all;
-                    for (auto& v : per) {
-                        most = std::max(most, (int)v.size());
-                        all.insert(all.end(), v.begin(), v.end());
-                        ptr.push_back((int)all.size());
+                    std::vector<Rec> all(r1 - r0);
+                    std::vector<int> next(ptr);
+                    for (auto R = r0; R != r1; ++R) {
+                        const int ldz = gr.h_slots[R->slot].ldz, x = R->idx / ldz, z = R->idx % ldz, b = at[R - r0];
+                        Rec T = *R;
+                        T.idx = (x - blocks[b].x0 + HW) * row + (z % bz) * 64 + z / bz;
+                        all[next[b]++] = T;
                     }
                     L.rptr = add_table(tab, ptr);
                     L.rec = add_table(tab, all);
                 }
                 if (kind == R_ADJ) {
-                    nodes.resize(blocks.size());
-                    for (int u = 0; u < gr.nnode; ++u) {
-                        const int s = gr.h_node_slot[u];
-                        if (s < i || s >= i + take[i]) continue;
-                        const int ldz = gr.h_slots[s].ldz, x = gr.h_node_idx[u] / ldz, z = gr.h_node_idx[u] % ldz;
+                    // nodes are in the order of slots and columns, hence of workgroups
+                    const auto u0 = std::lower_bound(gr.h_node_slot.begin(), gr.h_node_slot.end(), i) - gr.h_node_slot.begin();
+                    const auto u1 = std::lower_bound(gr.h_node_slot.begin(), gr.h_node_slot.end(), i + take[i]) - gr.h_node_slot.begin();
+                    std::vector<int> ptr(blocks.size() + 1, 0);
+                    std::vector<int4> all;
+                    all.reserve(u1 - u0);
+                    for (auto u = u0; u < u1; ++u) {
+                        const int s = gr.h_node_slot[u], ldz = gr.h_slots[s].ldz, x = gr.h_node_idx[u] / ldz, z = gr.h_node_idx[u] % ldz;
                         const int b = of[s][x], cw = (blocks[b].nb & 4) ? cxe : L.cx, j = x - blocks[b].x0;
                         const int owner = (j / cw) * 64 + z / bz, bit = (j % cw) * bz + z % bz;
-                        nodes[b].push_back(make_int4(owner << 8 | bit, gr.h_node_ptr[u], gr.h_node_ptr[u + 1], 0));
+                        all.push_back(make_int4(owner << 8 | bit, gr.h_node_ptr[u], gr.h_node_ptr[u + 1], 0));
+                        ptr[b + 1] += 1;
                     }
-                    std::vector<int> ptr(1, 0);
-                    std::vector<int4> all;
-                    for (auto& v : nodes) {
-                        std::sort(v.begin(), v.end(), [](const int4& a, const int4& b) { return a.x < b.x; });
-                        all.insert(all.end(), v.begin(), v.end());
-                        ptr.push_back((int)all.size());
-                        L.maxnodes = most = std::max(most, (int)v.size());
+                    for (size_t b = 0; b < blocks.size(); ++b) {
+                        L.maxnodes = most = std::max(most, ptr[b + 1]);
+                        ptr[b + 1] += ptr[b];
+                        std::sort(all.begin() + ptr[b], all.begin() + ptr[b + 1],
+                                  [](const int4& a, const int4& b) { return a.x < b.x; });
                     }
                     L.nptr = add_table(tab, ptr);
                     L.node = add_table(tab, all);
@@ -1382,6 +1385,10 @@ lsrtm_status plan(lsrtm_ctx* c) {
     // does not fit, only the shots of the active launch group hold them and
     // each migration pass first re-runs the group's background.
     const int G0 = c->opt_spl > 0 ? std::min(c->opt_spl, nshot) : nshot;
+    // Where checkpoints are rounded the interval shows in the results: there
+    // it is planned without the resident layout's larger replay buffer.
+    const bool rounds = c->g.ckpt_dtype != 0 && c->g.ckpt_every <= 0;
+    const auto seg_pts = [&](const Window& W) { return rounds ? W.npts : W.segn; };
     int G = G0, k = 1;
     long long need = 0;
     bool ckg = false, fits = false;
@@ -1396,7 +1403,7 @@ lsrtm_status plan(lsrtm_ctx* c) {
                     long long cur = 0, seg = 0;
                     for (int e = 0; e < gs; ++e, ++s) {
                         cur += c->wins[c->shots[s].win].npts;
-                        seg += c->wins[c->shots[s].win].segn;
+                        seg += seg_pts(c->wins[c->shots[s].win]);
                     }
                     grp_pts = std::max(grp_pts, cur);
                     grp_seg = std::max(grp_seg, seg);
@@ -1443,7 +1450,7 @@ lsrtm_status plan(lsrtm_ctx* c) {
                 long long cur = 0, seg = 0;
                 for (int e = 0; e < gs; ++e, ++s) {
                     cur += c->wins[c->shots[s].win].npts;
-                    seg += c->wins[c->shots[s].win].segn;
+                    seg += seg_pts(c->wins[c->shots[s].win]);
                 }
                 grp_pts = std::max(grp_pts, cur);
                 grp_seg = std::max(grp_seg, seg);
@@ -1482,6 +1489,22 @@ lsrtm_status plan(lsrtm_ctx* c) {
         if (bk != k) {
             k = bk;
             need = need_of(k);
+        }
+    }
+    if (rounds && c->res_bz) {
+        long long more = 0;      // of the resident layout's replay buffer
+        int s = 0;
+        for (int gs : group_sizes(nshot, G)) {
+            long long d = 0;
+            for (int e = 0; e < gs; ++e, ++s) d += c->wins[c->shots[s].win].segn - c->wins[c->shots[s].win].npts;
+            more = std::max(more, d);
+        }
+        more *= (long long)k * (nd + 1) * 4;
+        if (need + more <= budget) {
+            need += more;
+        } else {
+            c->res_bz = 0;
+            for (auto& W : c->wins) W.segn = W.npts;
         }
     }
     c->ck_group = ckg;

@@ -95,3 +95,18 @@ def test_more_launches_than_ids():
     a = _run(torch, w, 0, ckpt_every=1)
     b = _run(torch, w, 1, ckpt_every=1)
     assert all(torch.equal(x, y) for x, y in zip(a, b))
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_interval_of_rounded_checkpoints(dtype):
+    """16-bit checkpoints round the state at every interval, so the interval
+    that the planner picks is that of a plan without the resident layout's
+    larger replay buffer (the fused schedule's, which has no resident form)."""
+    torch = require_gpu()
+    w = synth.small((117, 60), nt=300, npml=6, seed=21, nshot=3)
+    picked = []
+    for fused in (False, True):
+        ctx = lsrtm.context_for(w, tile=1, ckpt_dtype=dtype, fused=fused)
+        picked.append(ctx.sizes()["ckpt_every"])
+        ctx.close()
+    assert picked[0] == picked[1]
