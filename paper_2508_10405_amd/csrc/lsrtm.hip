@@ -448,28 +448,41 @@ void tile_shape(int ndim, int id, int* bz, int* bx, int* by) {
     }
 }
 
-// Planes of a 3D march of a group: the shape's own number, or fewer where that
-// many would leave the GPU idle.  A launch takes about the planes of one march
-// (a plane is a chain of loads and two barriers) plus the four that filling the
-// y-queues costs, times the rounds in which its blocks find room (three blocks
-// of 256 threads on each of 256 CUs).  Two shots of 60 x 84 x 68 nodes: 66
-// blocks of 32 planes took 39 us per launch; large grids keep their shape's
-// planes, whose queues are refilled least often.
+// Planes of a 3D march: at most the shape's.  What a launch takes comes from two
+// things, in units of a plane: the planes of all blocks, each with the three that filling
+// its y-queues costs, over the blocks that run at once (three of 256 threads
+// with two nodes each on every one of 256 CUs), and the march of one block, a
+// chain of loads and barriers, that the last blocks leave at the end.  The
+// longer one counts in full, the other by half: long marches leave CUs idle
+// at the end, short ones refill the queues.  Migrations of 60 steps with the
+// shape's 32 planes and with the planes picked here: 3 shots of 141 x 241 x 241
+// 86.7 and 78.0 ms (22 planes), 3 of 150 x 240 x 130 54.2 and 45.5 (19), one of 120 x 220 x 220
+// 25.8 and 21.2 (10); a Born pass over 240 x 440 x 440 keeps its 32 (91.2; 24
+// planes 93.6, 44 93.8).  Two shots of 60 x 84 x 68 nodes, of which 66 blocks of
+// 32 planes took 39 us per launch, take marches of two.
 int march_planes(const Group& gr, int bz, int bx, int by) {
-    constexpr long long room = 768;
-    int best = by;
-    long long least = LLONG_MAX;
-    for (int l = by; l >= 1; l /= 2) {
-        long long blocks = 0;
+    const double room = 768.0 * 64 * 8 / (bz * bx);
+    int ny = 1;
+    for (const Slot& S : gr.h_slots) ny = std::max(ny, S.n[2]);
+    int best = by, own = by;
+    double least = 1e30, of_own = 0.0;
+    for (int n = (ny + by - 1) / by; n <= ny; ++n) {
+        const int l = (ny + n - 1) / n;          // n marches of about the same length
+        double planes = 0.0;
         for (const Slot& S : gr.h_slots)
-            blocks += (long long)((S.n[0] + bz - 1) / bz) * ((S.n[1] + bx - 1) / bx) * ((S.n[2] + l - 1) / l);
-        const long long cost = (blocks + room - 1) / room * (l + 4);
+            planes += (double)((S.n[0] + bz - 1) / bz) * ((S.n[1] + bx - 1) / bx) * (S.n[2] + 3.0 * ((S.n[2] + l - 1) / l));
+        const double all = planes / room, one = l + 3.0;
+        const double cost = std::max(all, one) + 0.5 * std::min(all, one);
         if (cost < least) {
             least = cost;
             best = l;
         }
+        if (of_own == 0.0) {
+            own = l;                             // the longest
+            of_own = cost;
+        }
     }
-    return best;
+    return least < 0.995 * of_own ? best : own;  // shorter ones have to pay
 }
 
 // Tile table of a group: (slot, z0, x0, w) of every tile of every slot; in
