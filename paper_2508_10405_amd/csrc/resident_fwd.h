@@ -339,6 +339,7 @@ __device__ __forceinline__ void fwd_body(const ResArgs& a, const ResBlock& B, fl
     }
     __syncthreads();
     record(a.n1 - 1);
+    if constexpr (SEGW) return;      // the next segment starts from its checkpoint
     pl.forget();
     if constexpr (BG) {
         pl.put(S.p, p);

@@ -110,3 +110,19 @@ def test_interval_of_rounded_checkpoints(dtype):
         picked.append(ctx.sizes()["ckpt_every"])
         ctx.close()
     assert picked[0] == picked[1]
+
+
+def test_groups_of_whole_rounds():
+    """Groups of unequal size (9 and 7 of 16 shots, 7 of them to a round):
+    data and image are those of one shot per launch."""
+    torch = require_gpu()
+    w = synth.small((48, 765), nt=12, npml=6, seed=17, nshot=16)
+    got = []
+    for spl in (9, 1):
+        ctx = lsrtm.context_for(w, tile=1, shots_per_launch=spl, ckpt_every=5)
+        if spl > 1:
+            assert ctx.sizes()["shots_per_launch"] == 9 and ctx.sizes()["groups"] == 2
+        d = ctx.born(to_dev(torch, w.dm))
+        got.append((d, ctx.adjoint(d)))
+        ctx.close()
+    assert all(torch.equal(x, y) for x, y in zip(*got))
