@@ -16,7 +16,7 @@
 // buffer's traffic.  Measured on 120 shots of 280 x 777 padded nodes, a Born
 // pass of 600 steps went from 219 to 80 ms, a migration pass of 500 steps from
 // 298 to 113 ms; on one shot of 140 x 240, 1000 steps, from 8.7 to 3.9 ms and
-// from 17.6 to 6.6 ms, where it is the launches that no longer count.
+// from 17.6 to 6.5 ms, where it is the launches that no longer count.
 #pragma once
 #include "common.h"
 
