@@ -181,7 +181,7 @@ struct lsrtm_ctx {
     bool cg_pre = false;           // the current CG run is preconditioned
     // PSF Hessian (image domain)
     int* psf_tab = nullptr;        // corner/weight tables of psf_spacing
-    int psf_spacing = 0;
+    int psf_spacing = 0;           // that the tables are of (0: none)
     Psf2Args psf2{};               // 2D products at psf_spacing
     bool psf2_ok = false;
     int4* psf_pieces = nullptr;
@@ -2579,13 +2579,14 @@ static lsrtm_status psf2_setup(lsrtm_ctx* c, const PsfArgs& pa, int s) {
             c->allocs.erase(std::find(c->allocs.begin(), c->allocs.end(), *p));
             *p = nullptr;
         }
+        // without room for them the products take the gathers
         if (p == (void**)&c->psf_pack) {
             c->psf_npack = 0;
-            CHK(dalloc_t(c, &c->psf_pack, npack, false));
+            if (dalloc_t(c, &c->psf_pack, npack, false) != LSRTM_OK) return LSRTM_OK;
             c->psf_npack = npack;
         } else {
             c->psf_npieces = 0;
-            CHK(dalloc_t(c, &c->psf_pieces, all.size(), false));
+            if (dalloc_t(c, &c->psf_pieces, all.size(), false) != LSRTM_OK) return LSRTM_OK;
             c->psf_npieces = all.size();
         }
     }
@@ -2652,6 +2653,7 @@ static lsrtm_status psf_setup(lsrtm_ctx* c, const float* psf, int spacing, int m
     }
     // kernels of earlier calls may still read the tables
     HIPCHK(c, hipStreamSynchronize(c->st));
+    c->psf_spacing = 0;            // of no spacing until all of them are there
     HIPCHK(c, hipMemcpy(c->psf_tab, tab.data(), tab.size() * sizeof(int), hipMemcpyHostToDevice));
     CHK(psf2_setup(c, *a, spacing));
     c->psf_spacing = spacing;

@@ -185,3 +185,44 @@ def test_psf_products_by_corner(torch, n, spacing, mono):
         y = ctx.psf_apply(psf, spacing, x, transpose=tr, mono=mono).double().cpu().numpy().reshape(nb, nx, nz)
         assert np.linalg.norm(y - ref) <= 1e-6 * np.linalg.norm(ref), (tr, np.linalg.norm(y - ref) / np.linalg.norm(ref))
     ctx.close()
+
+
+def test_psf_tables_without_room_for_windows(torch):
+    """A spacing whose packed windows (4 floats per node at spacing 7) find no
+    device memory is served by the gathers, and leaves nothing behind that a
+    call at the spacing before it could take for its own."""
+    nz, nx = 3000, 2800
+    g = torch.Generator(device="cuda").manual_seed(4)
+    ctx = lsrtm.Context((nz, nx), (10.0, 10.0), 10, 1e-3)
+    psf = torch.randn((2, 2, nx, nz), generator=g, device="cuda")
+    x = torch.randn((2, nx, nz), generator=g, device="cuda")
+    y3 = ctx.psf_apply(psf, 3, x)
+    torch.cuda.synchronize()
+    # take all there is, then give the allocator back the outputs of the calls below
+    held = [torch.empty(torch.cuda.mem_get_info()[0] - (1 << 30), dtype=torch.uint8, device="cuda")]
+    spare = []
+    for size, to in ((x.nbytes, spare), (16 << 20, held)):
+        while True:
+            try:
+                to.append(torch.empty(size, dtype=torch.uint8, device="cuda"))
+            except torch.OutOfMemoryError:
+                break
+    assert len(spare) >= 3
+    del spare[-3:]
+    y7, failed = None, None
+    try:
+        y7 = ctx.psf_apply(psf, 7, x)
+    except lsrtm.LsrtmError as e:
+        failed = e
+    again = ctx.psf_apply(psf, 3, x)
+    torch.cuda.synchronize()
+    del held, spare, to
+    torch.cuda.empty_cache()
+    assert torch.equal(again, y3)
+    assert failed is None, failed
+    fresh = lsrtm.Context((nz, nx), (10.0, 10.0), 10, 1e-3)
+    ref = fresh.psf_apply(psf, 7, x)
+    # sums of 49 * 8 terms in FP32, in two orders
+    assert float((y7 - ref).double().norm() / ref.double().norm()) <= 1e-6
+    ctx.close()
+    fresh.close()
