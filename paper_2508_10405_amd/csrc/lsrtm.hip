@@ -2517,7 +2517,7 @@ lsrtm_status lsrtm_cgnr_state(lsrtm_ctx* c, int get, float* r, float* z, float* 
 // of the taps per axis, else pieces of 10 points, which fill a wave; at most 16.
 static lsrtm_status psf2_setup(lsrtm_ctx* c, const PsfArgs& pa, int s) {
     c->psf2_ok = false;
-    if (c->ndim != 2 || s < 4) return LSRTM_OK;
+    if (c->ndim != 2 || pa.W < 2) return LSRTM_OK;
     Psf2Args& a = c->psf2;
     const int W = pa.W;
     a.s = s;

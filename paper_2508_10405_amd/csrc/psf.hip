@@ -26,8 +26,11 @@
 // What bounds them is the multiply-adds: 361 taps x 4 corners x 4 blocks per
 // point for H^T at spacing 20; H visits 9 corners, with the taps that a piece
 // of outputs cannot use left out.  The gathers stay for 3D, for windows whose
-// patch of x does not fit in LDS and for spacings below 4, whose windows of 1 or
-// 9 taps leave nothing to share (2: 23 and 21 us against 35 and 37).  Measured
+// patch of x does not fit in LDS and for spacings below 5, whose windows of 1 or
+// 9 taps leave nothing to share (calls of H and H^T with both parameters, gathers
+// and corners: 500 x 1000 at spacing 4 97 and 98 us against 117 and 133, 40 x 52 46
+// against 46; at spacing 5 and its 25 taps the corners win on every grid timed,
+// 20 x 30 to 500 x 1000).  Measured
 // on 240 x 737, both parameters, H and H^T: spacing 20 1258 and 1231 -> 146 and
 // 122 us, 12 438 and 427 -> 75 and 49, 6 109 and 105 -> 43 and 26.
 #include <algorithm>
