@@ -137,6 +137,8 @@ struct Psf2Args {
     int off[2];
     const float* psf;
     float* pack;           // [corner][2 W + 1][2 W + 1][blocks]
+    int* bad;              // number of the last packing that met a sample that is not finite
+    int packing;           // number of the packing in use, from 1
     const int4 *tz, *tx;   // pieces of H^T: (start, length, lower corner, upper corner)
     const int4 *fz, *fx;   // pieces of H: (start, length, first corner, last corner)
     int ntz, ntx, nfz, nfx;

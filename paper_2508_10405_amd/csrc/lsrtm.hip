@@ -188,6 +188,7 @@ struct lsrtm_ctx {
     size_t psf_npieces = 0;
     float* psf_pack = nullptr;
     long long psf_npack = 0;
+    int* psf_bad = nullptr;
     float* psf_dm = nullptr;       // [2][gpts] scatterer model
     float* psf_d = nullptr;        // data of the scatterer model
     float* psf_v[4] = {nullptr, nullptr, nullptr, nullptr};   // image-domain CG: r, z, p, w
@@ -2590,6 +2591,11 @@ static lsrtm_status psf2_setup(lsrtm_ctx* c, const PsfArgs& pa, int s) {
             c->psf_npieces = all.size();
         }
     }
+    if (!c->psf_bad) {
+        if (dalloc_t(c, &c->psf_bad, 1, false) != LSRTM_OK) return LSRTM_OK;
+        HIPCHK(c, launch_fill(reinterpret_cast<float*>(c->psf_bad), 1, 0.f, c->st));
+    }
+    a.bad = c->psf_bad;
     HIPCHK(c, hipMemcpy(c->psf_pieces, all.data(), all.size() * sizeof(int4), hipMemcpyHostToDevice));
     a.pack = c->psf_pack;
     a.tz = c->psf_pieces;
@@ -2676,6 +2682,10 @@ static lsrtm_status psf2_pack(lsrtm_ctx* c, const PsfArgs& a) {
     if (!c->psf2_ok) return LSRTM_OK;
     c->psf2.mono = a.mono;
     c->psf2.psf = a.psf;
+    if (c->psf2.packing++ == INT_MAX) {
+        HIPCHK(c, launch_fill(reinterpret_cast<float*>(c->psf_bad), 1, 0.f, c->st));
+        c->psf2.packing = 1;
+    }
     HIPCHK(c, launch_psf_pack(c->psf2, c->st));
     return LSRTM_OK;
 }

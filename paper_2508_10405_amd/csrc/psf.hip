@@ -88,51 +88,54 @@ __device__ __forceinline__ void corner_sum(const PsfArgs& a, const Cell (&cl)[3]
     }
 }
 
-__global__ void k_psf_apply(PsfArgs a, const float* __restrict__ x, float* __restrict__ y, int transpose) {
-    const long long N = a.N;
+// One output point of H x or H^T x by gathers: acc[v], v < 1 (mono) or 2.
+__device__ __forceinline__ void gather_point(const PsfArgs& a, const float* __restrict__ x, int transpose, int iz, int ix,
+                                             int iy, float (&acc)[2]) {
     const int nb = a.mono ? 1 : 2;
     const int Wy = a.ndim == 3 ? a.W : 0;
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < N;
-         i += (long long)gridDim.x * blockDim.x) {
-        const int iz = (int)(i % a.n[0]);
-        const long long r = i / a.n[0];
-        const int ix = (int)(r % a.n[1]);
-        const int iy = (int)(r / a.n[1]);
-        float acc[2] = {0.f, 0.f};
-        Cell cl[3];
-        if (transpose) {
-            cl[0] = cell_of(a, 0, iz);
-            cl[1] = cell_of(a, 1, ix);
-            cl[2] = a.ndim == 3 ? cell_of(a, 2, iy) : Cell{0, 0, 0.f};
-        }
-        for (int oy = -Wy; oy <= Wy; ++oy)
-            for (int ox = -a.W; ox <= a.W; ++ox)
-                for (int oz = -a.W; oz <= a.W; ++oz) {
-                    // forward: source point j = i - o; transpose: partner i + o
-                    const int sgn = transpose ? 1 : -1;
-                    const int jz = iz + sgn * oz, jx = ix + sgn * ox, jy = iy + sgn * oy;
-                    if ((unsigned)jz >= (unsigned)a.n[0] || (unsigned)jx >= (unsigned)a.n[1] ||
-                        (unsigned)jy >= (unsigned)a.n[2])
-                        continue;
-                    if (!transpose) {
-                        cl[0] = cell_of(a, 0, jz);
-                        cl[1] = cell_of(a, 1, jx);
-                        cl[2] = a.ndim == 3 ? cell_of(a, 2, jy) : Cell{0, 0, 0.f};
-                    }
-                    float hs[2][2];
-                    corner_sum(a, cl, oz, ox, oy, hs);
-                    const long long jl = jz + (long long)a.n[0] * (jx + (long long)a.n[1] * jy);
-                    for (int u = 0; u < nb; ++u) {
-                        const float xv = x[u * N + jl];
-                        for (int v = 0; v < nb; ++v) {
-                            // forward: y_p += H_pq x_q (u = q, v = p);
-                            // transpose: y_q += H_pq x_p (u = p, v = q)
-                            const float hv = transpose ? hs[u][v] : hs[v][u];
-                            acc[v] = fmaf(hv, xv, acc[v]);
-                        }
+    Cell cl[3];
+    if (transpose) {
+        cl[0] = cell_of(a, 0, iz);
+        cl[1] = cell_of(a, 1, ix);
+        cl[2] = a.ndim == 3 ? cell_of(a, 2, iy) : Cell{0, 0, 0.f};
+    }
+    for (int oy = -Wy; oy <= Wy; ++oy)
+        for (int ox = -a.W; ox <= a.W; ++ox)
+            for (int oz = -a.W; oz <= a.W; ++oz) {
+                // forward: source point j = i - o; transpose: partner i + o
+                const int sgn = transpose ? 1 : -1;
+                const int jz = iz + sgn * oz, jx = ix + sgn * ox, jy = iy + sgn * oy;
+                if ((unsigned)jz >= (unsigned)a.n[0] || (unsigned)jx >= (unsigned)a.n[1] ||
+                    (unsigned)jy >= (unsigned)a.n[2])
+                    continue;
+                if (!transpose) {
+                    cl[0] = cell_of(a, 0, jz);
+                    cl[1] = cell_of(a, 1, jx);
+                    cl[2] = a.ndim == 3 ? cell_of(a, 2, jy) : Cell{0, 0, 0.f};
+                }
+                float hs[2][2];
+                corner_sum(a, cl, oz, ox, oy, hs);
+                const long long jl = jz + (long long)a.n[0] * (jx + (long long)a.n[1] * jy);
+                for (int u = 0; u < nb; ++u) {
+                    const float xv = x[u * a.N + jl];
+                    for (int v = 0; v < nb; ++v) {
+                        // forward: y_p += H_pq x_q (u = q, v = p);
+                        // transpose: y_q += H_pq x_p (u = p, v = q)
+                        const float hv = transpose ? hs[u][v] : hs[v][u];
+                        acc[v] = fmaf(hv, xv, acc[v]);
                     }
                 }
-        for (int v = 0; v < nb; ++v) y[v * N + i] = acc[v];
+            }
+}
+
+__global__ void k_psf_apply(PsfArgs a, const float* __restrict__ x, float* __restrict__ y, int transpose) {
+    const int nb = a.mono ? 1 : 2;
+    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < a.N;
+         i += (long long)gridDim.x * blockDim.x) {
+        const long long r = i / a.n[0];
+        float acc[2] = {0.f, 0.f};
+        gather_point(a, x, transpose, (int)(i % a.n[0]), (int)(r % a.n[1]), (int)(r / a.n[1]), acc);
+        for (int v = 0; v < nb; ++v) y[v * a.N + i] = acc[v];
     }
 }
 
@@ -140,8 +143,10 @@ constexpr int PSF_WAVES = 3;
 
 // Corner windows packed as [corner][ox][oz][block], corner = kx Kz + kz, the
 // blocks (q, p) of one tap together, zero where c + o lies outside the grid.
+// A sample that is no finite number is noted under the number of this packing.
 __global__ void k_psf_pack(Psf2Args a) {
     const int D = 2 * a.W + 1, nb = a.mono ? 1 : 4;
+    bool finite = true;
     const long long n = (long long)a.K[0] * a.K[1] * D * D * nb;
     for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < n; e += (long long)gridDim.x * blockDim.x) {
         const int m = a.mono ? 3 : (int)(e % nb);            // block q * 2 + p
@@ -150,7 +155,35 @@ __global__ void k_psf_pack(Psf2Args a) {
         r /= D;
         const int ox = (int)(r % D), k = (int)(r / D);
         const int z = (k % a.K[0]) * a.s + oz, x = (k / a.K[0]) * a.s + ox;   // c - W = k s
-        a.pack[e] = z < a.n[0] && x < a.n[1] ? a.psf[m * a.N + (z + (long long)a.n[0] * x)] : 0.f;
+        const float f = z < a.n[0] && x < a.n[1] ? a.psf[m * a.N + (z + (long long)a.n[0] * x)] : 0.f;
+        a.pack[e] = f;
+        finite = finite && isfinite(f);
+    }
+    if (!finite) atomicMax(a.bad, a.packing);
+}
+
+// The corner sums multiply samples by weights and by staged values that are
+// zero where the definition leaves the term out, which is the same only for
+// finite samples.  With any other among the samples, a block serves its piece
+// (lz x lx points from (z0, x0)) by gathers.
+__device__ __forceinline__ void gather_piece(const Psf2Args& a, const float* __restrict__ x, float* __restrict__ y,
+                                             int transpose, int z0, int lz, int x0, int lx) {
+    PsfArgs g;
+    g.ndim = 2;
+    g.W = a.W;
+    g.mono = a.mono;
+    g.N = a.N;
+    g.tab = a.tab;
+    g.psf = a.psf;
+    for (int ax = 0; ax < 3; ++ax) {
+        g.n[ax] = ax < 2 ? a.n[ax] : 1;
+        g.off[ax] = ax < 2 ? a.off[ax] : 0;
+    }
+    for (int e = threadIdx.x; e < lz * lx; e += blockDim.x) {
+        const int z = z0 + e % lz, c = x0 + e / lz;
+        float acc[2] = {0.f, 0.f};
+        gather_point(g, x, transpose, z, c, 0, acc);
+        for (int v = 0; v < (a.mono ? 1 : 2); ++v) y[v * a.N + z + (long long)a.n[0] * c] = acc[v];
     }
 }
 
@@ -171,6 +204,7 @@ __global__ void __launch_bounds__(SPLIT * NTHREADS) k_psf_t(Psf2Args a, const fl
     const int W = a.W, D = 2 * W + 1;
     const int4 sz = a.tz[blockIdx.x % a.ntz], sx = a.tx[blockIdx.x / a.ntz];   // (start, length, corner, corner)
     const int lz = sz.y, lx = sx.y, pz = lz + 2 * W + 1, px = lx + 2 * W;
+    const int bad = *a.bad;
     for (int e = threadIdx.x; e < pz * px; e += SPLIT * NTHREADS) {
         const int jz = sz.x - W + e % pz, jx = sx.x - W + e / pz;
         const bool in = (unsigned)jz < (unsigned)a.n[0] && (unsigned)jx < (unsigned)a.n[1];
@@ -178,6 +212,10 @@ __global__ void __launch_bounds__(SPLIT * NTHREADS) k_psf_t(Psf2Args a, const fl
         for (int p = 0; p < NB; ++p) xs[p * pz * px + e] = in ? x[p * a.N + jz + (long long)a.n[0] * jx] : 0.f;
     }
     __syncthreads();
+    if (bad >= a.packing) {
+        gather_piece(a, x, y, 1, sz.x, lz, sx.x, lx);
+        return;
+    }
     const long long win = (long long)D * D * NB * NB;
     const float* P[4];
 #pragma unroll
@@ -260,6 +298,10 @@ __global__ void __launch_bounds__(64 * PSF_WAVES) k_psf_f(Psf2Args a, const floa
     const int4 sz = a.fz[blockIdx.x % a.nfz], sx = a.fx[blockIdx.x / a.nfz];   // (start, length, corners first .. last)
     const int lz = sz.y, lx = sx.y, np = (lz + 1) / 2;
     const int *tz = a.tab + 3 * a.off[0], *tx = a.tab + 3 * a.off[1];
+    if (*a.bad >= a.packing) {
+        gather_piece(a, x, y, 0, sz.x, lz, sx.x, lx);
+        return;
+    }
     float acc[CH][NB][2] = {};
     // points a corner serves on an axis
     auto lo = [&](int k) { return k == 0 ? 0 : W + (k - 1) * a.s + 1; };

@@ -226,3 +226,67 @@ def test_psf_tables_without_room_for_windows(torch):
     assert float((y7 - ref).double().norm() / ref.double().norm()) <= 1e-6
     ctx.close()
     fresh.close()
+
+
+@pytest.mark.parametrize("mono", [False, True])
+@pytest.mark.parametrize("n,spacing", [((33, 47), 5), ((61, 40), 16), ((50, 83), 23), ((40, 52), 4)])
+def test_psf_samples_that_are_not_finite(torch, n, spacing, mono):
+    """A PSF image with Inf and NaN samples reaches the outputs that the
+    definition gives a term with such a sample (weight not zero, sample and
+    partner inside the grid), and no others; then a finite stack on the same
+    context."""
+    nz, nx = n
+    W = (spacing - 1) // 2
+    rng = np.random.default_rng(spacing)
+    nb = 1 if mono else 2
+    P = rng.standard_normal((2, 2, nx, nz)).astype(np.float32)
+    ok = P.copy()
+    for value, (ix, iz) in ((np.nan, (0, 0)), (np.inf, (W, W + 1)), (-np.inf, (nx - 1, nz // 2)), (np.nan, (nx // 2, nz - 1))):
+        P[1, 1, ix, iz] = value
+    x = rng.standard_normal((nb, nx, nz)).astype(np.float32)
+    ctx = lsrtm.Context(n, (10.0, 10.0), 10, 1e-3)
+
+    def axis(m):
+        lat = np.arange(W, m, spacing)
+        j = np.arange(m)
+        k = np.clip((j - W) // spacing, 0, max(len(lat) - 2, 0))
+        c0, c1 = lat[k], lat[np.minimum(k + 1, len(lat) - 1)]
+        w = np.clip((j - c0) / spacing, 0.0, 1.0).astype(np.float32).astype(np.float64) * (c1 > c0)
+        return (c0, 1.0 - w), (c1, w)
+
+    def product(P, transpose):
+        ax, az = axis(nx), axis(nz)
+        out = np.zeros((nb, nx, nz))
+        bl = P.astype(np.float64)[1:, 1:] if mono else P.astype(np.float64)
+        for jx in range(nx):
+            for jz in range(nz):
+                x0, x1, z0, z1 = max(-W, -jx), min(W, nx - 1 - jx), max(-W, -jz), min(W, nz - 1 - jz)
+                h = np.zeros((nb, nb, x1 - x0 + 1, z1 - z0 + 1))
+                for cx, wx in ax:
+                    for cz, wz in az:
+                        w = wx[jx] * wz[jz]
+                        if w == 0.0:
+                            continue
+                        sx, sz = cx[jx] + np.arange(x0, x1 + 1), cz[jz] + np.arange(z0, z1 + 1)
+                        inn = ((sx >= 0) & (sx < nx))[:, None] & ((sz >= 0) & (sz < nz))[None, :]
+                        t = bl[:, :, np.clip(sx, 0, nx - 1)][..., np.clip(sz, 0, nz - 1)]
+                        h = h + np.where(inn, w * t, 0.0)
+                to = np.s_[jx + x0:jx + x1 + 1, jz + z0:jz + z1 + 1]
+                for q in range(nb):
+                    for p in range(nb):
+                        if transpose:
+                            out[q, jx, jz] += np.sum(h[q, p] * x[(p, *to)])
+                        else:
+                            out[(p, *to)] += h[q, p] * x[q, jx, jz]
+        return out
+    xd = to_dev(torch, x[0] if mono else x)
+    with np.errstate(invalid="ignore"):
+        for stack in (ok, P, ok):
+            for tr in (False, True):
+                ref = product(stack, tr)
+                y = ctx.psf_apply(to_dev(torch, stack), spacing, xd, transpose=tr, mono=mono).cpu().numpy().reshape(nb, nx, nz)
+                fin = np.isfinite(ref)
+                assert np.array_equal(np.isfinite(y), fin), (tr, int(np.isfinite(y).sum()), int(fin.sum()))
+                e = np.linalg.norm((y - ref)[fin]) / np.linalg.norm(ref[fin])
+                assert e <= 1e-6, (tr, e)
+    ctx.close()
