@@ -311,6 +311,7 @@ __global__ void __launch_bounds__(64 * PSF_WAVES) k_psf_f(Psf2Args a, const floa
         for (int kz = sz.z; kz <= sz.w; ++kz) {
             const int za = max(-W, sz.x - hi(kz, 0)), zb = min(W, sz.x + lz - 1 - lo(kz));
             if (xa > xb || za > zb) continue;
+            wave_order();                                    // the taps of the corner before have been read
             // w_c x on the points that these taps reach
             const int pz = lz + zb - za + 1, px = lx + xb - xa;
             for (int e = lane; e < pz * px; e += 64) {
@@ -321,7 +322,7 @@ __global__ void __launch_bounds__(64 * PSF_WAVES) k_psf_f(Psf2Args a, const floa
                 for (int q = 0; q < NB; ++q)
                     xs[q * pz * px + e] = w != 0.f ? w * x[q * a.N + jz + (long long)a.n[0] * jx] : 0.f;
             }
-            __builtin_amdgcn_wave_barrier();                 // the wave's own patch: no other wave reads it
+            wave_order();                                    // the wave's own patch: no other wave reads it
             const float* P = pack + ((long long)kx * a.K[0] + kz) * D * D * NB * NB;
 #pragma unroll
             for (int ch = 0; ch < CH; ++ch) {

@@ -303,12 +303,6 @@ __device__ __forceinline__ void fly8(double2* v) {
     v[7] = csub(e[3], o3);
 }
 
-// LDS accesses of the lanes of one wave, in program order.
-__device__ __forceinline__ void wave_order() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 // v[r] = point t + T r in, v[i T + k2] = frequency (t + T i) + 8 k2 out; x is
 // the group's LDS row.
 template <int B, bool INV>
