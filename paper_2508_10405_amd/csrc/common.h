@@ -170,13 +170,6 @@ __device__ __forceinline__ int xcd_remap(int bid, int nblocks) {
     return base + k;
 }
 
-// Orders the LDS accesses of the lanes of one wave: what a lane wrote before is
-// there for the others after, and what they read before is read.
-__device__ __forceinline__ void wave_order() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 // A set of cells (tile-local row lz, column lx; negative = halo) that the
 // block stages: rows ZL + jz (jz < NZ) and columns XL + jx (jx < NX), where
 // an index jz >= ZW moves down by ZS rows and jx >= XW right by XS columns,

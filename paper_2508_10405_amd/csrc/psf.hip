@@ -37,6 +37,7 @@
 
 #include "common.h"
 #include "kernels.h"
+#include "wave.h"
 
 namespace lsrtm {
 

@@ -24,6 +24,7 @@
 // a call at once, and only the estimates go through memory.
 #include "common.h"
 #include "kernels.h"
+#include "wave.h"
 #include <hipfft/hipfft.h>
 
 #include <cmath>
