@@ -46,15 +46,15 @@ struct WArgs {
 
 constexpr int NPART = 256;
 
-// Images that the LDS route takes per launch: its estimates then take less
-// memory than the spectra of one image do in the other.
+// Images that the LDS route takes per launch, and has room for from its first
+// call on (a later call of more images allocates nothing): 16 B per block node,
+// where the spectra of one image take 24 in the other route.
 constexpr int WIMG = 4;
 constexpr int WPART = 64;            // partial maxima per image of that route
 
 struct WienerWork {
     int ndim = 0, n[3] = {0, 0, 0}, block = 0;
-    int images = 0;                  // images that est holds (LDS route)
-    float* est = nullptr;            // [images][nwin][bs] block estimates
+    float* est = nullptr;            // [WIMG][nwin][bs] block estimates (LDS route)
     float* part = nullptr;           // [WIMG][3][WPART] partial maxima
     double2* root = nullptr;         // [block] exp(-2 pi i k / block)
     long long nwin = 0, bs = 0;
@@ -572,6 +572,7 @@ const char* wiener_apply(WienerWork** work, int ndim, const int n[3], int block,
         if (in_lds) {
             if (hipMalloc(&W->part, WIMG * 3 * WPART * sizeof(float)) != hipSuccess) return "out of memory";
             if (hipMalloc(&W->root, block * sizeof(double2)) != hipSuccess) return "out of memory";
+            if (hipMalloc(&W->est, WIMG * W->nwin * W->bs * sizeof(float)) != hipSuccess) return "out of memory";
             std::vector<double2> r(block);
             for (int k = 0; k < block; ++k)
                 r[k] = {std::cos(2.0 * M_PI * k / block), -std::sin(2.0 * M_PI * k / block)};
@@ -605,14 +606,6 @@ const char* wiener_apply(WienerWork** work, int ndim, const int n[3], int block,
     a.N = (long long)n[0] * n[1] * n[2];
     a.taper = W->taper;
     if (in_lds) {
-        const int most = nimg < WIMG ? nimg : WIMG;
-        if (W->images < most) {
-            if (W->est) (void)hipFree(W->est);
-            W->est = nullptr;
-            W->images = 0;
-            if (hipMalloc(&W->est, most * W->nwin * W->bs * sizeof(float)) != hipSuccess) return "out of memory";
-            W->images = most;
-        }
         for (int k = 0; k < nimg; k += WIMG) {
             const int m = nimg - k < WIMG ? nimg - k : WIMG;
             const float *r = ref + k * a.N, *b = blur + k * a.N, *x = in + k * a.N;

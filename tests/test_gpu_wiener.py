@@ -120,3 +120,30 @@ def test_wiener_stacks(torch, block):
             print("wiener stack", block, third, i, e, flush=True)
             assert e <= TOL
     ctx.close()
+
+
+@pytest.mark.parametrize("block", [16, 32, 64, 24])
+def test_wiener_under_capture(torch, block):
+    """After a first call of one image, a stack of five is captured into a
+    graph (nothing is allocated any more); its replays, with eager calls of
+    other stacks between them, give the eager result for the inputs of the
+    moment."""
+    from paper_2508_10405_amd import lsrtm
+    n, k = (71, 37), 5
+    g = torch.Generator(device="cuda").manual_seed(block)
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        ctx = lsrtm.Context(n, (10.0, 10.0), 10, 1e-3)
+        ref, blur = (torch.randn((k, 37, 71), generator=g, device="cuda") for _ in range(2))
+        ctx.wiener(ref[0].contiguous(), blur[0].contiguous(), block=block)
+        st.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=st):
+            out = ctx.wiener(ref, blur, block=block)
+        for _ in range(3):
+            ref.copy_(torch.randn((k, 37, 71), generator=g, device="cuda"))
+            graph.replay()
+            got = out.clone()
+            assert torch.equal(got, ctx.wiener(ref, blur, block=block))
+        st.synchronize()
+    ctx.close()
