@@ -190,7 +190,7 @@ __device__ __forceinline__ void adj_body(const ResArgs& a, const ResBlock& B, fl
 #pragma unroll
                 for (int k = 0; k < BZ; ++k) {
                     e[k] = e[k] + tn[k] * (phi.get(c, k) + e[k]);
-                    if (!skip) chi.set(c, k, tb[k] * (chi.get(c, k) + uz[c][k]));
+                    if (!skip) chi.set(c, k, chi.times(tb[k], chi.get(c, k) + uz[c][k]));
                 }
             }
             d_col<BZ, 1>(e, a.C.c[0], dd);
@@ -269,7 +269,7 @@ __device__ __forceinline__ void adj_body(const ResArgs& a, const ResBlock& B, fl
 #pragma unroll
                 for (int k = 0; k < BZ; ++k) {
                     g[k] = g[k] + th[k] * (chi.get(c, k) + g[k]);
-                    phi.set(c, k, tb[k] * (phi.get(c, k) + Q[c][k]));
+                    phi.set(c, k, phi.times(tb[k], phi.get(c, k) + Q[c][k]));
                 }
             }
             d_col<BZ, 0>(g, a.C.c[0], dz[c]);

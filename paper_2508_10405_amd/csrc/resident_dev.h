@@ -411,10 +411,18 @@ __device__ __forceinline__ void res_priority(int w) {
     if (w < 2 || w >= RES_WAVES - 2) __builtin_amdgcn_s_setprio(2);
 }
 
+// a b, and 0 where a is 0, whatever b is.
+__device__ __forceinline__ float mul0(float a, float b) {
+    float r;
+    asm("v_mul_legacy_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
 // CPML memories of the z strips: in registers where they are to spare, or in
 // LDS slots of the lanes that hold strip rows (the other lanes share one slot of
 // zeros).  Every lane does the arithmetic, with zero coefficients outside the
-// strips: a branch around it put the wave's outstanding memory accesses in front
+// strips, where mul0 keeps an Inf or NaN of the fields out of the shared slot (the
+// lane whose store is the last there would hand its own to all the others): a branch around it put the wave's outstanding memory accesses in front
 // of it (a replay step of 7 shots of 280 x 777 took 8.6 us with the branch, 5.6
 // without).
 template <int BZ, int CX, bool REG>
@@ -426,12 +434,14 @@ struct ZMem {
         if (REG) r[REG ? c : 0][REG ? k : 0] = v;
         else l[(c * BZ + k) * RES_ZSLOTS] = v;
     }
+    // a coefficient times what goes into a memory
+    static __device__ __forceinline__ float times(float a, float v) { return REG ? a * v : mul0(a, v); }
     // g += psi with psi = b psi + a g (a lane's rows outside the strips have
     // a = 0, psi = 0)
     __device__ __forceinline__ void step(const float (&a)[BZ], const float (&b)[BZ], int c, float (&g)[BZ]) {
 #pragma unroll
         for (int k = 0; k < BZ; ++k) {
-            const float ps = fmaf(b[k], get(c, k), a[k] * g[k]);
+            const float ps = fmaf(b[k], get(c, k), times(a[k], g[k]));
             set(c, k, ps);
             g[k] = g[k] + ps;
         }

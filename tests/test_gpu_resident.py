@@ -126,3 +126,39 @@ def test_groups_of_whole_rounds():
         got.append((d, ctx.adjoint(d)))
         ctx.close()
     assert all(torch.equal(x, y) for x, y in zip(*got))
+
+
+@pytest.mark.parametrize("nz,nx,npml,nshot", [(320, 203, 20, 24), (300, 203, 20, 24), (240, 100, 0, 30), (128, 60, 9, 2)])
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+def test_not_finite_values_stay_in_their_cone(nz, nx, npml, nshot, bad):
+    """One Inf or NaN among the data, in the perturbation and in a wavelet, and
+    a march too short for it to reach the whole grid: the same values are
+    finite, and equal, on either schedule (wide launches keep the z strips'
+    memories in LDS slots that many lanes share, narrow ones in registers)."""
+    torch = require_gpu()
+    nt = 5
+    w = synth.small((nz - 2 * npml, nx - 2 * npml), nt=nt, npml=npml, seed=nz, nshot=nshot)
+    at = (nz - 2 * npml - 8, nx // 2 - npml)             # in the last lane with rows outside the z strips
+    w.rec[0][0] = at
+    w.src[0] = at
+    got = []
+    for resident in (0, 1):
+        ctx = lsrtm.context_for(w, tile=1, ckpt_every=nt)
+        ctx.set_option(lsrtm.OPT_RESIDENT, resident)
+        dm = to_dev(torch, w.dm)
+        d = ctx.born(dm)
+        y = d.clone()
+        y[(nt - 1) * len(w.rec[0])] = bad                # last step, first receiver of shot 0
+        dm[0, at[1], at[0]] = bad
+        out = [ctx.adjoint(y), ctx.born(dm)]
+        wav = to_dev(torch, w.wavelet)
+        wav[0, 3] = bad
+        ctx.set_acquisition(w.win, w.src, w.rec, wav)
+        out.append(ctx.forward())
+        got.append(out)
+        ctx.close()
+    for i, (a, b) in enumerate(zip(*got)):
+        fin = torch.isfinite(a)
+        assert 0 < int(fin.sum()) < fin.numel(), i
+        assert torch.equal(fin, torch.isfinite(b)), (i, int(fin.sum()), int(torch.isfinite(b).sum()))
+        assert torch.equal(a[fin], b[fin]), i
