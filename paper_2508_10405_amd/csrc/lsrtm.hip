@@ -35,6 +35,7 @@
 
 #include "../../include/lsrtm.h"
 #include "kernels.h"
+#include "resgate.h"
 #include "resident.h"
 
 using namespace lsrtm;
@@ -210,6 +211,8 @@ struct lsrtm_ctx {
     bool res_ok = false;           // the plan's windows fit
     bool res_on = false;           // passes run on it (replay-cache layout too)
     int res_bz = 0;
+    int res_dev = 0, res_cus = 0;  // the device and its CUs
+    int res_most = 0;              // workgroups of the largest launch
     char* res_tab = nullptr;       // tables of the resident launches
     unsigned long long* res_ex = nullptr;   // exchange words
     long long res_exn = 0;
@@ -993,10 +996,6 @@ lsrtm_status ensure_ckpts(lsrtm_ctx* c) {
 lsrtm_status autotune(lsrtm_ctx* c, int nsteps, bool groups, double* out);
 lsrtm_status plan(lsrtm_ctx* c);
 
-// Resident launches of a process run one call at a time: two of them sharing
-// the GPU would each hold workgroups that the other one waits for.
-std::mutex g_res_mu;
-
 // The two schedules keep the replay cache in layouts of their own.
 void set_resident(lsrtm_ctx* c, bool on) {
     if (c->res_on == on) return;
@@ -1014,7 +1013,7 @@ lsrtm_status run_passes(lsrtm_ctx* c, F body) {
         return body();
     }
     {
-        std::lock_guard<std::mutex> lock(g_res_mu);
+        ResRoom room(c->res_dev, c->res_most, c->res_cus);
         set_resident(c, true);
         CHK(fill(c, reinterpret_cast<float*>(c->res_ctl), 1));
         const lsrtm_status s = body();
@@ -1139,9 +1138,10 @@ lsrtm_status plan_resident(lsrtm_ctx* c) {
     c->res_ok = false;
     if (!c->res_bz) return LSRTM_OK;
     const int bz = c->res_bz, npml = c->g.npml;
-    int dev = 0, ncu = 0;
-    HIPCHK(c, hipGetDevice(&dev));
-    HIPCHK(c, hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
+    HIPCHK(c, hipGetDevice(&c->res_dev));
+    HIPCHK(c, hipDeviceGetAttribute(&c->res_cus, hipDeviceAttributeMultiprocessorCount, c->res_dev));
+    const int ncu = c->res_cus;
+    c->res_most = 0;
     long long exn = 0;
     size_t rounds = 1;
     std::vector<std::pair<int, bool>> sl;
@@ -1267,6 +1267,7 @@ lsrtm_status plan_resident(lsrtm_ctx* c) {
                 L.blocks = add_table(tab, blocks);
                 L.lds = res_lds_bytes(kind, bz, L.cx, most);
                 exn = std::max(exn, L.nblocks * res_ex_words(bz, kind == R_BORN ? 2 : 1));
+                c->res_most = std::max(c->res_most, L.nblocks);
                 gr.res[kind].push_back(L);
             }
             rounds = std::max(rounds, gr.res[kind].size());

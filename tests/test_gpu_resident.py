@@ -162,3 +162,47 @@ def test_not_finite_values_stay_in_their_cone(nz, nx, npml, nshot, bad):
         assert 0 < int(fin.sum()) < fin.numel(), i
         assert torch.equal(fin, torch.isfinite(b)), (i, int(fin.sum()), int(torch.isfinite(b).sum()))
         assert torch.equal(a[fin], b[fin]), i
+
+
+def test_small_contexts_side_by_side():
+    """Contexts on streams and threads of their own whose launches fit the GPU
+    together (one shot each, 30 workgroups) do not take turns; their results
+    are those of one alone."""
+    import threading
+    import time
+    torch = require_gpu()
+    n, calls = 4, 25
+    w = synth.small((100, 200), nt=1000, npml=20, seed=3, nshot=1)
+    jobs = []
+    for _ in range(n):
+        st = torch.cuda.Stream()
+        with torch.cuda.stream(st):
+            ctx = lsrtm.context_for(w, tile=1)
+            dm = to_dev(torch, w.dm)
+            d = ctx.born(dm)
+            ref = ctx.born(dm).clone()
+        torch.cuda.synchronize()
+        jobs.append((st, ctx, dm, d, ref))
+
+    def run(job):
+        st, ctx, dm, d, _ = job
+        with torch.cuda.stream(st):
+            for _ in range(calls):
+                ctx.born(dm, d)
+            st.synchronize()
+
+    def timed(which):
+        ts = [threading.Thread(target=run, args=(j,)) for j in which]
+        t = time.perf_counter()
+        for th in ts:
+            th.start()
+        for th in ts:
+            th.join()
+        return time.perf_counter() - t
+    timed(jobs)
+    one, all_ = min(timed(jobs[:1]) for _ in range(3)), min(timed(jobs) for _ in range(3))
+    print(f"one context {one * 1e3 / calls:.2f} ms a call, {n} side by side {all_ * 1e3 / calls:.2f}", flush=True)
+    for _, ctx, _, d, ref in jobs:
+        assert torch.equal(d, ref)
+        ctx.close()
+    assert all_ < 0.7 * n * one
