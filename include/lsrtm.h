@@ -137,7 +137,10 @@ enum {
                                        its window fits (default; padded depth
                                        up to 384 nodes, two-phase steps), 0 =
                                        one velocity and one pressure kernel per
-                                       step.  Both give identical results       */
+                                       step.  Both give identical results.  2 =
+                                       as 1, but no launch finds room on the
+                                       GPU: every call goes the way back to
+                                       the kernels per step (a rehearsal)       */
 };
 
 /* Create a context for one grid on one HIP stream (hipStream_t, may be 0).
@@ -394,6 +397,17 @@ lsrtm_status lsrtm_autotune(lsrtm_ctx* ctx, int nsteps, int tune_groups, double*
  * HOST long long [nout]; the first min(nout, 14) entries are written.
  * Errors: EINVAL (NULL ctx or out). */
 lsrtm_status lsrtm_sizes(lsrtm_ctx* ctx, long long* out, int nout);
+
+/* Resident 2D time stepping (LSRTM_OPT_RESIDENT): out[0] = 1 if the plan's
+ * calls take it, out[1] = 1 if the last call of a pass (forward, Born,
+ * migration; the last pass of a CGNR call) ran on it, out[2] = calls so far
+ * that found the GPU held by other work (the launch waits half a second for
+ * its workgroups) and ran again on the kernels per step.  After such a call
+ * the next ones take those kernels for 10 s, and for twice as long, up to 160
+ * s, each time the GPU is still held then; setting the option ends the pause.
+ * HOST long long [nout]; the first min(nout, 3) entries are written.
+ * Errors: EINVAL (NULL ctx or out). */
+lsrtm_status lsrtm_resident(lsrtm_ctx* ctx, long long* out, int nout);
 
 /* Timing statistics of the last pass (HOST double [nout]); see
  * LSRTM_STAT_* for the layout.  Per-kernel times need LSRTM_OPT_TIMING.

@@ -206,7 +206,7 @@ struct lsrtm_ctx {
     int opt_tile_v = -1;           // two-phase steps: tile of the velocity phases (-1: tile)
     int opt_tile_a = -1;           // two-phase steps: tile of the adjoint A phase (-1: tile)
     long long opt_rcache_mb = 0;   // HBM the replay cache may take (0: none)
-    int opt_res = 1;               // 2D: resident time stepping where the plan allows it
+    int opt_res = 1;               // 2D: resident time stepping where the plan allows it (2: rehearse its giving up)
     // resident time stepping
     bool res_ok = false;           // the plan's windows fit
     bool res_on = false;           // passes run on it (replay-cache layout too)
@@ -219,6 +219,10 @@ struct lsrtm_ctx {
     int* res_ctl = nullptr;        // [0] gave up, [1 + i] arrivals of launch i of a group's pass
     int res_ctln = 0, res_launch = 0;
     int res_id = 0;                // launches since the exchange words were cleared
+    bool res_last = false;         // the last run_passes stayed on it
+    int res_gave_up = 0;           // calls that found no room on the GPU
+    int res_pause = 0;             // seconds without another try after the last of them (0: it is over)
+    std::chrono::steady_clock::time_point res_since;
     // timing
     std::vector<EvPair> evpool;
     size_t evused = 0;
@@ -1005,23 +1009,39 @@ void set_resident(lsrtm_ctx* c, bool on) {
 
 // Runs the passes of one call (body) on the resident kernels where the plan
 // allows it, and again on the streaming kernels if a launch gave up waiting
-// for room on the GPU.
+// for room on the GPU.  Such a call has waited half a second for nothing, so
+// the next ones do not try for RES_PAUSE seconds (5 % of the time at most), and
+// for twice as long, up to 16 times, whenever they find the GPU still held.
+constexpr int RES_PAUSE = 10;
+
 template <typename F>
 lsrtm_status run_passes(lsrtm_ctx* c, F body) {
-    if (!c->res_ok || !c->opt_res) {
+    const auto now = std::chrono::steady_clock::now();
+    const bool paused = c->res_pause > 0 && now - c->res_since < std::chrono::seconds(c->res_pause);
+    c->res_last = false;
+    if (!c->res_ok || !c->opt_res || paused) {
         set_resident(c, false);
         return body();
     }
+    const size_t samples = c->evused;
     {
         ResRoom room(c->res_dev, c->res_most, c->res_cus);
         set_resident(c, true);
-        CHK(fill(c, reinterpret_cast<float*>(c->res_ctl), 1));
+        HIPCHK(c, launch_fill(reinterpret_cast<float*>(c->res_ctl), 1, c->opt_res == 2 ? 1.f : 0.f, c->st));
         const lsrtm_status s = body();
         int gave_up = 0;
         HIPCHK(c, hipMemcpyAsync(&gave_up, c->res_ctl, sizeof(int), hipMemcpyDeviceToHost, c->st));
         HIPCHK(c, hipStreamSynchronize(c->st));
-        if (!gave_up) return s;
+        if (!gave_up) {
+            c->res_last = true;
+            c->res_pause = 0;
+            return s;
+        }
     }
+    c->res_gave_up += 1;
+    c->res_pause = std::min(16 * RES_PAUSE, std::max(RES_PAUSE, 2 * c->res_pause));
+    c->res_since = std::chrono::steady_clock::now();
+    c->evused = samples;           // those of the launches that gave up
     background_changed(c);
     set_resident(c, false);
     return body();
@@ -2126,7 +2146,10 @@ lsrtm_status lsrtm_set_option(lsrtm_ctx* c, int key, long long v) {
         return LSRTM_OK;
     }
     case LSRTM_OPT_GRAPH: c->opt_graph = v != 0; return LSRTM_OK;
-    case LSRTM_OPT_RESIDENT: c->opt_res = v != 0; return LSRTM_OK;
+    case LSRTM_OPT_RESIDENT:
+        c->opt_res = v == 0 ? 0 : v == 2 ? 2 : 1;
+        c->res_pause = 0;
+        return LSRTM_OK;
     case LSRTM_OPT_TIMING: c->opt_timing = v != 0; return LSRTM_OK;
     case LSRTM_OPT_MEM_BUDGET_MB:
         if (v < 0 || v > kMaxMB) FAIL(c, LSRTM_EINVAL, "memory budget must be in [0, %lld] MB", kMaxMB);
@@ -2259,6 +2282,13 @@ lsrtm_status lsrtm_sizes(lsrtm_ctx* c, long long* out, int nout) {
                        c->tile, c->ck_group ? 1 : 0, c->fused ? 1 : 0, c->opt_tile_v, c->opt_tile_a, c->rc_m,
                        (long long)c->graphs.size()};
     for (int i = 0; i < nout && i < 14; ++i) out[i] = v[i];
+    return LSRTM_OK;
+}
+
+lsrtm_status lsrtm_resident(lsrtm_ctx* c, long long* out, int nout) {
+    if (!c || !out) return LSRTM_EINVAL;
+    const long long v[3] = {c->res_ok && c->opt_res ? 1 : 0, c->res_last ? 1 : 0, c->res_gave_up};
+    for (int i = 0; i < nout && i < 3; ++i) out[i] = v[i];
     return LSRTM_OK;
 }
 

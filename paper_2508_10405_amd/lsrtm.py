@@ -79,6 +79,7 @@ SIGNATURES = {
     "lsrtm_cgnr_step": (_c_int, [_vp, ctypes.POINTER(_c_double)]),
     "lsrtm_set_option": (_c_int, [_vp, _c_int, _c_ll]),
     "lsrtm_sizes": (_c_int, [_vp, ctypes.POINTER(_c_ll), _c_int]),
+    "lsrtm_resident": (_c_int, [_vp, ctypes.POINTER(_c_ll), _c_int]),
     "lsrtm_autotune": (_c_int, [_vp, _c_int, _c_int, ctypes.POINTER(_c_double)]),
     "lsrtm_stats": (_c_int, [_vp, ctypes.POINTER(_c_double), _c_int]),
     "lsrtm_tile_shape": (_c_int, [_c_int, _c_int, ctypes.POINTER(_c_int)]),
@@ -258,6 +259,14 @@ class Context:
     @property
     def data_len(self) -> int:
         return self.sizes()["data_len"]
+
+    def resident(self):
+        """Resident 2D time stepping (lsrtm_resident): whether the plan's calls
+        take it, whether the last one ran on it, and the calls so far that
+        found no room for it on the GPU."""
+        out = (_c_ll * 3)()
+        self._check(lib().lsrtm_resident(self._h, out, 3), "resident")
+        return {"planned": bool(out[0]), "last": bool(out[1]), "gave_up": int(out[2])}
 
     def stats(self):
         m = 1 + 2 * NKERNEL

@@ -219,3 +219,24 @@ def test_binding_constants_match_the_header():
     assert ck == lsrtm.CKPT
     nk = int(re.search(r"LSRTM_NKERNEL\s*=\s*(\d+)", src).group(1))
     assert nk == lsrtm.NKERNEL == len(lsrtm.KERNEL_NAMES)
+
+
+def test_resident_state_of_a_fresh_context():
+    """lsrtm_resident: nothing planned, nothing run, nothing given up; three
+    entries written; NULL arguments refused."""
+    L = lsrtm.lib()
+    g = lsrtm.Grid()
+    g.ndim = 2
+    g.n[0], g.n[1], g.n[2] = 10, 12, 1
+    g.h[0] = g.h[1] = g.h[2] = 10.0
+    g.npml, g.pml_R, g.pml_f0, g.nt, g.dt = 4, 1e-4, 10.0, 10, 1e-3
+    h = ctypes.c_void_p()
+    assert L.lsrtm_create(ctypes.byref(g), None, ctypes.byref(h)) == 0
+    out = (ctypes.c_longlong * 4)(*([-7] * 4))
+    assert L.lsrtm_resident(h, out, 4) == lsrtm.OK
+    assert list(out) == [0, 0, 0, -7]
+    assert L.lsrtm_resident(h, None, 3) == lsrtm.EINVAL
+    assert L.lsrtm_resident(None, out, 3) == lsrtm.EINVAL
+    for v in (0, 1, 2, 7, -1):
+        assert L.lsrtm_set_option(h, lsrtm.OPT_RESIDENT, v) == lsrtm.OK
+    L.lsrtm_destroy(h)

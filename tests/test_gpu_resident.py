@@ -206,3 +206,70 @@ def test_small_contexts_side_by_side():
         assert torch.equal(d, ref)
         ctx.close()
     assert all_ < 0.7 * n * one
+
+
+@pytest.mark.parametrize("nz,nx,npml,nshot,nt,k,opts", CASES)
+def test_calls_run_resident(nz, nx, npml, nshot, nt, k, opts):
+    """The calls compared above do run on the resident kernels, first and
+    later ones, without one that gives up."""
+    torch = require_gpu()
+    w = synth.small((nz - 2 * npml, nx - 2 * npml), nt=nt, npml=npml, seed=nz + nx, nshot=nshot, uneven=nshot > 2)
+    ctx = lsrtm.context_for(w, tile=1, ckpt_every=k, **opts)
+    ctx.set_option(lsrtm.OPT_RESIDENT, 1)
+    dm = to_dev(torch, w.dm)
+    on = {"planned": True, "last": True, "gave_up": 0}
+    for _ in range(2):
+        d = ctx.forward()
+        assert ctx.resident() == on
+        d = ctx.born(dm, d)
+        assert ctx.resident() == on
+        ctx.adjoint(d)
+        assert ctx.resident() == on
+    ctx.cgnr(d, 1)
+    assert ctx.resident() == on
+    ctx.close()
+
+
+@pytest.mark.parametrize("opts", [{}, {"graph": False}, {"replay_cache_mb": 2000}, {"ckpt_dtype": "bf16"},
+                                  {"ckpt_per_group": True, "shots_per_launch": 2}, {"timing": True}])
+def test_launches_that_find_no_room(opts):
+    """A call whose launches give up runs again on the streaming kernels, in
+    the middle of a CGNR run too: the results are theirs bit for bit, also
+    those of the calls after it.  It is counted, and the next calls do not try
+    again until the pause is over."""
+    torch = require_gpu()
+    w = synth.small((100, 120), nt=40, npml=10, seed=6, nshot=4)
+    got = []
+    for resident in (0, 2, 1):
+        ctx = lsrtm.context_for(w, tile=1, ckpt_every=9, **opts)
+        dm = to_dev(torch, w.dm)
+        out = []
+        gave_up = 0
+        for call in (ctx.forward, lambda: ctx.born(dm), lambda: ctx.adjoint(out[1]), lambda: ctx.born(dm),
+                     lambda: ctx.adjoint(out[0])):
+            ctx.set_option(lsrtm.OPT_RESIDENT, resident)      # ends the pause
+            out.append(call())
+            gave_up += resident == 2
+            assert ctx.resident() == {"planned": resident > 0, "last": resident == 1, "gave_up": gave_up}
+        out.append(ctx.adjoint(out[0]))
+        assert ctx.resident()["gave_up"] == gave_up
+        x = ctx.cgnr_begin(out[1])
+        for it in range(3):
+            if resident == 2:
+                ctx.set_option(lsrtm.OPT_RESIDENT, 2 if it == 1 else 1)
+            out.append(torch.tensor(ctx.cgnr_iterate(x)))
+            gave_up += resident == 2 and it == 1
+            assert ctx.resident()["gave_up"] == gave_up
+        out.append(x)
+        got.append(out)
+        if "timing" in opts:
+            # the samples of the launches that gave up are not counted
+            d = ctx.adjoint(out[0])
+            ctx.set_option(lsrtm.OPT_RESIDENT, resident)
+            ctx.adjoint(out[0])
+            assert ctx.stats()["adj_a"][1] == w.nt or resident != 1
+            assert (ctx.stats()["adj_b"][1] > 0) == (resident != 1)
+        ctx.close()
+    for other in got[1:]:
+        for i, (a, b) in enumerate(zip(got[0], other)):
+            assert torch.equal(a, b), i
