@@ -1000,6 +1000,12 @@ lsrtm_status ensure_ckpts(lsrtm_ctx* c) {
 lsrtm_status autotune(lsrtm_ctx* c, int nsteps, bool groups, double* out);
 lsrtm_status plan(lsrtm_ctx* c);
 
+// The streaming kernels' tile is set or tuned before their first pass.
+lsrtm_status tile_ready(lsrtm_ctx* c) {
+    if (c->opt_tile >= 0 || c->tuned) return LSRTM_OK;
+    return autotune(c, 4, false, nullptr);
+}
+
 // The two schedules keep the replay cache in layouts of their own.
 void set_resident(lsrtm_ctx* c, bool on) {
     if (c->res_on == on) return;
@@ -1021,6 +1027,7 @@ lsrtm_status run_passes(lsrtm_ctx* c, F body) {
     c->res_last = false;
     if (!c->res_ok || !c->opt_res || paused) {
         set_resident(c, false);
+        CHK(tile_ready(c));
         return body();
     }
     const size_t samples = c->evused;
@@ -1044,6 +1051,7 @@ lsrtm_status run_passes(lsrtm_ctx* c, F body) {
     c->evused = samples;           // those of the launches that gave up
     background_changed(c);
     set_resident(c, false);
+    CHK(tile_ready(c));
     return body();
 }
 
@@ -1051,15 +1059,10 @@ lsrtm_status check_ready(lsrtm_ctx* c) {
     if (!c) return LSRTM_EINVAL;
     if (!c->have_model) FAIL(c, LSRTM_ESTATE, "set_model has not been called");
     if (!c->have_acq) FAIL(c, LSRTM_ESTATE, "set_acquisition has not been called");
-    if (c->opt_tile >= 0) {
-        c->tile = c->opt_tile;
-    } else if (!c->tuned && c->res_ok && c->opt_res) {
-        c->tile = default_tile(c->ndim);   // serves the pseudo-Hessian pass only
-    } else if (!c->tuned) {
-        c->tile = default_tile(c->ndim);
-        CHK(autotune(c, 4, false, nullptr));
-    }
-    return LSRTM_OK;
+    if (c->opt_tile >= 0) c->tile = c->opt_tile;
+    else if (!c->tuned) c->tile = default_tile(c->ndim);
+    // the resident kernels have no tiles
+    return c->res_ok && c->opt_res ? LSRTM_OK : tile_ready(c);
 }
 
 lsrtm_status prep_model_windows(lsrtm_ctx* c) {
@@ -2927,6 +2930,7 @@ lsrtm_status lsrtm_set_preconditioner(lsrtm_ctx* c, const float* minv) {
 
 lsrtm_status lsrtm_pseudo_hessian(lsrtm_ctx* c, float* h, float* minv, double eps_rel) {
     CHK(check_ready(c));
+    CHK(tile_ready(c));
     if (!h) FAIL(c, LSRTM_EINVAL, "h is NULL");
     if (!(eps_rel >= 0.0)) FAIL(c, LSRTM_EINVAL, "eps_rel must be >= 0");
     CHK(pass_begin(c));

@@ -273,3 +273,25 @@ def test_launches_that_find_no_room(opts):
     for other in got[1:]:
         for i, (a, b) in enumerate(zip(got[0], other)):
             assert torch.equal(a, b), i
+
+
+def test_streaming_passes_of_resident_plans_are_tuned(tmp_path, monkeypatch):
+    """Passes of a resident plan need no tile, so none is tuned for them; the
+    pseudo-Hessian pass and a call that found no room take the streaming
+    kernels, whose tile is tuned before the first of these (the tuner adds a
+    line to its file)."""
+    torch = require_gpu()
+    w = synth.small((60, 80), nt=20, npml=8, seed=4, nshot=2)
+    dm = to_dev(torch, w.dm)
+    for i, streaming in enumerate((lambda c: c.pseudo_hessian(), lambda c: c.born(dm))):
+        file = tmp_path / f"tune{i}.txt"
+        monkeypatch.setenv("LSRTM_TUNE_CACHE", str(file))
+        ctx = lsrtm.context_for(w)
+        ctx.born(dm)
+        ctx.adjoint(ctx.forward())
+        assert ctx.resident()["last"] and not file.exists()
+        ctx.set_option(lsrtm.OPT_RESIDENT, 2)
+        for _ in range(2):
+            streaming(ctx)
+            assert len(file.read_text().splitlines()) == 1
+        ctx.close()
