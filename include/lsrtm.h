@@ -137,7 +137,9 @@ enum {
                                        its window fits (default; padded depth
                                        up to 384 nodes, two-phase steps), 0 =
                                        one velocity and one pressure kernel per
-                                       step.  Both give identical results.  2 =
+                                       step.  Both give identical results.  The
+                                       replay buffer has a layout for each:
+                                       re-plans when turned on or off.  2 =
                                        as 1, but no launch finds room on the
                                        GPU: every call goes the way back to
                                        the kernels per step (a rehearsal)       */

@@ -21,6 +21,7 @@
 // migration pass instead of being recomputed, and by every later 2D Born pass
 // in place of the background steps of those segments.
 #include <algorithm>
+#include <array>
 #include <chrono>
 #include <climits>
 #include <cmath>
@@ -70,7 +71,8 @@ struct ShotInfo {
 
 // One launch of the resident 2D kernels: the slabs of a run of slots.
 struct ResLaunch {
-    int cx = 1, nblocks = 0, maxnodes = 0;
+    int cx = 1, nblocks = 0;
+    int most = 0;                  // receivers (adjoint: receiver nodes) of the workgroup that has most
     size_t lds = 0;
     // tables, as offsets in the plan's block of them
     size_t blocks = 0;
@@ -695,7 +697,7 @@ lsrtm_status res_run(lsrtm_ctx* c, Group& gr, int kind, const Slot* sl, int n0, 
         a.y = y;
         a.nptr = reinterpret_cast<const int*>(c->res_tab + L.nptr);
         a.node = reinterpret_cast<const int4*>(c->res_tab + L.node);
-        a.maxnodes = L.maxnodes;
+        a.maxnodes = L.most;
         a.ex = c->res_ex;
         if (++c->res_id >= RES_IDS) {
             CHK(fill(c, reinterpret_cast<float*>(c->res_ex), 2 * c->res_exn));
@@ -1107,15 +1109,32 @@ lsrtm_status prep_model_windows(lsrtm_ctx* c) {
     return LSRTM_OK;
 }
 
-// Slabs of an axis of nx padded columns: (first column, in the strips).  The
-// slabs that reach a strip are as wide as their body allows.
-void res_slabs(int nx, int npml, int cx, int cxe, std::vector<std::pair<int, bool>>& out) {
-    out.clear();
+// Slabs of an axis of nx padded columns (the ones that reach a strip are as
+// wide as their body allows): first column and whether in the strips, and the
+// slab of every column.
+struct ResCut {
+    std::vector<std::pair<int, bool>> slabs;
+    std::vector<int> of;
+};
+ResCut res_cut(int nx, int npml, int cx) {
+    ResCut r;
+    r.of.resize(nx);
     for (int x = 0; x < nx;) {
         const bool inner = x >= npml && x + RES_WAVES * cx <= nx - npml - 1;
-        out.push_back({x, !inner});
-        x += RES_WAVES * (inner ? cx : cxe);
+        const int x1 = std::min(nx, x + RES_WAVES * (inner ? cx : res_cx_edge(cx)));
+        for (int i = x; i < x1; ++i) r.of[i] = (int)r.slabs.size();
+        r.slabs.push_back({x, !inner});
+        x = x1;
     }
+    return r;
+}
+// of every window, at 1 .. RES_CX_MAX columns per wave
+using ResCuts = std::vector<std::array<ResCut, RES_CX_MAX + 1>>;
+ResCuts res_cuts(const lsrtm_ctx* c) {
+    ResCuts cuts(c->wins.size());
+    for (size_t w = 0; w < c->wins.size(); ++w)
+        for (int cx = 1; cx <= RES_CX_MAX; ++cx) cuts[w][cx] = res_cut(c->wins[w].N[1], c->g.npml, cx);
+    return cuts;
 }
 
 // Appends a table to a plan's block of tables; returns its offset.
@@ -1154,141 +1173,169 @@ double res_step_us(int kind, int nodes) {
     return base[kind] + per[kind] * nodes;
 }
 
-// Launches of the resident kernels for every group and kind: consecutive
-// slots whose slabs fill the GPU together, one workgroup per CU, the slab
-// width of every launch chosen for the least estimated time.
-lsrtm_status plan_resident(lsrtm_ctx* c) {
-    c->res_ok = false;
-    if (!c->res_bz) return LSRTM_OK;
-    const int bz = c->res_bz, npml = c->g.npml;
-    HIPCHK(c, hipGetDevice(&c->res_dev));
-    HIPCHK(c, hipDeviceGetAttribute(&c->res_cus, hipDeviceAttributeMultiprocessorCount, c->res_dev));
-    const int ncu = c->res_cus;
-    c->res_most = 0;
-    long long exn = 0;
-    size_t rounds = 1;
-    std::vector<std::pair<int, bool>> sl;
-    std::vector<char> tab;
-    for (auto& gr : c->groups) {
-        // receivers and receiver nodes by slot, left of each column
-        std::vector<std::vector<int>> rcols(gr.ns), ncols(gr.ns);
-        for (int s = 0; s < gr.ns; ++s) {
-            rcols[s].assign(gr.h_slots[s].n[1] + 1, 0);
-            ncols[s].assign(gr.h_slots[s].n[1] + 1, 0);
-        }
-        for (const Rec& R : gr.h_rec) rcols[R.slot][R.idx / gr.h_slots[R.slot].ldz + 1] += 1;
-        for (int i = 0; i < gr.nnode; ++i)
-            ncols[gr.h_node_slot[i]][gr.h_node_idx[i] / gr.h_slots[gr.h_node_slot[i]].ldz + 1] += 1;
-        for (int s = 0; s < gr.ns; ++s) {
-            std::partial_sum(rcols[s].begin(), rcols[s].end(), rcols[s].begin());
-            std::partial_sum(ncols[s].begin(), ncols[s].end(), ncols[s].begin());
-        }
-        for (int kind = 0; kind < R_KINDS; ++kind) {
-            gr.res[kind].clear();
-            // workgroups of a slot, and most receivers of one, for every width
-            const auto& cols = kind == R_ADJ ? ncols : rcols;
-            const bool lists = kind != R_SEG;
-            std::vector<int> nb[RES_CX_MAX + 1], mn[RES_CX_MAX + 1];
-            for (int cx = 1; cx <= RES_CX_MAX; ++cx)
-                for (int s = 0; s < gr.ns; ++s) {
-                    const int nx = gr.h_slots[s].n[1], cxe = res_cx_edge(cx);
-                    res_slabs(nx, npml, cx, cxe, sl);
-                    int most = 0;
-                    for (size_t b = 0; lists && b < sl.size(); ++b) {
-                        const int x1 = b + 1 < sl.size() ? sl[b + 1].first : nx;
-                        most = std::max(most, cols[s][x1] - cols[s][sl[b].first]);
-                    }
-                    nb[cx].push_back((int)sl.size());
-                    mn[cx].push_back(most);
+// One launch: slots first .. first + take - 1 of a group, cx columns per wave.
+struct ResPick {
+    int first, take, cx;
+};
+using ResPicks = std::vector<std::array<std::vector<ResPick>, R_KINDS>>;   // of every group
+
+// Picks the launches of the resident kernels for groups of the given sizes:
+// consecutive slots whose slabs fill the GPU together, one workgroup per CU, the
+// slab width of every launch chosen for the least estimated time.  False if a
+// shot fits none (too many slabs, or too many receivers on one).
+bool res_pick(const lsrtm_ctx* c, const std::vector<int>& sizes, int bz, int ncu, const ResCuts& cuts, ResPicks& picks) {
+    // workgroups of a shot, and most receivers and receiver nodes of one
+    struct Fit {
+        int blocks, recs, nodes;
+    };
+    std::vector<std::array<Fit, RES_CX_MAX + 1>> fit(c->nshot);
+    std::vector<int> cols, count, distinct;
+    for (int s = 0; s < c->nshot; ++s) {
+        const ShotInfo& sh = c->shots[s];
+        const int ldz = c->wins[sh.win].ldz;
+        cols.resize(sh.nrec);
+        for (int r = 0; r < sh.nrec; ++r) cols[r] = sh.rec_lin[r] / ldz;
+        distinct.clear();
+        for (int cx = 1; cx <= RES_CX_MAX; ++cx) {
+            const ResCut& cut = cuts[sh.win][cx];
+            Fit& f = fit[s][cx];
+            f.blocks = (int)cut.slabs.size();
+            count.assign(cut.slabs.size(), 0);
+            for (int x : cols) ++count[cut.of[x]];
+            f.recs = f.nodes = *std::max_element(count.begin(), count.end());
+            // receivers that share nodes are told apart only where it matters
+            if (res_lds_bytes(R_ADJ, bz, cx, f.nodes) > RES_LDS) {
+                if (distinct.empty()) {
+                    distinct = sh.rec_lin;
+                    std::sort(distinct.begin(), distinct.end());
+                    distinct.erase(std::unique(distinct.begin(), distinct.end()), distinct.end());
                 }
-            // best[i]: least time of slots i ..; take[i], width[i]: its first launch
-            std::vector<double> best(gr.ns + 1, 1e30);
-            std::vector<int> take(gr.ns + 1, 0), width(gr.ns + 1, 0);
-            best[gr.ns] = 0.0;
-            for (int i = gr.ns - 1; i >= 0; --i)
+                count.assign(cut.slabs.size(), 0);
+                for (int i : distinct) ++count[cut.of[i / ldz]];
+                f.nodes = *std::max_element(count.begin(), count.end());
+            }
+        }
+    }
+    picks.assign(sizes.size(), {});
+    int s0 = 0;
+    for (size_t g = 0; g < sizes.size(); s0 += sizes[g], ++g) {
+        const int ns = sizes[g];
+        for (int kind = 0; kind < R_KINDS; ++kind) {
+            // best[i]: least time of slots i ..; pick[i]: its first launch
+            std::vector<double> best(ns + 1, 1e30);
+            std::vector<ResPick> pick(ns);
+            best[ns] = 0.0;
+            for (int i = ns - 1; i >= 0; --i)
                 for (int cx = 1; cx <= RES_CX_MAX; ++cx) {
                     int blocks = 0, most = 0;
-                    for (int e = i; e < gr.ns; ++e) {
-                        blocks += nb[cx][e];
-                        most = std::max(most, mn[cx][e]);
+                    for (int e = i; e < ns; ++e) {
+                        const Fit& f = fit[s0 + e][cx];
+                        blocks += f.blocks;
+                        most = std::max(most, kind == R_SEG ? 0 : kind == R_ADJ ? f.nodes : f.recs);
                         if (blocks > ncu || res_lds_bytes(kind, bz, cx, most) > RES_LDS) break;
                         const double t = res_step_us(kind, bz * cx) + best[e + 1];
                         if (t < best[i]) {
                             best[i] = t;
-                            take[i] = e + 1 - i;
-                            width[i] = cx;
+                            pick[i] = {i, e + 1 - i, cx};
                         }
                     }
                 }
-            if (best[0] >= 1e30) return LSRTM_OK;
-            for (int i = 0; i < gr.ns; i += take[i]) {
+            if (best[0] >= 1e30) return false;
+            for (int i = 0; i < ns; i += pick[i].take) picks[g][kind].push_back(pick[i]);
+        }
+    }
+    return true;
+}
+
+// Tables of the picked launches.
+lsrtm_status plan_resident(lsrtm_ctx* c, const ResCuts& cuts, const ResPicks& picks) {
+    c->res_ok = false;
+    if (!c->res_bz) return LSRTM_OK;
+    const int bz = c->res_bz;
+    c->res_most = 0;
+    long long exn = 0;
+    size_t rounds = 1;
+    std::vector<char> tab;
+    for (size_t g = 0; g < c->groups.size(); ++g) {
+        Group& gr = c->groups[g];
+        const auto from = [&](int s) {   // receivers are in slot order
+            return std::lower_bound(gr.h_rec.begin(), gr.h_rec.end(), s, [](const Rec& R, int v) { return R.slot < v; });
+        };
+        const auto cut_of = [&](int s, int cx) -> const ResCut& { return cuts[c->shots[gr.s0 + s].win][cx]; };
+        std::vector<std::pair<ResPick, ResLaunch>> done;   // launches of kinds that record: the same tables
+        for (int kind = 0; kind < R_KINDS; ++kind) {
+            gr.res[kind].clear();
+            for (const ResPick& P : picks[g][kind]) {
+                const bool records = kind == R_BG || kind == R_BORN || kind == R_BORN_RC;
+                const int row = bz * 64, end = P.first + P.take;
                 ResLaunch L;
-                L.cx = width[i];
-                const int cxe = res_cx_edge(L.cx), row = bz * 64;
-                std::vector<ResBlock> blocks;
-                std::vector<int> first(gr.ns + 1, 0);
-                std::vector<std::vector<int>> of(gr.ns);   // workgroup of every column
-                for (int s = i; s < i + take[i]; ++s) {
-                    const int nx = gr.h_slots[s].n[1];
-                    res_slabs(nx, npml, L.cx, cxe, sl);
-                    of[s].resize(nx);
-                    for (size_t b = 0; b < sl.size(); ++b) {
-                        const int x1 = b + 1 < sl.size() ? sl[b + 1].first : nx;
-                        for (int x = sl[b].first; x < x1; ++x) of[s][x] = (int)blocks.size();
-                        blocks.push_back({s, sl[b].first,
-                                          (b > 0 ? 1 : 0) | (b + 1 < sl.size() ? 2 : 0) | (sl[b].second ? 4 : 0), 0});
+                const auto same = std::find_if(done.begin(), done.end(), [&](const auto& d) {
+                    return d.first.first == P.first && d.first.take == P.take && d.first.cx == P.cx;
+                });
+                if (records && same != done.end()) {
+                    L = same->second;
+                } else {
+                    L.cx = P.cx;
+                    std::vector<ResBlock> blocks;
+                    std::vector<int> base(P.take);           // first workgroup of every slot
+                    for (int s = P.first; s < end; ++s) {
+                        const auto& sl = cut_of(s, L.cx).slabs;
+                        base[s - P.first] = (int)blocks.size();
+                        for (size_t b = 0; b < sl.size(); ++b)
+                            blocks.push_back({s, sl[b].first,
+                                              (b > 0 ? 1 : 0) | (b + 1 < sl.size() ? 2 : 0) | (sl[b].second ? 4 : 0), 0});
                     }
+                    const auto block_of = [&](int s, int x) { return base[s - P.first] + cut_of(s, L.cx).of[x]; };
+                    L.nblocks = (int)blocks.size();
+                    if (records) {
+                        const auto r0 = from(P.first), r1 = from(end);
+                        std::vector<int> ptr(blocks.size() + 1, 0), at(r1 - r0), col(r1 - r0);
+                        for (auto R = r0; R != r1; ++R) {
+                            col[R - r0] = R->idx / gr.h_slots[R->slot].ldz;
+                            ptr[1 + (at[R - r0] = block_of(R->slot, col[R - r0]))] += 1;
+                        }
+                        for (size_t b = 0; b < blocks.size(); ++b) {
+                            L.most = std::max(L.most, ptr[b + 1]);
+                            ptr[b + 1] += ptr[b];
+                        }
+                        std::vector<Rec> all(r1 - r0);
+                        std::vector<int> next(ptr);
+                        for (auto R = r0; R != r1; ++R) {
+                            const int x = col[R - r0], z = R->idx - x * gr.h_slots[R->slot].ldz, b = at[R - r0];
+                            Rec T = *R;
+                            T.idx = (x - blocks[b].x0 + HW) * row + (z % bz) * 64 + z / bz;
+                            all[next[b]++] = T;
+                        }
+                        L.rptr = add_table(tab, ptr);
+                        L.rec = add_table(tab, all);
+                    }
+                    if (kind == R_ADJ) {
+                        // nodes are in the order of slots and columns, hence of workgroups
+                        const auto u0 = std::lower_bound(gr.h_node_slot.begin(), gr.h_node_slot.end(), P.first) - gr.h_node_slot.begin();
+                        const auto u1 = std::lower_bound(gr.h_node_slot.begin(), gr.h_node_slot.end(), end) - gr.h_node_slot.begin();
+                        std::vector<int> ptr(blocks.size() + 1, 0);
+                        std::vector<int4> all;
+                        all.reserve(u1 - u0);
+                        for (auto u = u0; u < u1; ++u) {
+                            const int s = gr.h_node_slot[u], ldz = gr.h_slots[s].ldz, x = gr.h_node_idx[u] / ldz, z = gr.h_node_idx[u] % ldz;
+                            const int b = block_of(s, x), cw = (blocks[b].nb & 4) ? res_cx_edge(L.cx) : L.cx, j = x - blocks[b].x0;
+                            const int owner = (j / cw) * 64 + z / bz, bit = (j % cw) * bz + z % bz;
+                            all.push_back(make_int4(owner << 8 | bit, gr.h_node_ptr[u], gr.h_node_ptr[u + 1], 0));
+                            ptr[b + 1] += 1;
+                        }
+                        for (size_t b = 0; b < blocks.size(); ++b) {
+                            L.most = std::max(L.most, ptr[b + 1]);
+                            ptr[b + 1] += ptr[b];
+                            std::sort(all.begin() + ptr[b], all.begin() + ptr[b + 1],
+                                      [](const int4& a, const int4& b) { return a.x < b.x; });
+                        }
+                        L.nptr = add_table(tab, ptr);
+                        L.node = add_table(tab, all);
+                    }
+                    L.blocks = add_table(tab, blocks);
+                    if (records) done.push_back({P, L});
                 }
-                L.nblocks = (int)blocks.size();
-                int most = 0;
-                const auto from = [&](int s) {   // receivers are in slot order
-                    return std::lower_bound(gr.h_rec.begin(), gr.h_rec.end(), s,
-                                            [](const Rec& R, int v) { return R.slot < v; });
-                };
-                if (kind == R_BG || kind == R_BORN || kind == R_BORN_RC) {
-                    const auto r0 = from(i), r1 = from(i + take[i]);
-                    std::vector<int> ptr(blocks.size() + 1, 0), at(r1 - r0);
-                    for (auto R = r0; R != r1; ++R) ptr[1 + (at[R - r0] = of[R->slot][R->idx / gr.h_slots[R->slot].ldz])] += 1;
-                    for (size_t b = 0; b < blocks.size(); ++b) {
-                        most = std::max(most, ptr[b + 1]);
-                        ptr[b + 1] += ptr[b];
-                    }
-                    std::vector<Rec> all(r1 - r0);
-                    std::vector<int> next(ptr);
-                    for (auto R = r0; R != r1; ++R) {
-                        const int ldz = gr.h_slots[R->slot].ldz, x = R->idx / ldz, z = R->idx % ldz, b = at[R - r0];
-                        Rec T = *R;
-                        T.idx = (x - blocks[b].x0 + HW) * row + (z % bz) * 64 + z / bz;
-                        all[next[b]++] = T;
-                    }
-                    L.rptr = add_table(tab, ptr);
-                    L.rec = add_table(tab, all);
-                }
-                if (kind == R_ADJ) {
-                    // nodes are in the order of slots and columns, hence of workgroups
-                    const auto u0 = std::lower_bound(gr.h_node_slot.begin(), gr.h_node_slot.end(), i) - gr.h_node_slot.begin();
-                    const auto u1 = std::lower_bound(gr.h_node_slot.begin(), gr.h_node_slot.end(), i + take[i]) - gr.h_node_slot.begin();
-                    std::vector<int> ptr(blocks.size() + 1, 0);
-                    std::vector<int4> all;
-                    all.reserve(u1 - u0);
-                    for (auto u = u0; u < u1; ++u) {
-                        const int s = gr.h_node_slot[u], ldz = gr.h_slots[s].ldz, x = gr.h_node_idx[u] / ldz, z = gr.h_node_idx[u] % ldz;
-                        const int b = of[s][x], cw = (blocks[b].nb & 4) ? cxe : L.cx, j = x - blocks[b].x0;
-                        const int owner = (j / cw) * 64 + z / bz, bit = (j % cw) * bz + z % bz;
-                        all.push_back(make_int4(owner << 8 | bit, gr.h_node_ptr[u], gr.h_node_ptr[u + 1], 0));
-                        ptr[b + 1] += 1;
-                    }
-                    for (size_t b = 0; b < blocks.size(); ++b) {
-                        L.maxnodes = most = std::max(most, ptr[b + 1]);
-                        ptr[b + 1] += ptr[b];
-                        std::sort(all.begin() + ptr[b], all.begin() + ptr[b + 1],
-                                  [](const int4& a, const int4& b) { return a.x < b.x; });
-                    }
-                    L.nptr = add_table(tab, ptr);
-                    L.node = add_table(tab, all);
-                }
-                L.blocks = add_table(tab, blocks);
-                L.lds = res_lds_bytes(kind, bz, L.cx, most);
+                L.lds = res_lds_bytes(kind, bz, L.cx, L.most);
                 exn = std::max(exn, L.nblocks * res_ex_words(bz, kind == R_BORN ? 2 : 1));
                 c->res_most = std::max(c->res_most, L.nblocks);
                 gr.res[kind].push_back(L);
@@ -1298,10 +1345,11 @@ lsrtm_status plan_resident(lsrtm_ctx* c) {
     }
     c->res_ctln = (int)((2 * c->nseg + 4) * rounds + 1);
     c->res_exn = exn;
-    CHK(dalloc_t(c, &c->res_tab, tab.size(), true));
+    // without room for these the passes stay on the streaming kernels
+    if (dalloc_t(c, &c->res_tab, tab.size(), true) != LSRTM_OK || dalloc_t(c, &c->res_ex, exn, true) != LSRTM_OK ||
+        dalloc_t(c, &c->res_ctl, c->res_ctln, true) != LSRTM_OK)
+        return LSRTM_OK;
     HIPCHK(c, hipMemcpy(c->res_tab, tab.data(), tab.size(), hipMemcpyHostToDevice));
-    CHK(dalloc_t(c, &c->res_ex, exn, true));
-    CHK(dalloc_t(c, &c->res_ctl, c->res_ctln, true));
     c->res_ok = true;
     return LSRTM_OK;
 }
@@ -1397,11 +1445,6 @@ lsrtm_status plan(lsrtm_ctx* c) {
     }
 
     c->fused = nd == 2 && c->opt_fused;
-    // the resident kernels store a column's replay rows in whole waves
-    c->res_bz = res_rows(c);
-    for (auto& W : c->wins)
-        W.segn = c->res_bz ? res_segn(W.npts, W.N[1], c->res_bz) : W.npts;
-
     // ---- memory plan --------------------------------------------------------
     size_t fr = 0, tot = 0;
     HIPCHK(c, hipMemGetInfo(&fr, &tot));
@@ -1426,23 +1469,23 @@ lsrtm_status plan(lsrtm_ctx* c) {
     // Where checkpoints are rounded the interval shows in the results: there
     // it is planned without the resident layout's larger replay buffer.
     const bool rounds = c->g.ckpt_dtype != 0 && c->g.ckpt_every <= 0;
+    const int bz = c->opt_res ? res_rows(c) : 0;
+    ResCuts cuts;
+    int per_round = 0;             // shots of a round of resident launches, where it is the same for all
+    if (bz) {
+        HIPCHK(c, hipGetDevice(&c->res_dev));
+        HIPCHK(c, hipDeviceGetAttribute(&c->res_cus, hipDeviceAttributeMultiprocessorCount, c->res_dev));
+        cuts = res_cuts(c);
+        if (c->wins.size() == 1) per_round = c->res_cus / (int)cuts[0][RES_CX_MAX].slabs.size();
+    }
     // Group sizes: balanced, or as many groups of whole rounds of the resident
     // launches, what is left over shared among the first, where that makes
     // fewer rounds (120 shots of 280 x 777 in groups of at most 32, 7 shots to a
     // round: 32, 32, 28, 28 and 18 rounds instead of 4 x 30 and 20; a Born pass 79.7 ms
     // instead of 84.1, a migration 112.8 instead of 120.2).
-    int per_round = 0;
-    if (c->res_bz && c->wins.size() == 1 && !rounds) {
-        int dev = 0, ncu = 0;
-        HIPCHK(c, hipGetDevice(&dev));
-        HIPCHK(c, hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-        std::vector<std::pair<int, bool>> sl;
-        res_slabs(c->wins[0].N[1], npml, RES_CX_MAX, res_cx_edge(RES_CX_MAX), sl);
-        per_round = ncu / (int)sl.size();
-    }
-    const auto sizes_of = [&](int most) {
+    const auto sizes_of = [&](int most, bool res) {
         const std::vector<int> even = group_sizes(nshot, most);
-        if (per_round < 2 || most < per_round) return even;
+        if (!res || per_round < 2 || most < per_round) return even;
         const int q = most / per_round * per_round;
         int left = nshot - q * (int)even.size();
         if (left < 0) return even;
@@ -1458,130 +1501,144 @@ lsrtm_status plan(lsrtm_ctx* c) {
         };
         return count(whole) < count(even) ? whole : even;
     };
-    const auto seg_pts = [&](const Window& W) { return rounds ? W.npts : W.segn; };
-    int G = G0, k = 1;
-    long long need = 0;
-    bool ckg = false, fits = false;
-    for (int mode = c->opt_ckg ? 1 : 0; mode < 2 && !fits; ++mode) {
-        ckg = mode == 1;
-        G = G0;
-        for (;;) {
-            long long grp_pts = 0, grp_seg = 0;
-            {
-                int s = 0;
-                for (int gs : sizes_of(G)) {
-                    long long cur = 0, seg = 0;
-                    for (int e = 0; e < gs; ++e, ++s) {
-                        cur += c->wins[c->shots[s].win].npts;
-                        seg += seg_pts(c->wins[c->shots[s].win]);
-                    }
-                    grp_pts = std::max(grp_pts, cur);
-                    grp_seg = std::max(grp_seg, seg);
-                }
-            }
-            const long long seg_step = grp_seg * (nd + 1) * 4;
-            const double ck_mem = ckg ? (double)G * max_ck : (double)ck_per_shot_sum;
-            if (c->g.ckpt_every > 0) {
-                k = std::min(c->g.ckpt_every, nt);
-            } else {
-                const double kk = std::sqrt((double)nt * ck_mem / (double)std::max(1LL, seg_step));
-                k = (int)std::max(1.0, std::min((double)nt, std::round(kk)));
-            }
-            const int nseg = (nt + k - 1) / k;
-            need = fixed + grp_pts * (nbg + nsc + 2) * 4LL + (long long)k * seg_step +
-                   (long long)((nseg - 1) * ck_mem) + (long long)nseg * nshot * (1 + nd) * 4;
-            if (need <= budget) {
-                fits = true;
-                break;
-            }
-            if (G == 1) break;
-            G = (G + 1) / 2;
-        }
-    }
-    if (!fits)
-        FAIL(c, LSRTM_ENOMEM, "memory plan needs %.2f GB, budget %.2f GB", need / 1e9, budget / 1e9);
-    // An interval that the planner chose is the one of least memory.  From
-    // there it may change where that pays; results do not depend on it, except
-    // that 16-bit checkpoints round at other steps.
-    // With a replay cache (whole segments only) it may shrink, down to half,
-    // when the cache then holds more steps.
-    // A resident segment costs by its ends too (a checkpoint, two launches that
-    // read and write a shot's registers: 40 to 90 us), so resident plans take the
-    // longest one, up to a fifth of the march, that is within a thirtieth of the
-    // least memory, which is flat there (500 steps of 120 shots of 280 x 777: segments of
-    // 45 steps 8.7 GB and 151 ms, of 64 steps 9.0 GB and 143 ms), as long as the
-    // cache holds no less.
-    const bool lengthen = c->res_bz > 0 && c->g.ckpt_dtype == 0;
-    if ((c->opt_rcache_mb > 0 || lengthen) && !c->fused && !ckg && c->g.ckpt_every <= 0) {
+    // The resident kernels store a column's replay rows in whole waves.
+    const auto seg_of = [&](const Window& W, bool res) { return res ? res_segn(W.npts, W.N[1], bz) : W.npts; };
+    struct Sizing {
+        std::vector<int> sizes;    // shots of every launch group, at most G
+        int G = 1, k = 1;
+        long long need = 0;
+        bool ckg = false, fits = false;
+    };
+    const auto size_plan = [&](bool res) {
+        Sizing z;
+        // points of the largest group and of all shots, and their replay buffers'
         long long grp_pts = 0, grp_seg = 0, all_seg = 0;
-        {
+        const auto group = [&]() {
+            z.sizes = sizes_of(z.G, res);
+            grp_pts = grp_seg = all_seg = 0;
             int s = 0;
-            for (int gs : sizes_of(G)) {
+            for (int gs : z.sizes) {
                 long long cur = 0, seg = 0;
                 for (int e = 0; e < gs; ++e, ++s) {
                     cur += c->wins[c->shots[s].win].npts;
-                    seg += seg_pts(c->wins[c->shots[s].win]);
+                    seg += seg_of(c->wins[c->shots[s].win], res);
                 }
                 grp_pts = std::max(grp_pts, cur);
                 grp_seg = std::max(grp_seg, seg);
                 all_seg += seg;
             }
-        }
-        const long long seg_step = grp_seg * (nd + 1) * 4;   // replay buffer bytes per step
-        const long long step_all = all_seg * (nd + 1) * 4;   // cache bytes per step, all groups
-        auto need_of = [&](int kk) -> long long {
-            const int ns = (nt + kk - 1) / kk;
-            return fixed + grp_pts * (nbg + nsc + 2) * 4LL + (long long)kk * seg_step +
-                   (long long)((ns - 1) * (double)ck_per_shot_sum) + (long long)ns * nshot * (1 + nd) * 4;
         };
-        auto held = [&](int kk) -> long long {   // steps of every group the cache would hold
-            const long long nk = need_of(kk);
-            if (nk > budget) return -1;
-            const long long cap = std::min(c->opt_rcache_mb * 1024LL * 1024LL, budget - nk);
-            const int ns = (nt + kk - 1) / kk;
-            const long long m = std::min<long long>(ns, cap / ((long long)kk * step_all));
-            return m >= ns ? nt : m * kk;
-        };
-        int bk = k;
-        long long best = held(k);
-        for (int kk = k - 1; kk >= std::max(1, k / 2); --kk) {
-            const long long h = held(kk);
-            if (h > best) {
-                best = h;
-                bk = kk;
+        for (int mode = c->opt_ckg ? 1 : 0; mode < 2 && !z.fits; ++mode) {
+            z.ckg = mode == 1;
+            z.G = G0;
+            for (;;) {
+                group();
+                const long long seg_step = grp_seg * (nd + 1) * 4;
+                const double ck_mem = z.ckg ? (double)z.G * max_ck : (double)ck_per_shot_sum;
+                if (c->g.ckpt_every > 0) {
+                    z.k = std::min(c->g.ckpt_every, nt);
+                } else {
+                    const double kk = std::sqrt((double)nt * ck_mem / (double)std::max(1LL, seg_step));
+                    z.k = (int)std::max(1.0, std::min((double)nt, std::round(kk)));
+                }
+                const int nseg = (nt + z.k - 1) / z.k;
+                z.need = fixed + grp_pts * (nbg + nsc + 2) * 4LL + (long long)z.k * seg_step +
+                         (long long)((nseg - 1) * ck_mem) + (long long)nseg * nshot * (1 + nd) * 4;
+                if (z.need <= budget) {
+                    z.fits = true;
+                    break;
+                }
+                if (z.G == 1) break;
+                z.G = (z.G + 1) / 2;
             }
         }
-        for (int kk = std::max(bk + 1, (nt + 4) / 5); lengthen && kk > bk; --kk)
-            if (need_of(kk) <= need + need / 30 && held(kk) >= best) {
-                bk = kk;
-                break;
+        if (!z.fits) return z;
+        // An interval that the planner chose is the one of least memory.  From
+        // there it may change where that pays; results do not depend on it, except
+        // that 16-bit checkpoints round at other steps.
+        // With a replay cache (whole segments only) it may shrink, down to half,
+        // when the cache then holds more steps.
+        // A resident segment costs by its ends too (a checkpoint, two launches that
+        // read and write a shot's registers: 40 to 90 us), so resident plans take the
+        // longest one, up to a fifth of the march, that is within a thirtieth of the
+        // least memory, which is flat there (500 steps of 120 shots of 280 x 777: segments of
+        // 45 steps 8.7 GB and 151 ms, of 64 steps 9.0 GB and 143 ms), as long as the
+        // cache holds no less.
+        const bool lengthen = res && c->g.ckpt_dtype == 0;
+        if ((c->opt_rcache_mb > 0 || lengthen) && !c->fused && !z.ckg && c->g.ckpt_every <= 0) {
+            const long long seg_step = grp_seg * (nd + 1) * 4;   // replay buffer bytes per step
+            const long long step_all = all_seg * (nd + 1) * 4;   // cache bytes per step, all groups
+            auto need_of = [&](int kk) -> long long {
+                const int ns = (nt + kk - 1) / kk;
+                return fixed + grp_pts * (nbg + nsc + 2) * 4LL + (long long)kk * seg_step +
+                       (long long)((ns - 1) * (double)ck_per_shot_sum) + (long long)ns * nshot * (1 + nd) * 4;
+            };
+            auto held = [&](int kk) -> long long {   // steps of every group the cache would hold
+                const long long nk = need_of(kk);
+                if (nk > budget) return -1;
+                const long long cap = std::min(c->opt_rcache_mb * 1024LL * 1024LL, budget - nk);
+                const int ns = (nt + kk - 1) / kk;
+                const long long m = std::min<long long>(ns, cap / ((long long)kk * step_all));
+                return m >= ns ? nt : m * kk;
+            };
+            int bk = z.k;
+            long long best = held(z.k);
+            for (int kk = z.k - 1; kk >= std::max(1, z.k / 2); --kk) {
+                const long long h = held(kk);
+                if (h > best) {
+                    best = h;
+                    bk = kk;
+                }
             }
-        if (bk != k) {
-            k = bk;
-            need = need_of(k);
+            for (int kk = std::max(bk + 1, (nt + 4) / 5); lengthen && kk > bk; --kk)
+                if (need_of(kk) <= z.need + z.need / 30 && held(kk) >= best) {
+                    bk = kk;
+                    break;
+                }
+            if (bk != z.k) {
+                z.k = bk;
+                z.need = need_of(z.k);
+            }
         }
-    }
-    if (rounds && c->res_bz) {
-        long long more = 0;      // of the resident layout's replay buffer
-        int s = 0;
-        for (int gs : sizes_of(G)) {
-            long long d = 0;
-            for (int e = 0; e < gs; ++e, ++s) d += c->wins[c->shots[s].win].segn - c->wins[c->shots[s].win].npts;
-            more = std::max(more, d);
-        }
-        more *= (long long)k * (nd + 1) * 4;
-        if (need + more <= budget) {
-            need += more;
+        return z;
+    };
+    // What fits is decided without the resident kernels' larger replay buffer
+    // (1.1 times at 280 padded rows, 2 to 4 times below 65): they are taken where
+    // that buffer fits the budget too, with the same checkpoint layout.
+    Sizing z = size_plan(false);
+    if (!z.fits)
+        FAIL(c, LSRTM_ENOMEM, "memory plan needs %.2f GB, budget %.2f GB", z.need / 1e9, budget / 1e9);
+    ResPicks picks;
+    c->res_bz = 0;
+    if (bz) {
+        Sizing r = z;
+        if (rounds) {
+            // of the resident layout's replay buffer
+            long long more = 0;
+            int s = 0;
+            for (int gs : z.sizes) {
+                long long d = 0;
+                for (int e = 0; e < gs; ++e, ++s) d += seg_of(c->wins[c->shots[s].win], true) - c->wins[c->shots[s].win].npts;
+                more = std::max(more, d);
+            }
+            r.need += more * z.k * (nd + 1) * 4;
+            r.fits = r.need <= budget;
         } else {
-            c->res_bz = 0;
-            for (auto& W : c->wins) W.segn = W.npts;
+            r = size_plan(true);
+        }
+        if (r.fits && r.ckg == z.ckg && res_pick(c, r.sizes, bz, c->res_cus, cuts, picks)) {
+            c->res_bz = bz;
+            z = r;
         }
     }
+    for (auto& W : c->wins) W.segn = seg_of(W, c->res_bz > 0);
+    const int G = z.G;
+    const bool ckg = z.ckg;
+    const long long need = z.need;
+    c->k = z.k;
     c->ck_group = ckg;
-    const std::vector<int> sizes = sizes_of(G);
-    c->G = *std::max_element(sizes.begin(), sizes.end());
-    c->k = k;
-    c->nseg = (nt + k - 1) / k;
+    c->G = *std::max_element(z.sizes.begin(), z.sizes.end());
+    c->nseg = (nt + c->k - 1) / c->k;
     c->plan_bytes = need;
 
     // ---- model windows -------------------------------------------------------
@@ -1606,7 +1663,7 @@ lsrtm_status plan(lsrtm_ctx* c) {
     }
     // ---- groups ----------------------------------------------------------------
     int s0 = 0;
-    for (int gs : sizes_of(G)) {
+    for (int gs : z.sizes) {
         Group gr;
         gr.s0 = s0;
         gr.ns = gs;
@@ -1831,7 +1888,7 @@ lsrtm_status plan(lsrtm_ctx* c) {
         }
         HIPCHK(c, hipMemcpy(gr.d_node_ptr, nptr.data(), nptr.size() * sizeof(int), hipMemcpyHostToDevice));
     }
-    CHK(plan_resident(c));
+    CHK(plan_resident(c, cuts, picks));
     c->have_acq = true;
     CHK(prep_model_windows(c));
     return LSRTM_OK;
@@ -2150,8 +2207,14 @@ lsrtm_status lsrtm_set_option(lsrtm_ctx* c, int key, long long v) {
     }
     case LSRTM_OPT_GRAPH: c->opt_graph = v != 0; return LSRTM_OK;
     case LSRTM_OPT_RESIDENT:
-        c->opt_res = v == 0 ? 0 : v == 2 ? 2 : 1;
         c->res_pause = 0;
+        if ((c->opt_res != 0) == (v != 0)) {
+            c->opt_res = v == 0 ? 0 : v == 2 ? 2 : 1;
+            return LSRTM_OK;
+        }
+        c->opt_res = v == 0 ? 0 : v == 2 ? 2 : 1;
+        // the replay buffer's layout
+        if (c->have_acq && c->ndim == 2 && (v != 0 || c->res_bz)) return plan(c);
         return LSRTM_OK;
     case LSRTM_OPT_TIMING: c->opt_timing = v != 0; return LSRTM_OK;
     case LSRTM_OPT_MEM_BUDGET_MB:

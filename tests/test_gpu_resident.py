@@ -295,3 +295,85 @@ def test_streaming_passes_of_resident_plans_are_tuned(tmp_path, monkeypatch):
             streaming(ctx)
             assert len(file.read_text().splitlines()) == 1
         ctx.close()
+
+
+def _context(torch, w, resident, **opts):
+    """Planned with the option set (or None for the default)."""
+    ctx = lsrtm.Context(tuple(reversed(w.lnvp.shape)), w.h, w.nt, w.dt, npml=w.npml, pml_R=w.pml_R, pml_f0=w.pml_freq,
+                        tile=1, **opts)
+    if resident is not None:
+        ctx.set_option(lsrtm.OPT_RESIDENT, resident)
+    ctx.set_model(to_dev(torch, w.lnvp), to_dev(torch, w.lnip))
+    ctx.set_acquisition(w.win, w.src, w.rec, to_dev(torch, w.wavelet))
+    return ctx
+
+
+@pytest.mark.parametrize("opts", [{"ckpt_every": 60}, {}, {"ckpt_dtype": "bf16"}, {"ckpt_dtype": "bf16", "ckpt_every": 60}])
+def test_budgets_that_held_the_plan_still_do(opts):
+    """The resident kernels' replay buffer takes four times the memory at 32
+    padded rows.  A budget that holds a plan without it holds one with the
+    option on, with the same checkpoint layout; the results are the same."""
+    torch = require_gpu()
+    w = synth.small((20, 400), nt=60, npml=6, seed=31, nshot=8, nrec=40)
+    dm = to_dev(torch, w.dm)
+    seen = set()
+    ref = None
+    for budget in list(range(66, 100, 2)) + list(range(100, 460, 20)):
+        plans = []
+        for resident in (0, 1):
+            try:
+                ctx = _context(torch, w, resident, mem_budget_mb=budget, **opts)
+            except lsrtm.LsrtmError as e:
+                assert e.status == lsrtm.ENOMEM
+                plans.append(None)
+                continue
+            sz = ctx.sizes()
+            assert sz["plan_bytes"] <= budget << 20
+            plans.append(sz["ckpt_per_group"])
+            if resident:
+                on = ctx.resident()["planned"]
+                if (on, sz["ckpt_per_group"], sz["groups"]) not in seen:
+                    d = ctx.born(dm)
+                    got = (d, ctx.adjoint(d)) if "ckpt_dtype" not in opts else (d,)
+                    ref = ref or got
+                    assert ctx.resident()["last"] == on
+                    assert all(torch.equal(a, b) for a, b in zip(ref, got))
+                seen.add((on, sz["ckpt_per_group"], sz["groups"]))
+            ctx.close()
+        assert plans[0] == plans[1], (budget, plans)
+    assert {on for on, _, _ in seen} == {True, False}
+
+
+def test_plans_without_the_resident_layout():
+    """With the option off, and where a slab has more receivers than its LDS
+    holds, the replay buffer has the size that the streaming kernels need, the
+    groups are balanced, and turning the option off and on re-plans."""
+    torch = require_gpu()
+    k = 10
+    w = synth.small((20, 765), nt=40, npml=6, seed=32, nshot=16, nrec=40)
+    off, on = _context(torch, w, 0, ckpt_every=k, shots_per_launch=9), _context(torch, w, 1, ckpt_every=k, shots_per_launch=9)
+    assert off.sizes()["shots_per_launch"] == 8 and on.sizes()["shots_per_launch"] == 9
+    padded, plain = 777 * 2 * 64, 777 * 32
+    grp = lambda n: n * (plain * (7 + 7 + 2) * 4)
+    assert on.sizes()["plan_bytes"] - off.sizes()["plan_bytes"] == grp(9) - grp(8) + k * 3 * 4 * (9 * padded - 8 * plain)
+    sizes = on.sizes()
+    on.set_option(lsrtm.OPT_RESIDENT, 0)
+    assert on.sizes() == off.sizes() and not on.resident()["planned"]
+    on.set_option(lsrtm.OPT_RESIDENT, 1)
+    assert on.sizes() == sizes and on.resident()["planned"]
+    for ctx in (off, on):
+        ctx.close()
+    many = synth.small((20, 60), nt=20, npml=6, seed=33, nshot=2)
+    many.rec[0] = np.stack([np.random.default_rng(1).integers(0, 20, 12000), np.full(12000, 30)], axis=1)
+    for dup, fits in ((many.rec[0], False), (many.rec[0][:4000], True)):
+        many.rec[0] = dup
+        ctx, ref = (_context(torch, many, r, ckpt_every=7) for r in (1, 0))
+        assert ctx.resident()["planned"] == fits
+        if not fits:
+            assert ctx.sizes()["plan_bytes"] == ref.sizes()["plan_bytes"]
+        d = ctx.born(to_dev(torch, many.dm))
+        assert torch.equal(d, ref.born(to_dev(torch, many.dm)))
+        assert torch.equal(ctx.adjoint(d), ref.adjoint(d))
+        assert ctx.resident()["last"] == fits
+        ctx.close()
+        ref.close()
