@@ -1193,13 +1193,21 @@ bool res_pick(const lsrtm_ctx* c, const std::vector<int>& sizes, int bz, int ncu
     for (int s = 0; s < c->nshot; ++s) {
         const ShotInfo& sh = c->shots[s];
         const int ldz = c->wins[sh.win].ldz;
-        cols.resize(sh.nrec);
-        for (int r = 0; r < sh.nrec; ++r) cols[r] = sh.rec_lin[r] / ldz;
+        cols.clear();
         distinct.clear();
         for (int cx = 1; cx <= RES_CX_MAX; ++cx) {
             const ResCut& cut = cuts[sh.win][cx];
             Fit& f = fit[s][cx];
             f.blocks = (int)cut.slabs.size();
+            // counted only where all of the shot's on one slab would not fit
+            f.recs = f.nodes = sh.nrec;
+            bool any = true;
+            for (int kind = 0; kind < R_KINDS; ++kind) any = any && res_lds_bytes(kind, bz, cx, kind == R_SEG ? 0 : sh.nrec) <= RES_LDS;
+            if (any) continue;
+            if (cols.empty()) {
+                cols.resize(sh.nrec);
+                for (int r = 0; r < sh.nrec; ++r) cols[r] = sh.rec_lin[r] / ldz;
+            }
             count.assign(cut.slabs.size(), 0);
             for (int x : cols) ++count[cut.of[x]];
             f.recs = f.nodes = *std::max_element(count.begin(), count.end());
@@ -1256,6 +1264,9 @@ lsrtm_status plan_resident(lsrtm_ctx* c, const ResCuts& cuts, const ResPicks& pi
     long long exn = 0;
     size_t rounds = 1;
     std::vector<char> tab;
+    size_t listed = 0;
+    for (const Group& gr : c->groups) listed += gr.h_rec.size() * sizeof(Rec) + gr.h_node_idx.size() * sizeof(int4);
+    tab.reserve(listed + (1 << 20));
     for (size_t g = 0; g < c->groups.size(); ++g) {
         Group& gr = c->groups[g];
         const auto from = [&](int s) {   // receivers are in slot order
@@ -1326,8 +1337,9 @@ lsrtm_status plan_resident(lsrtm_ctx* c, const ResCuts& cuts, const ResPicks& pi
                         for (size_t b = 0; b < blocks.size(); ++b) {
                             L.most = std::max(L.most, ptr[b + 1]);
                             ptr[b + 1] += ptr[b];
-                            std::sort(all.begin() + ptr[b], all.begin() + ptr[b + 1],
-                                      [](const int4& a, const int4& b) { return a.x < b.x; });
+                            const auto less = [](const int4& a, const int4& b) { return a.x < b.x; };
+                            if (!std::is_sorted(all.begin() + ptr[b], all.begin() + ptr[b + 1], less))   // they are, on one row
+                                std::sort(all.begin() + ptr[b], all.begin() + ptr[b + 1], less);
                         }
                         L.nptr = add_table(tab, ptr);
                         L.node = add_table(tab, all);
@@ -1852,7 +1864,6 @@ lsrtm_status plan(lsrtm_ctx* c) {
         CHK(dalloc_t(c, &gr.d_win, wins6.size(), true));
         HIPCHK(c, hipMemcpy(gr.d_win, wins6.data(), wins6.size() * sizeof(int), hipMemcpyHostToDevice));
         gr.nrec = (int)recs.size();
-        gr.h_rec = recs;
         CHK(dalloc_t(c, &gr.d_rec, std::max<size_t>(1, recs.size()), true));
         if (!recs.empty())
             HIPCHK(c, hipMemcpy(gr.d_rec, recs.data(), recs.size() * sizeof(Rec), hipMemcpyHostToDevice));
@@ -1874,9 +1885,6 @@ lsrtm_status plan(lsrtm_ctx* c) {
         }
         nptr.push_back((int)nrec.size());
         gr.nnode = (int)nslot.size();
-        gr.h_node_slot = nslot;
-        gr.h_node_idx = nidx;
-        gr.h_node_ptr = nptr;
         CHK(dalloc_t(c, &gr.d_node_slot, std::max<size_t>(1, nslot.size()), true));
         CHK(dalloc_t(c, &gr.d_node_idx, std::max<size_t>(1, nidx.size()), true));
         CHK(dalloc_t(c, &gr.d_node_ptr, nptr.size(), true));
@@ -1887,6 +1895,10 @@ lsrtm_status plan(lsrtm_ctx* c) {
             HIPCHK(c, hipMemcpy(gr.d_node_rec, nrec.data(), nrec.size() * sizeof(Rec), hipMemcpyHostToDevice));
         }
         HIPCHK(c, hipMemcpy(gr.d_node_ptr, nptr.data(), nptr.size() * sizeof(int), hipMemcpyHostToDevice));
+        gr.h_rec = std::move(recs);
+        gr.h_node_slot = std::move(nslot);
+        gr.h_node_idx = std::move(nidx);
+        gr.h_node_ptr = std::move(nptr);
     }
     CHK(plan_resident(c, cuts, picks));
     c->have_acq = true;
