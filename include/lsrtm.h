@@ -134,11 +134,14 @@ enum {
                                        group plus 8 (default)                   */
     LSRTM_OPT_RESIDENT = 13         /* 2D: 1 = keep a shot's fields in registers
                                        through many time steps per launch where
-                                       its window fits (default; padded depth
-                                       up to 384 nodes, two-phase steps), 0 =
-                                       one velocity and one pressure kernel per
-                                       step.  Both give identical results.  The
-                                       replay buffer has a layout for each:
+                                       its window fits (padded depth up to 384
+                                       nodes, two-phase steps) and an estimate
+                                       finds that faster for the kind of call
+                                       (default; not for many shallow shots or
+                                       very few steps), 3 = wherever it fits,
+                                       0 = one velocity and one pressure kernel
+                                       per step.  All give identical results.
+                                       The replay buffer has a layout for each:
                                        re-plans when turned on or off.  2 =
                                        as 1, but no launch finds room on the
                                        GPU: every call goes the way back to
@@ -400,8 +403,8 @@ lsrtm_status lsrtm_autotune(lsrtm_ctx* ctx, int nsteps, int tune_groups, double*
  * Errors: EINVAL (NULL ctx or out). */
 lsrtm_status lsrtm_sizes(lsrtm_ctx* ctx, long long* out, int nout);
 
-/* Resident 2D time stepping (LSRTM_OPT_RESIDENT): out[0] = 1 if the plan's
- * calls take it, out[1] = 1 if the last call of a pass (forward, Born,
+/* Resident 2D time stepping (LSRTM_OPT_RESIDENT): out[0] = 1 if calls of the
+ * plan take it, out[1] = 1 if the last call of a pass (forward, Born,
  * migration; the last pass of a CGNR call) ran on it, out[2] = calls so far
  * that found the GPU held by other work (the launch waits half a second for
  * its workgroups) and ran again on the kernels per step.  After such a call

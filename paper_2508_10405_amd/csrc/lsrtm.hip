@@ -208,10 +208,13 @@ struct lsrtm_ctx {
     int opt_tile_v = -1;           // two-phase steps: tile of the velocity phases (-1: tile)
     int opt_tile_a = -1;           // two-phase steps: tile of the adjoint A phase (-1: tile)
     long long opt_rcache_mb = 0;   // HBM the replay cache may take (0: none)
-    int opt_res = 1;               // 2D: resident time stepping where the plan allows it (2: rehearse its giving up)
+    int opt_res = 1;               // 2D: resident time stepping where the plan allows it (2: rehearse its
+                                   // giving up, 3: whatever the estimate says)
     // resident time stepping
     bool res_ok = false;           // the plan's windows fit
-    bool res_on = false;           // passes run on it (replay-cache layout too)
+    bool res_pass[3] = {};         // by kind of pass (PASS_*): estimated to be the faster ones
+    bool res_on = false;           // the pass under way runs on them
+    bool rc_res = false;           // layout of the replay cache: theirs
     int res_bz = 0;
     int res_dev = 0, res_cus = 0;  // the device and its CUs
     int res_most = 0;              // workgroups of the largest launch
@@ -291,6 +294,12 @@ template <typename T>
 lsrtm_status dalloc_t(lsrtm_ctx* c, T** p, size_t n, bool acq) {
     return dalloc(c, reinterpret_cast<void**>(p), n * sizeof(T), acq);
 }
+
+// Kinds of calls that choose between the resident and the streaming kernels.
+enum { PASS_FORWARD = 0, PASS_BORN = 1, PASS_MIGRATION = 2 };
+
+// The replay cache holds a group's replays, in the layout of the pass under way.
+bool rc_ready(const lsrtm_ctx* c, const Group& gr) { return c->rc_m > 0 && gr.rc_valid && c->rc_res == c->res_on; }
 
 // The background changed (model, or a failed snapshot): stored checkpoints
 // and cached replays are stale.
@@ -731,7 +740,7 @@ lsrtm_status res_forward(lsrtm_ctx* c, Group& gr, int mode, float* d, bool write
     if (mode == 1) CHK(fill(c, c->pool + c->bg_region, gr.sc_used));
     CHK(res_begin(c));
     const int nt = c->g.nt, jc = c->nseg - c->rc_m;
-    const bool use_rc = mode == 1 && !write_ck && c->rc_m > 0 && gr.rc_valid;
+    const bool use_rc = mode == 1 && !write_ck && rc_ready(c, gr);
     for (int n = 0; n < nt;) {
         const int j = n / c->k;
         int end = nt;
@@ -923,7 +932,7 @@ lsrtm_status run_group_impl(lsrtm_ctx* c, Group& gr, int gi, int pass, float* d,
     }
     // a migration pass that fills the replay cache and one that reads it are
     // different graphs, and so are Born passes with and without it
-    const int rcv = (pass == P_ADJ || pass == P_BORN) && gr.rc_valid ? 1 : 0;
+    const int rcv = (pass == P_ADJ || pass == P_BORN) && rc_ready(c, gr) ? 1 : 0;
     const auto key = std::make_tuple(((pass * 2 + (write_ck ? 1 : 0)) * 2 + rcv) * 2 + (c->res_on ? 1 : 0), gi,
                                      (const void*)d, c->tile);
     auto it = c->graphs.find(key);
@@ -1008,13 +1017,6 @@ lsrtm_status tile_ready(lsrtm_ctx* c) {
     return autotune(c, 4, false, nullptr);
 }
 
-// The two schedules keep the replay cache in layouts of their own.
-void set_resident(lsrtm_ctx* c, bool on) {
-    if (c->res_on == on) return;
-    for (auto& gr : c->groups) gr.rc_valid = false;
-    c->res_on = on;
-}
-
 // Runs the passes of one call (body) on the resident kernels where the plan
 // allows it, and again on the streaming kernels if a launch gave up waiting
 // for room on the GPU.  Such a call has waited half a second for nothing, so
@@ -1023,21 +1025,27 @@ void set_resident(lsrtm_ctx* c, bool on) {
 constexpr int RES_PAUSE = 10;
 
 template <typename F>
-lsrtm_status run_passes(lsrtm_ctx* c, F body) {
+lsrtm_status run_passes(lsrtm_ctx* c, int pass, F body) {
+    const auto run = [&](bool resident) -> lsrtm_status {
+        c->res_on = resident;
+        // the two schedules keep the replay cache in layouts of their own, and
+        // the migrations fill it
+        if (pass == PASS_MIGRATION && c->rc_res != resident) {
+            for (auto& gr : c->groups) gr.rc_valid = false;
+            c->rc_res = resident;
+        }
+        if (!resident) CHK(tile_ready(c));
+        return body();
+    };
     const auto now = std::chrono::steady_clock::now();
     const bool paused = c->res_pause > 0 && now - c->res_since < std::chrono::seconds(c->res_pause);
     c->res_last = false;
-    if (!c->res_ok || !c->opt_res || paused) {
-        set_resident(c, false);
-        CHK(tile_ready(c));
-        return body();
-    }
+    if (!c->res_ok || !c->opt_res || !c->res_pass[pass] || paused) return run(false);
     const size_t samples = c->evused;
     {
         ResRoom room(c->res_dev, c->res_most, c->res_cus);
-        set_resident(c, true);
         HIPCHK(c, launch_fill(reinterpret_cast<float*>(c->res_ctl), 1, c->opt_res == 2 ? 1.f : 0.f, c->st));
-        const lsrtm_status s = body();
+        const lsrtm_status s = run(true);
         int gave_up = 0;
         HIPCHK(c, hipMemcpyAsync(&gave_up, c->res_ctl, sizeof(int), hipMemcpyDeviceToHost, c->st));
         HIPCHK(c, hipStreamSynchronize(c->st));
@@ -1052,9 +1060,7 @@ lsrtm_status run_passes(lsrtm_ctx* c, F body) {
     c->res_since = std::chrono::steady_clock::now();
     c->evused = samples;           // those of the launches that gave up
     background_changed(c);
-    set_resident(c, false);
-    CHK(tile_ready(c));
-    return body();
+    return run(false);
 }
 
 lsrtm_status check_ready(lsrtm_ctx* c) {
@@ -1253,6 +1259,67 @@ bool res_pick(const lsrtm_ctx* c, const std::vector<int>& sizes, int bz, int ncu
         }
     }
     return true;
+}
+
+// A plan's groups and checkpoint interval.
+struct Sizing {
+    std::vector<int> sizes;        // shots of every launch group, at most G
+    int G = 1, k = 1;
+    long long need = 0;
+    bool ckg = false, fits = false;
+};
+
+// Estimated microseconds of a call of one kind on the streaming kernels: two
+// launches per step, whose time goes from the launches' own (a forward step
+// 5.6 us) to that of the nodes' traffic (8.4 us per million padded nodes), and the
+// checkpoints.
+double streaming_us(const lsrtm_ctx* c, int pass, const Sizing& z) {
+    static const double call[3] = {104, 81, 92}, launch[3] = {5.6, 6.4, 14.4}, start[3] = {6.7, 5.5, 12.3},
+                        node[3] = {8.4, 15.2, 26.5}, end[3] = {8.0, 0.0, 2.2}, end_node[3] = {9.3, 0.0, 2.9};
+    const int nt = c->g.nt, ends = pass == PASS_BORN || (pass == PASS_FORWARD && z.ckg) ? 0 : (nt - 1) / z.k;
+    double t = call[pass];
+    int s = 0;
+    for (int gs : z.sizes) {
+        double m = 0.0;
+        for (int e = 0; e < gs; ++e, ++s) m += 1e-6 * c->wins[c->shots[s].win].npts;
+        t += nt * std::pow(std::pow(launch[pass], 4) + std::pow(start[pass] + node[pass] * m, 4), 0.25) +
+             ends * (end[pass] + end_node[pass] * m);
+    }
+    return t;
+}
+
+// The same on the resident kernels: a step of every launch, one after the other,
+// the ends of the launches, which load and store the nodes of a thread, and the
+// checkpoints.
+//
+// The two decide which kernels a kind of call takes.  Many shallow shots are
+// faster on the streaming kernels: a lane owns two rows at least, so 28 padded
+// rows use 14 of 64 lanes, and a step of a launch costs 3 us however few nodes it
+// has; so are very short marches.  Calls of 100 steps, streaming and resident: 256
+// shots of 8 x 737 rows and columns 6.0 and 15.9 ms (forward), 8.1 and 14.2 (Born), 14.9 and 39.1
+// (migration), 64 of 28 x 260 1.42 and 2.05, 1.49 and 1.74, 3.01 and 4.39; 64 of 64 x
+// 280 1.95 and 1.90 (forward); 64 of 140 x 280 3.7 and 2.6; one of 140 x 280 1.02 and
+// 0.48, of 12 steps 0.191 and 0.197.  The constants are a fit to 471 such calls (1
+// to 256 shots, 8 to 384 rows, 60 to 777 columns, 12 and 100 steps).  The line lies at
+// 0.95 of the streaming kernels' estimate: none of the 471 then takes the resident
+// ones and loses by it, ten that would have gained 2 to 15 % do not take them.
+double resident_us(const lsrtm_ctx* c, int pass, const Sizing& z, int bz, const ResPicks& picks) {
+    static const double call[3] = {137, 97, 131}, node[3] = {1.9, 6.35, 1.95}, step[3] = {0.77, 0.87, 0.85},
+                        end[3] = {8.7, 0.0, 0.5}, end_node[3] = {29.0, 0.0, 52.0};
+    const int nt = c->g.nt, ends = pass == PASS_BORN || (pass == PASS_FORWARD && z.ckg) ? 0 : (nt - 1) / z.k;
+    double t = call[pass];
+    int s = 0;
+    for (size_t g = 0; g < z.sizes.size(); ++g) {
+        double m = 0.0;
+        for (int e = 0; e < z.sizes[g]; ++e, ++s) m += 1e-6 * c->wins[c->shots[s].win].npts;
+        t += ends * (end[pass] + end_node[pass] * m);
+        for (int kind = 0; kind < R_KINDS; ++kind) {
+            if (pass != (kind == R_BG ? PASS_FORWARD : kind == R_BORN ? PASS_BORN : kind == R_BORN_RC ? -1 : PASS_MIGRATION)) continue;
+            for (const ResPick& P : picks[g][kind])
+                t += (ends + 1) * node[pass] * bz * P.cx + nt * step[pass] * res_step_us(kind, bz * P.cx);
+        }
+    }
+    return t;
 }
 
 // Tables of the picked launches.
@@ -1515,12 +1582,6 @@ lsrtm_status plan(lsrtm_ctx* c) {
     };
     // The resident kernels store a column's replay rows in whole waves.
     const auto seg_of = [&](const Window& W, bool res) { return res ? res_segn(W.npts, W.N[1], bz) : W.npts; };
-    struct Sizing {
-        std::vector<int> sizes;    // shots of every launch group, at most G
-        int G = 1, k = 1;
-        long long need = 0;
-        bool ckg = false, fits = false;
-    };
     const auto size_plan = [&](bool res) {
         Sizing z;
         // points of the largest group and of all shots, and their replay buffers'
@@ -1616,7 +1677,8 @@ lsrtm_status plan(lsrtm_ctx* c) {
     };
     // What fits is decided without the resident kernels' larger replay buffer
     // (1.1 times at 280 padded rows, 2 to 4 times below 65): they are taken where
-    // that buffer fits the budget too, with the same checkpoint layout.
+    // that buffer fits the budget too, with the same checkpoint layout, for the
+    // kinds of calls that are estimated to be faster on them.
     Sizing z = size_plan(false);
     if (!z.fits)
         FAIL(c, LSRTM_ENOMEM, "memory plan needs %.2f GB, budget %.2f GB", z.need / 1e9, budget / 1e9);
@@ -1639,8 +1701,11 @@ lsrtm_status plan(lsrtm_ctx* c) {
             r = size_plan(true);
         }
         if (r.fits && r.ckg == z.ckg && res_pick(c, r.sizes, bz, c->res_cus, cuts, picks)) {
-            c->res_bz = bz;
-            z = r;
+            for (int pass : {PASS_FORWARD, PASS_BORN, PASS_MIGRATION}) {
+                c->res_pass[pass] = c->opt_res == 3 || resident_us(c, pass, r, bz, picks) <= 0.95 * streaming_us(c, pass, z);
+                if (c->res_pass[pass]) c->res_bz = bz;
+            }
+            if (c->res_bz) z = r;
         }
     }
     for (auto& W : c->wins) W.segn = seg_of(W, c->res_bz > 0);
@@ -2218,16 +2283,15 @@ lsrtm_status lsrtm_set_option(lsrtm_ctx* c, int key, long long v) {
         return LSRTM_OK;
     }
     case LSRTM_OPT_GRAPH: c->opt_graph = v != 0; return LSRTM_OK;
-    case LSRTM_OPT_RESIDENT:
+    case LSRTM_OPT_RESIDENT: {
+        const int was = c->opt_res;
+        c->opt_res = v == 0 ? 0 : v == 2 || v == 3 ? (int)v : 1;
         c->res_pause = 0;
-        if ((c->opt_res != 0) == (v != 0)) {
-            c->opt_res = v == 0 ? 0 : v == 2 ? 2 : 1;
-            return LSRTM_OK;
-        }
-        c->opt_res = v == 0 ? 0 : v == 2 ? 2 : 1;
         // the replay buffer's layout
-        if (c->have_acq && c->ndim == 2 && (v != 0 || c->res_bz)) return plan(c);
+        const bool other = (was != 0) != (v != 0) || (was == 3) != (v == 3);
+        if (c->have_acq && c->ndim == 2 && other && (v != 0 || c->res_bz)) return plan(c);
         return LSRTM_OK;
+    }
     case LSRTM_OPT_TIMING: c->opt_timing = v != 0; return LSRTM_OK;
     case LSRTM_OPT_MEM_BUDGET_MB:
         if (v < 0 || v > kMaxMB) FAIL(c, LSRTM_EINVAL, "memory budget must be in [0, %lld] MB", kMaxMB);
@@ -2385,7 +2449,7 @@ lsrtm_status lsrtm_stats(lsrtm_ctx* c, double* out, int nout) {
 lsrtm_status lsrtm_forward(lsrtm_ctx* c, float* d) {
     CHK(check_ready(c));
     if (!d && c->data_len > 0) FAIL(c, LSRTM_EINVAL, "d is NULL");
-    return run_passes(c, [&]() -> lsrtm_status {
+    return run_passes(c, PASS_FORWARD, [&]() -> lsrtm_status {
         CHK(pass_begin(c));
         for (size_t gi = 0; gi < c->groups.size(); ++gi)
             CHK(run_group(c, c->groups[gi], (int)gi, P_FWD, d, !c->ck_group));
@@ -2415,7 +2479,7 @@ static lsrtm_status born_impl(lsrtm_ctx* c, const float* dm, float* d) {
         a.dlnk = W.dlnk;
         HIPCHK(c, launch_dm_prep(a, c->st));
     }
-    return run_passes(c, [&]() -> lsrtm_status {
+    return run_passes(c, PASS_BORN, [&]() -> lsrtm_status {
         const bool write_ck = !c->ckpt_valid && !c->ck_group;
         for (size_t gi = 0; gi < c->groups.size(); ++gi) CHK(run_group(c, c->groups[gi], (int)gi, P_BORN, d, write_ck));
         if (write_ck) {
@@ -2436,7 +2500,7 @@ lsrtm_status lsrtm_born(lsrtm_ctx* c, const float* dm, float* d) {
 }
 
 static lsrtm_status adjoint_impl(lsrtm_ctx* c, const float* d, float* img, int accumulate) {
-    CHK(run_passes(c, [&]() -> lsrtm_status {
+    CHK(run_passes(c, PASS_MIGRATION, [&]() -> lsrtm_status {
         if (!c->ck_group) CHK(ensure_ckpts(c));
         HIPCHK(c, launch_fill_f64(c->acc64, 2 * c->gpts, c->st));
         for (size_t gi = 0; gi < c->groups.size(); ++gi) {

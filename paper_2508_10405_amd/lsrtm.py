@@ -261,7 +261,7 @@ class Context:
         return self.sizes()["data_len"]
 
     def resident(self):
-        """Resident 2D time stepping (lsrtm_resident): whether the plan's calls
+        """Resident 2D time stepping (lsrtm_resident): whether calls of the plan
         take it, whether the last one ran on it, and the calls so far that
         found no room for it on the GPU."""
         out = (_c_ll * 3)()

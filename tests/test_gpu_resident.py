@@ -142,7 +142,7 @@ def test_not_finite_values_stay_in_their_cone(nz, nx, npml, nshot, bad):
     w.rec[0][0] = at
     w.src[0] = at
     got = []
-    for resident in (0, 1):
+    for resident in (0, 3):
         ctx = lsrtm.context_for(w, tile=1, ckpt_every=nt)
         ctx.set_option(lsrtm.OPT_RESIDENT, resident)
         dm = to_dev(torch, w.dm)
@@ -155,6 +155,7 @@ def test_not_finite_values_stay_in_their_cone(nz, nx, npml, nshot, bad):
         wav[0, 3] = bad
         ctx.set_acquisition(w.win, w.src, w.rec, wav)
         out.append(ctx.forward())
+        assert ctx.resident()["last"] == (resident > 0)
         got.append(out)
         ctx.close()
     for i, (a, b) in enumerate(zip(*got)):
@@ -210,12 +211,17 @@ def test_small_contexts_side_by_side():
 
 @pytest.mark.parametrize("nz,nx,npml,nshot,nt,k,opts", CASES)
 def test_calls_run_resident(nz, nx, npml, nshot, nt, k, opts):
-    """The calls compared above do run on the resident kernels, first and
-    later ones, without one that gives up."""
+    """Wherever the windows fit (3), first and later calls do run on the
+    resident kernels, without one that gives up, and give the streaming ones'
+    bits."""
     torch = require_gpu()
     w = synth.small((nz - 2 * npml, nx - 2 * npml), nt=nt, npml=npml, seed=nz + nx, nshot=nshot, uneven=nshot > 2)
+    a = _run(torch, w, 0, ckpt_every=k, **opts)
+    b = _run(torch, w, 3, ckpt_every=k, **opts)
+    for i, (x, y) in enumerate(zip(a, b)):
+        assert torch.equal(x, y), (i, float((x - y).abs().max()))
     ctx = lsrtm.context_for(w, tile=1, ckpt_every=k, **opts)
-    ctx.set_option(lsrtm.OPT_RESIDENT, 1)
+    ctx.set_option(lsrtm.OPT_RESIDENT, 3)
     dm = to_dev(torch, w.dm)
     on = {"planned": True, "last": True, "gave_up": 0}
     for _ in range(2):
@@ -320,7 +326,7 @@ def test_budgets_that_held_the_plan_still_do(opts):
     ref = None
     for budget in list(range(66, 100, 2)) + list(range(100, 460, 20)):
         plans = []
-        for resident in (0, 1):
+        for resident in (0, 3):
             try:
                 ctx = _context(torch, w, resident, mem_budget_mb=budget, **opts)
             except lsrtm.LsrtmError as e:
@@ -351,7 +357,7 @@ def test_plans_without_the_resident_layout():
     torch = require_gpu()
     k = 10
     w = synth.small((20, 765), nt=40, npml=6, seed=32, nshot=16, nrec=40)
-    off, on = _context(torch, w, 0, ckpt_every=k, shots_per_launch=9), _context(torch, w, 1, ckpt_every=k, shots_per_launch=9)
+    off, on = (_context(torch, w, r, ckpt_every=k, shots_per_launch=9) for r in (0, 3))
     assert off.sizes()["shots_per_launch"] == 8 and on.sizes()["shots_per_launch"] == 9
     padded, plain = 777 * 2 * 64, 777 * 32
     grp = lambda n: n * (plain * (7 + 7 + 2) * 4)
@@ -359,7 +365,7 @@ def test_plans_without_the_resident_layout():
     sizes = on.sizes()
     on.set_option(lsrtm.OPT_RESIDENT, 0)
     assert on.sizes() == off.sizes() and not on.resident()["planned"]
-    on.set_option(lsrtm.OPT_RESIDENT, 1)
+    on.set_option(lsrtm.OPT_RESIDENT, 3)
     assert on.sizes() == sizes and on.resident()["planned"]
     for ctx in (off, on):
         ctx.close()
@@ -367,7 +373,7 @@ def test_plans_without_the_resident_layout():
     many.rec[0] = np.stack([np.random.default_rng(1).integers(0, 20, 12000), np.full(12000, 30)], axis=1)
     for dup, fits in ((many.rec[0], False), (many.rec[0][:4000], True)):
         many.rec[0] = dup
-        ctx, ref = (_context(torch, many, r, ckpt_every=7) for r in (1, 0))
+        ctx, ref = (_context(torch, many, r, ckpt_every=7) for r in (3, 0))
         assert ctx.resident()["planned"] == fits
         if not fits:
             assert ctx.sizes()["plan_bytes"] == ref.sizes()["plan_bytes"]
@@ -377,3 +383,41 @@ def test_plans_without_the_resident_layout():
         assert ctx.resident()["last"] == fits
         ctx.close()
         ref.close()
+
+
+# (padded nz, padded nx, npml, shots, steps), whether forward, Born, migration take the resident kernels
+ROUTES = [
+    ((8, 240, 0, 256, 100), (False, False, False)),      # 4 of 64 lanes, 256 shots
+    ((28, 757, 10, 64, 100), (False, False, False)),
+    ((40, 260, 10, 256, 100), (False, True, False)),
+    ((64, 280, 20, 64, 12), (False, False, False)),      # a short march
+    ((28, 260, 10, 4, 100), (True, True, True)),         # few shots
+    ((140, 240, 20, 1, 1000), (True, True, True)),
+    ((280, 777, 20, 14, 100), (True, True, True)),
+]
+
+
+@pytest.mark.parametrize("shape,expect", ROUTES)
+@pytest.mark.parametrize("opts", [{}, {"replay_cache_mb": 4000}])
+def test_route_by_estimate(shape, expect, opts):
+    """Which kernels a kind of call takes by itself, and that calls of a plan
+    on mixed routes share checkpoints and cached replays rightly."""
+    torch = require_gpu()
+    nz, nx, npml, nshot, nt = shape
+    w = synth.small((nz - 2 * npml, nx - 2 * npml), nt=nt, npml=npml, seed=nz, nshot=nshot, nrec=30)
+    dm = to_dev(torch, w.dm)
+    got = []
+    for resident in (1, 0):
+        ctx = _context(torch, w, None if resident else 0, mem_budget_mb=30000, **opts)
+        out, route = [], []
+        for call in (ctx.forward, lambda: ctx.born(dm), lambda: ctx.adjoint(out[1]), lambda: ctx.born(dm),
+                     lambda: ctx.adjoint(out[1]), ctx.forward):
+            out.append(call())
+            route.append(ctx.resident()["last"])
+        assert tuple(route) == ((*expect, *expect[1:], expect[0]) if resident else (False,) * 6)
+        assert ctx.resident()["planned"] == (bool(resident) and any(expect))
+        x, mis = ctx.cgnr(out[1], 1)
+        got.append(out + [x, torch.tensor(mis)])
+        ctx.close()
+    for i, (a, b) in enumerate(zip(*got)):
+        assert torch.equal(a, b), i
