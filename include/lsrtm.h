@@ -378,11 +378,15 @@ lsrtm_status lsrtm_set_option(lsrtm_ctx* ctx, int key, long long value);
  * over nsteps time steps on the actual launch groups for every tile shape,
  * and with tune_groups = 1 also for several shot-per-launch sizes and (2D)
  * both step schedules (rebuilding the memory plan), then keeps the fastest.
+ * A plan whose Born passes and migrations take the resident kernels
+ * (LSRTM_OPT_RESIDENT) is ranked by theirs, over one checkpoint segment; its
+ * tile serves the pseudo-Hessian pass and calls that find no room for them.
  * For two-phase steps it then tries every other shape for the velocity
  * phases and for the adjoint A phase (LSRTM_OPT_TILE_V / _TILE_ADJ_A, set to
  * the picks or -1).  out (HOST double[5], may be NULL) = (tile id, shots per
  * launch, ms per time step, velocity-phase tile, adjoint-A tile).  With
- * LSRTM_TUNE_CACHE naming a file, results are read from and appended to it.
+ * LSRTM_TUNE_CACHE naming a file, results are read from and appended to it
+ * (2D lines with LSRTM_OPT_RESIDENT on are told apart from those without).
  * Invalidates stored checkpoints.  When no tile is set, the same tile tuning
  * (without group sizes and schedules) runs on the first pass by itself,
  * unless the passes take the resident kernels (LSRTM_OPT_RESIDENT), which

@@ -306,7 +306,7 @@ def test_streaming_passes_of_resident_plans_are_tuned(tmp_path, monkeypatch):
 def _context(torch, w, resident, **opts):
     """Planned with the option set (or None for the default)."""
     ctx = lsrtm.Context(tuple(reversed(w.lnvp.shape)), w.h, w.nt, w.dt, npml=w.npml, pml_R=w.pml_R, pml_f0=w.pml_freq,
-                        tile=1, **opts)
+                        **opts)
     if resident is not None:
         ctx.set_option(lsrtm.OPT_RESIDENT, resident)
     ctx.set_model(to_dev(torch, w.lnvp), to_dev(torch, w.lnip))
@@ -421,3 +421,33 @@ def test_route_by_estimate(shape, expect, opts):
         ctx.close()
     for i, (a, b) in enumerate(zip(*got)):
         assert torch.equal(a, b), i
+
+
+def test_autotune_times_the_kernels_of_the_passes(tmp_path, monkeypatch):
+    """One small shot, whose fused steps are one launch and two-phase streaming
+    steps two: the tuner compares the fused steps with the resident ones that
+    its passes take, and a tuning file of the streaming kernels is not theirs."""
+    torch = require_gpu()
+    w = synth.small((100, 200), nt=200, npml=20, seed=8, nshot=1)
+    dm = to_dev(torch, w.dm)
+    ms = []
+    for resident in (0, 1):
+        file = tmp_path / f"tune{resident}.txt"
+        monkeypatch.setenv("LSRTM_TUNE_CACHE", str(file))
+        ctx = _context(torch, w, resident)
+        pts = ctx.sizes()["padded_points"]
+        if resident:
+            file.write_text(f"nd=2 nshot=1 pts={pts} nt=200 n=100x200x1 npml=20|1 0 1 -1 -1\n")
+        res = ctx.autotune(nsteps=8, groups=True)
+        ms.append(res["ms_per_step"])
+        if resident:
+            assert ctx.sizes()["fused"] == 0
+            assert ctx.resident()["planned"]
+            d = ctx.born(dm)
+            assert ctx.resident()["last"]
+        else:
+            d_ref = ctx.born(dm)
+        print("autotune", resident, res, ctx.sizes()["fused"], flush=True)
+        ctx.close()
+    assert 0.0 < ms[1] < ms[0]
+    assert torch.equal(d, d_ref)
