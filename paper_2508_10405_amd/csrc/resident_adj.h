@@ -357,7 +357,7 @@ __device__ __forceinline__ void adj_body(const ResArgs& a, const ResBlock& B, fl
 template <int BZ, int CX>
 __global__ void __attribute__((amdgpu_flat_work_group_size(RES_NT, RES_NT), amdgpu_waves_per_eu(2, 2)))
 k2r_adj(ResArgs a) {
-    extern __shared__ float lds[];
+    extern __shared__ __align__(16) float lds[];
     __shared__ int flag;
     if (!res_admit(a, &flag)) return;
     const ResBlock B = a.blocks[xcd_remap(blockIdx.x, gridDim.x)];

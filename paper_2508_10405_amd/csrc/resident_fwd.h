@@ -368,7 +368,7 @@ __device__ __forceinline__ void fwd_body(const ResArgs& a, const ResBlock& B, fl
 template <int BZ, int CX, int KIND>
 __global__ void __attribute__((amdgpu_flat_work_group_size(RES_NT, RES_NT), amdgpu_waves_per_eu(2, 2)))
 k2r_fwd(ResArgs a) {
-    extern __shared__ float lds[];
+    extern __shared__ __align__(16) float lds[];
     __shared__ int flag;
     if (!res_admit(a, &flag)) return;
     const ResBlock B = a.blocks[xcd_remap(blockIdx.x, gridDim.x)];
