@@ -423,14 +423,17 @@ k_w_block(WArgs a, double eps_rel, const float* __restrict__ ref, const float* _
             for (int k2 = 0; k2 < T; ++k2) x[(t + T * i) + 8 * k2] = to32(v[i * T + k2]);
     }
     __syncthreads();
-    // the filter, as in k_w_filter; a half spectrum has every magnitude
+    // the filter, as in k_w_filter; a half spectrum has every magnitude.  A NaN in
+    // the block leaves no number in the spectra of these sizes there, and the
+    // estimate is zero; here two columns share a transform, which leaves a few, so
+    // it is looked for
     float mx = 0.f;
     for (int u = threadIdx.x; u < H * B; u += NT) {
         const float2 b = spec[1][u / B][u % B];
-        mx = fmaxf(mx, fmaxf(fabsf(b.x), fabsf(b.y)));
+        mx = fmaxf(mx, b.x != b.x || b.y != b.y ? INFINITY : fmaxf(fabsf(b.x), fabsf(b.y)));
     }
     const float beta = group_max<NT>(mx, red);
-    if (!(beta > 0.f)) {
+    if (!(beta > 0.f && beta < INFINITY)) {
         for (int u = threadIdx.x; u < B * B; u += NT) est[u] = 0.f;
         return;
     }

@@ -147,3 +147,30 @@ def test_wiener_under_capture(torch, block):
             assert torch.equal(got, ctx.wiener(ref, blur, block=block))
         st.synchronize()
     ctx.close()
+
+
+@pytest.mark.parametrize("block", [16, 32, 64])
+def test_wiener_nan_in_the_blurred_image(torch, block):
+    """A NaN in m_blur takes the blocks that hold it out of the result (their
+    estimates are zero) and touches nothing else."""
+    from paper_2508_10405_amd import lsrtm
+    n = (171, 137)
+    g = torch.Generator(device="cuda").manual_seed(block)
+    ctx = lsrtm.Context(n, (10.0, 10.0), 10, 1e-3)
+    ref, blur, x = (torch.randn((137, 171), generator=g, device="cuda") for _ in range(3))
+    clean = ctx.wiener(ref, blur, x, block=block)
+    h = block // 2
+    for at in ((0, 0), (70, 85), (136, 30), (64, 64), (h, 2 * h)):
+        bad = blur.clone()
+        # the largest magnitude scales the image: not that one
+        assert float(bad[at].abs()) < float(bad.abs().max())
+        bad[at] = float("nan")
+        out = ctx.wiener(ref, bad, x, block=block)
+        assert bool(torch.isfinite(out).all()), at
+        # blocks start at (k - 1) h: those with the NaN are k = c / h and c / h + 1 per axis
+        near = torch.zeros_like(out, dtype=torch.bool)
+        kx, kz = at[0] // h, at[1] // h
+        near[max(0, (kx - 1) * h):(kx + 2) * h, max(0, (kz - 1) * h):(kz + 2) * h] = True
+        assert torch.equal(out[~near], clean[~near]), at
+        assert not bool(out[kx * h:(kx + 1) * h, kz * h:(kz + 1) * h].any()), at
+    ctx.close()
