@@ -1,4 +1,4 @@
-// Device code shared by the resident 2D kernels (kern2r_fwd.hip, kern2r_adj.hip).
+// Device code shared by the resident 2D kernels (resident_fwd.h, resident_adj.h).
 //
 // Layout of a slab: wave w of a workgroup owns columns w CX .. w CX + CX - 1
 // of its slab; lane l owns rows l BZ .. l BZ + BZ - 1 of each, so a wave spans
@@ -165,7 +165,9 @@ struct Place {
         return *reinterpret_cast<G*>(reinterpret_cast<Byte<G>*>(f + ((long long)(x + c) * ldz + k)) + (unsigned)(lane * (4 * BZ)));
     }
     // Replay buffer of a step: [column][row k][lane], so that a wave's accesses
-    // are whole lines and lie a constant apart (lanes past the grid hold zeros).
+    // are whole lines and lie a constant apart.  Rows past the grid hold whatever
+    // the differences make of the rows above them; their readers have zeros there
+    // to multiply them by (Q, U_a, dt b_a), and store none of their own.
     template <typename G>
     __device__ __forceinline__ G& seg(G* f, int c, int k) const {
         return *reinterpret_cast<G*>(reinterpret_cast<Byte<G>*>(f + (long long)x * ROW) + (unsigned)(lane * 4) + (c * BZ + k) * 256);
@@ -174,7 +176,7 @@ struct Place {
         if (XP && !col(c)) return 0.f;
         return __builtin_nontemporal_load(&seg(f, c, k));
     }
-    // whole lines, the zeros past the grid included: stores of the 224 bytes of
+    // whole lines, the rows past the grid included: stores of the 224 bytes of
     // 56 lanes ran at two thirds of the rate
     __device__ __forceinline__ void seg_store(gfloat* f, int c, int k, float v) const {
         if (col(c)) __builtin_nontemporal_store(v, &seg(f, c, k));
