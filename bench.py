@@ -70,6 +70,12 @@ KERNEL_SYMBOL = {"born_v": "k2_v<*, true, false>", "born_p": "k2_p<*, true, fals
 # axis whose strip it lies in (two memories read and written).
 STEP_BYTES = {2: {"born": 68, "replay": 48, "adjoint": 64}, 3: {"born": 88, "replay": 64, "adjoint": 80},
               "2r": {"born": 0, "replay": 12, "adjoint": 12}}
+# resident 2D steps move next to nothing: they are priced at the floating-point
+# operations per padded node of the derivatives (11 each), the field updates and
+# the images, against the rate of FP32 multiply-adds without packed instructions
+# (256 CUs x 64 lanes x 2 x 2.4 GHz)
+STEP_FLOPS = {"born": 112, "replay": 56, "adjoint": 66}
+FP32_PEAK_TFLOPS = 78.6
 STEP_KERNELS = {"born": ("born_v", "born_p"), "replay": ("bg_v", "bg_p"), "adjoint": ("adj_a", "adj_b")}
 STRIP_BYTES = 16
 
@@ -429,7 +435,7 @@ def main():
             continue
         t = kms[k] / kcnt[k] * 1e-3
         tr = read_traffic(ptag, k, pts_per_launch, nd) if k in btab and not resident else None
-        gbs = btab[k] * pts_per_launch / t / 1e9 if k in btab else None
+        gbs = btab[k] * pts_per_launch / t / 1e9 if btab.get(k) else None
         kernels[k] = {"avg_ms": t * 1e3, "launches_timed": kcnt[k], "GBs": gbs,
                       "frac": gbs / HBM_PEAK_GBS if gbs else None,
                       "counter_GBs": tr / t / 1e9 if tr else None,
@@ -446,6 +452,10 @@ def main():
         steps[name] = {"kernels": list(ks), "step_ms": t * 1e3, "bytes_per_launch": byt,
                        "GBs": byt / t / 1e9, "frac": byt / t / 1e9 / HBM_PEAK_GBS,
                        "traffic": sum(trs) if all(trs) else None}
+        if resident:
+            tf = STEP_FLOPS[name] * pts_per_launch / t / 1e12
+            steps[name].update(GBs=byt / t / 1e9 if byt else None, hbm_frac=byt / t / 1e9 / HBM_PEAK_GBS if byt else None,
+                               flops_per_launch=STEP_FLOPS[name] * pts_per_launch, TFLOPs=tf, frac=tf / FP32_PEAK_TFLOPS)
     # the dominant step by the event time the sampled iteration spent in it
     dom = max(steps, key=lambda n: sum(kms[k] for k in steps[n]["kernels"])) if steps else None
     ds = steps.get(dom, {})
@@ -629,11 +639,17 @@ def main():
                    "ckpt_per_group": bool(sz["ckpt_per_group"]),
                    "schedule": "fused step" if sz["fused"] else "resident steps" if resident else "two-phase step",
                    "parallelism": "shots batched on 1 GPU"},
-        "roofline": {"bound": "issue and exchange latency" if resident else "hbm", "kernel": f"{dom} step ({' + '.join(ds['kernels'])})" if ds else None,
-                     "achieved": ds.get("GBs"), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+        "roofline": {"bound": "fp32" if resident else "hbm",
+                     "kernel": f"{dom} step ({' + '.join(ds['kernels'])})" if ds else None,
+                     "achieved": ds.get("TFLOPs" if resident else "GBs"),
+                     "peak": FP32_PEAK_TFLOPS if resident else HBM_PEAK_GBS,
+                     "unit": "TFLOP/s" if resident else "GB/s",
                      "frac": ds.get("frac"), "traffic": ds.get("traffic"),
                      "bytes_per_launch": ds.get("bytes_per_launch"), "avg_launch_ms": ds.get("step_ms"),
-                     "accounting": "minimum bytes of one time step per padded node plus 16 B per node and "
+                     "accounting": "floating-point operations of one time step's derivatives, updates and images "
+                                   "per padded node, times the nodes of one launch group, over the average duration "
+                                   "of the step; bytes_per_launch is the replay buffer's" if resident else
+                                   "minimum bytes of one time step per padded node plus 16 B per node and "
                                    "axis in the absorbing strips, times the nodes of one launch group, over "
                                    "the summed average durations of the step's kernels",
                      "dominant_kernel": {"kernel": dk, "GBs": kernels[dk]["GBs"], "frac": kernels[dk]["frac"],
