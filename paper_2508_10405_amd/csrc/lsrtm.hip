@@ -191,7 +191,6 @@ struct lsrtm_ctx {
     size_t psf_npieces = 0;
     float* psf_pack = nullptr;
     long long psf_npack = 0;
-    int* psf_bad = nullptr;
     float* psf_dm = nullptr;       // [2][gpts] scatterer model
     float* psf_d = nullptr;        // data of the scatterer model
     float* psf_v[4] = {nullptr, nullptr, nullptr, nullptr};   // image-domain CG: r, z, p, w
@@ -2784,6 +2783,7 @@ static lsrtm_status psf2_setup(lsrtm_ctx* c, const PsfArgs& pa, int s) {
     if (2 * std::max(a.lds_t + 4096, 3 * a.lds_f) > 150 * 1024) return LSRTM_OK;
     std::vector<int4> all;
     for (auto* v : {&t[0], &t[1], &f[0], &f[1]}) all.insert(all.end(), v->begin(), v->end());
+    all.push_back(make_int4(0, 0, 0, 0));        // the packings' note: none yet
     const long long npack = (long long)a.K[0] * a.K[1] * (2 * W + 1) * (2 * W + 1) * 4;
     for (void** p : {(void**)&c->psf_pieces, (void**)&c->psf_pack}) {
         const bool big = p == (void**)&c->psf_pack ? npack > c->psf_npack : all.size() > c->psf_npieces;
@@ -2804,17 +2804,13 @@ static lsrtm_status psf2_setup(lsrtm_ctx* c, const PsfArgs& pa, int s) {
             c->psf_npieces = all.size();
         }
     }
-    if (!c->psf_bad) {
-        if (dalloc_t(c, &c->psf_bad, 1, false) != LSRTM_OK) return LSRTM_OK;
-        HIPCHK(c, launch_fill(reinterpret_cast<float*>(c->psf_bad), 1, 0.f, c->st));
-    }
-    a.bad = c->psf_bad;
     HIPCHK(c, hipMemcpy(c->psf_pieces, all.data(), all.size() * sizeof(int4), hipMemcpyHostToDevice));
     a.pack = c->psf_pack;
     a.tz = c->psf_pieces;
     a.tx = a.tz + t[0].size();
     a.fz = a.tx + t[1].size();
     a.fx = a.fz + f[0].size();
+    a.bad = reinterpret_cast<int*>(c->psf_pieces + all.size() - 1);
     a.ntz = (int)t[0].size();
     a.ntx = (int)t[1].size();
     a.nfz = (int)f[0].size();
@@ -2896,7 +2892,7 @@ static lsrtm_status psf2_pack(lsrtm_ctx* c, const PsfArgs& a) {
     c->psf2.mono = a.mono;
     c->psf2.psf = a.psf;
     if (c->psf2.packing++ == INT_MAX) {
-        HIPCHK(c, launch_fill(reinterpret_cast<float*>(c->psf_bad), 1, 0.f, c->st));
+        HIPCHK(c, launch_fill(reinterpret_cast<float*>(c->psf2.bad), 1, 0.f, c->st));
         c->psf2.packing = 1;
     }
     HIPCHK(c, launch_psf_pack(c->psf2, c->st));
