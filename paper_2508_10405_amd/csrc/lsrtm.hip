@@ -791,7 +791,7 @@ lsrtm_status group_forward(lsrtm_ctx* c, Group& gr, int mode, float* d, bool wri
     // the background from there instead of advancing it (nothing after them
     // needs the background state)
     const int jc = c->nseg - c->rc_m;
-    const bool use_rc = mode == 1 && !write_ck && c->rc_m > 0 && gr.rc_valid && c->ndim == 2 && !fz;
+    const bool use_rc = mode == 1 && !write_ck && rc_ready(c, gr) && c->ndim == 2 && !fz;
     for (int n = 0; n < c->g.nt; ++n) {
         tstep(c, n);
         const int j = n / c->k;

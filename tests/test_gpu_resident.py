@@ -451,3 +451,45 @@ def test_autotune_times_the_kernels_of_the_passes(tmp_path, monkeypatch):
         ctx.close()
     assert 0.0 < ms[1] < ms[0]
     assert torch.equal(d, d_ref)
+
+
+def test_born_passes_keep_off_the_other_layout():
+    """A Born pass on the streaming kernels while the replay cache holds the
+    resident kernels' layout (its launch found no room) does not read it."""
+    torch = require_gpu()
+    w = synth.small((100, 120), nt=40, npml=10, seed=12, nshot=4)
+    dm = to_dev(torch, w.dm)
+    ctx = _context(torch, w, 1, ckpt_every=9, replay_cache_mb=2000)
+    d = ctx.born(dm)
+    img = ctx.adjoint(d)
+    assert ctx.resident()["last"] and ctx.sizes()["replay_cache_segments"] > 0
+    assert torch.equal(ctx.born(dm), d)
+    ctx.set_option(lsrtm.OPT_RESIDENT, 2)
+    for _ in range(2):                    # gives up, then the pause
+        assert torch.equal(ctx.born(dm), d)
+        assert not ctx.resident()["last"]
+    ctx.set_option(lsrtm.OPT_RESIDENT, 1)
+    assert torch.equal(ctx.born(dm), d) and torch.equal(ctx.adjoint(d), img)
+    ctx.close()
+
+
+def test_mixed_plans_share_no_layout():
+    """Migrations resident, Born passes streaming (32 small shots, 12 steps in
+    one segment): Born passes do without the replays that the migrations keep."""
+    torch = require_gpu()
+    w = synth.small((16, 68), nt=12, npml=6, seed=14, nshot=32, nrec=20)
+    dm = to_dev(torch, w.dm)
+    got = []
+    for resident in (None, 0):
+        ctx = _context(torch, w, resident, ckpt_every=20, replay_cache_mb=2000)
+        assert ctx.sizes()["replay_cache_segments"] == 1
+        out, route = [], []
+        for call in (lambda: ctx.born(dm), lambda: ctx.adjoint(out[0]), lambda: ctx.born(dm), lambda: ctx.adjoint(out[0]),
+                     lambda: ctx.born(dm)):
+            out.append(call())
+            route.append(ctx.resident()["last"])
+        assert route == ([False, True, False, True, False] if resident is None else [False] * 5)
+        got.append(out)
+        ctx.close()
+    for i, (a, b) in enumerate(zip(*got)):
+        assert torch.equal(a, b), i
