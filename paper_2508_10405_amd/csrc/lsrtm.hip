@@ -757,20 +757,52 @@ lsrtm_status res_forward(lsrtm_ctx* c, Group& gr, int mode, float* d, bool write
     return LSRTM_OK;
 }
 
+// Replays segment j of a group's background from its checkpoint into the replay
+// buffers of the slots sl (null: the group's own).
+lsrtm_status replay(lsrtm_ctx* c, Group& gr, int j, const Slot* sl) {
+    const bool fz = c->fused;
+    const int n0 = j * c->k, n1 = std::min(n0 + c->k, c->g.nt);
+    if (j == 0) CHK(fill(c, c->pool, gr.bg_used));
+    else CHK(ckpt(c, gr, j, false, desc(gr, fz ? n0 : 0)));
+    if (c->res_on) return res_run(c, gr, R_SEG, sl ? sl : gr.d_slots, n0, n1, 0, 0, nullptr, nullptr);
+    for (int n = n0; n < n1; ++n) {
+        tstep(c, n);
+        const Slot* cur = sl ? sl : desc(gr, fz ? n : 0);
+        CHK(stencil(c, gr, K_SEG_V, n, n - n0, 0, cur));
+        if (!fz) CHK(stencil(c, gr, K_SEG_P, n, n - n0, 0, cur));
+    }
+    return LSRTM_OK;
+}
+
+// The slots of a segment that the replay cache holds, or null.
+const Slot* rc_slots(const lsrtm_ctx* c, const Group& gr, int j) {
+    const int jc = c->nseg - c->rc_m;
+    return j >= jc ? gr.d_rc + (long long)(j - jc) * gr.ns : nullptr;
+}
+
+// Brings the replay cache into the layout of the pass under way, from the
+// checkpoints it was filled from: the same replays.
+lsrtm_status refill_cache(lsrtm_ctx* c) {
+    for (auto& gr : c->groups) {
+        if (!gr.rc_valid) continue;
+        if (c->res_on) CHK(res_begin(c));
+        else CHK(build_tiles(c, gr, c->tile));
+        for (int j = c->nseg - 1; j >= c->nseg - c->rc_m; --j) CHK(replay(c, gr, j, rc_slots(c, gr, j)));
+    }
+    c->rc_res = c->res_on;
+    return LSRTM_OK;
+}
+
 // The reverse steps of a group's migration (the caller clears the fields,
 // injects the data of the last step and reduces the images).
 lsrtm_status res_adjoint(lsrtm_ctx* c, Group& gr, const float* d) {
     CHK(res_begin(c));
-    const int nt = c->g.nt, jc = c->nseg - c->rc_m;
+    const int nt = c->g.nt;
     for (int j = c->nseg - 1; j >= 0; --j) {
         const int n0 = j * c->k, n1 = std::min(n0 + c->k, nt);
-        const Slot* sl = j >= jc ? gr.d_rc + (long long)(j - jc) * gr.ns : gr.d_slots;
-        if (j < jc || !gr.rc_valid) {
-            if (j == 0) CHK(fill(c, c->pool, gr.bg_used));
-            else CHK(ckpt(c, gr, j, false, gr.d_slots));
-            CHK(res_run(c, gr, R_SEG, sl, n0, n1, 0, 0, nullptr, nullptr));
-        }
-        CHK(res_run(c, gr, R_ADJ, sl, n0, n1, 0, n1 == nt, nullptr, c->data_len > 0 ? d : nullptr));
+        const Slot* rcd = rc_slots(c, gr, j);
+        if (!rcd || !gr.rc_valid) CHK(replay(c, gr, j, rcd));
+        CHK(res_run(c, gr, R_ADJ, rcd ? rcd : gr.d_slots, n0, n1, 0, n1 == nt, nullptr, c->data_len > 0 ? d : nullptr));
     }
     return LSRTM_OK;
 }
@@ -837,21 +869,11 @@ lsrtm_status group_adjoint(lsrtm_ctx* c, Group& gr, const float* d) {
     if (c->res_on) CHK(res_adjoint(c, gr, d));
     // segments j >= jc replay into the replay cache, and only when it does
     // not hold this group's replays yet
-    const int jc = c->nseg - c->rc_m;
     for (int j = c->res_on ? -1 : c->nseg - 1; j >= 0; --j) {
         const int n0 = j * c->k, n1 = std::min(n0 + c->k, nt);
-        const Slot* rcd = j >= jc ? gr.d_rc + (long long)(j - jc) * gr.ns : nullptr;
+        const Slot* rcd = rc_slots(c, gr, j);
         tstep(c, n0);
-        if (!rcd || !gr.rc_valid) {
-            if (j == 0) CHK(fill(c, c->pool, gr.bg_used));
-            else CHK(ckpt(c, gr, j, false, desc(gr, fz ? n0 : 0)));
-            for (int n = n0; n < n1; ++n) {
-                tstep(c, n);
-                const Slot* cur = rcd ? rcd : desc(gr, fz ? n : 0);
-                CHK(stencil(c, gr, K_SEG_V, n, n - n0, 0, cur));
-                if (!fz) CHK(stencil(c, gr, K_SEG_P, n, n - n0, 0, cur));
-            }
-        }
+        if (!rcd || !gr.rc_valid) CHK(replay(c, gr, j, rcd));
         // 2D: the adjoint velocity kernel of step n injects the data of step
         // n - 1 into the new adjoint pressure; 3D uses the injection kernel
         const TileRec tr{gr.d_trp, gr.d_trec, nullptr, d};
@@ -1027,13 +1049,18 @@ template <typename F>
 lsrtm_status run_passes(lsrtm_ctx* c, int pass, F body) {
     const auto run = [&](bool resident) -> lsrtm_status {
         c->res_on = resident;
-        // the two schedules keep the replay cache in layouts of their own, and
-        // the migrations fill it
-        if (pass == PASS_MIGRATION && c->rc_res != resident) {
-            for (auto& gr : c->groups) gr.rc_valid = false;
-            c->rc_res = resident;
-        }
         if (!resident) CHK(tile_ready(c));
+        // The two schedules keep the replay cache in layouts of their own.  The
+        // migrations fill it.  Born passes on the other schedule do without it,
+        // except after 16-bit checkpoints, whose rounding they have from there.
+        if (c->rc_m > 0 && c->rc_res != resident) {
+            if (pass == PASS_MIGRATION) {
+                for (auto& gr : c->groups) gr.rc_valid = false;
+                c->rc_res = resident;
+            } else if (pass == PASS_BORN && c->g.ckpt_dtype != 0) {
+                CHK(refill_cache(c));
+            }
+        }
         return body();
     };
     const auto now = std::chrono::steady_clock::now();
@@ -1041,6 +1068,9 @@ lsrtm_status run_passes(lsrtm_ctx* c, int pass, F body) {
     c->res_last = false;
     if (!c->res_ok || !c->opt_res || !c->res_pass[pass] || paused) return run(false);
     const size_t samples = c->evused;
+    const bool had_ckpts = c->ckpt_valid;
+    std::vector<char> had_replays;
+    for (const auto& gr : c->groups) had_replays.push_back(gr.rc_valid);
     {
         ResRoom room(c->res_dev, c->res_most, c->res_cus);
         HIPCHK(c, launch_fill(reinterpret_cast<float*>(c->res_ctl), 1, c->opt_res == 2 ? 1.f : 0.f, c->st));
@@ -1058,7 +1088,11 @@ lsrtm_status run_passes(lsrtm_ctx* c, int pass, F body) {
     c->res_pause = std::min(16 * RES_PAUSE, std::max(RES_PAUSE, 2 * c->res_pause));
     c->res_since = std::chrono::steady_clock::now();
     c->evused = samples;           // those of the launches that gave up
-    background_changed(c);
+    // what was stored before the call is still there, but for what it stored
+    // again: a forward call its checkpoints, a migration, or a Born pass that had
+    // to, the cache in rc_res's layout, which the streaming kernels fill anew
+    c->ckpt_valid = had_ckpts && pass != PASS_FORWARD;
+    for (size_t g = 0; g < c->groups.size(); ++g) c->groups[g].rc_valid = had_replays[g];
     return run(false);
 }
 
@@ -1699,9 +1733,30 @@ lsrtm_status plan(lsrtm_ctx* c) {
         } else {
             r = size_plan(true);
         }
-        if (r.fits && r.ckg == z.ckg && res_pick(c, r.sizes, bz, c->res_cus, cuts, picks)) {
+        // Born passes after 16-bit checkpoints have the rounding of the segments that
+        // the cache holds, which therefore stay as many
+        const auto cached = [&](const Sizing& q, bool res) -> long long {
+            if (c->opt_rcache_mb <= 0 || q.ckg) return 0;
+            long long seg = 0;
+            for (const auto& sh : c->shots) seg += seg_of(c->wins[sh.win], res);
+            const long long cap = std::min(c->opt_rcache_mb * 1024LL * 1024LL, budget - q.need);
+            const int nseg = (nt + q.k - 1) / q.k;
+            return std::max(0LL, std::min<long long>(nseg, cap / (seg * q.k * (nd + 1) * 4)));
+        };
+        const long long held16 = c->g.ckpt_dtype != 0 ? cached(z, false) : 0;
+        const bool same16 = c->g.ckpt_dtype == 0 || cached(r, true) == held16;
+        if (r.fits && r.ckg == z.ckg && same16 && res_pick(c, r.sizes, bz, c->res_cus, cuts, picks)) {
+            double res[3], str[3];
             for (int pass : {PASS_FORWARD, PASS_BORN, PASS_MIGRATION}) {
-                c->res_pass[pass] = c->opt_res == 3 || resident_us(c, pass, r, bz, picks) <= 0.95 * streaming_us(c, pass, z);
+                res[pass] = resident_us(c, pass, r, bz, picks);
+                str[pass] = streaming_us(c, pass, z);
+            }
+            if (held16 > 0) {        // one layout for both, or every call would fill the cache anew
+                res[PASS_BORN] = res[PASS_MIGRATION] = res[PASS_BORN] + res[PASS_MIGRATION];
+                str[PASS_BORN] = str[PASS_MIGRATION] = str[PASS_BORN] + str[PASS_MIGRATION];
+            }
+            for (int pass : {PASS_FORWARD, PASS_BORN, PASS_MIGRATION}) {
+                c->res_pass[pass] = c->opt_res == 3 || res[pass] <= 0.95 * str[pass];
                 if (c->res_pass[pass]) c->res_bz = bz;
             }
             if (c->res_bz) z = r;

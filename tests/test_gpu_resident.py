@@ -493,3 +493,38 @@ def test_mixed_plans_share_no_layout():
         ctx.close()
     for i, (a, b) in enumerate(zip(*got)):
         assert torch.equal(a, b), i
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+def test_cached_replays_of_rounded_checkpoints(dtype):
+    """Born passes take the segments that the replay cache holds from there,
+    with the rounding of 16-bit checkpoints: as many segments as without the
+    resident layout, after launches that found no room and during the pause too."""
+    torch = require_gpu()
+    w = synth.small((100, 120), nt=60, npml=10, seed=15, nshot=6)
+    dm = to_dev(torch, w.dm)
+    planned = set()
+    for mb in (4, 30, 60, 90, 130, 2000):
+        got = []
+        for resident in (0, 1):
+            ctx = _context(torch, w, resident, ckpt_dtype=dtype, ckpt_every=9, replay_cache_mb=mb, shots_per_launch=4)
+            held = ctx.sizes()["replay_cache_segments"]
+            out = []
+            # the option before each call: 2 gives up, 1 after it ends the pause, None leaves it
+            for kind, option in (("f", 1), ("b", 1), ("a", 1), ("b", 1), ("b", 2), ("b", None), ("a", None), ("b", None),
+                                 ("b", 1), ("a", 1), ("b", 1), ("f", 2), ("b", None), ("b", 1), ("a", 2), ("b", None), ("b", 1),
+                                 ("a", 1), ("b", 1)):
+                if resident and option is not None:
+                    ctx.set_option(lsrtm.OPT_RESIDENT, option)
+                out.append(ctx.forward() if kind == "f" else ctx.born(dm) if kind == "b" else ctx.adjoint(out[0]))
+            got.append(out)
+            if resident:
+                planned.add(ctx.resident()["planned"])
+                segments.append(held)
+            else:
+                segments = [held]
+            ctx.close()
+        assert dtype == "f32" or segments[0] == segments[1]
+        for i, (a, b) in enumerate(zip(*got)):
+            assert torch.equal(a, b), (mb, i, segments)
+    assert True in planned
