@@ -287,8 +287,8 @@ __device__ __forceinline__ void adj_body(const ResArgs& a, const ResBlock& B, fl
             for (int k = 0; k < BZ; ++k) {
                 sz[c][k] = 0.5f * (x[k] + (k ? x[k ? k - 1 : 0] : xb));
                 // the last node of an axis takes the other half of its own
-                // product too (0.5 x is exact, so the fma rounds as the sum)
-                if (k == zlast) sz[c][k] = fmaf(flast, x[k], sz[c][k]);
+                // product too (rounded by itself: half an odd subnormal is inexact)
+                if (k == zlast) sz[c][k] = sz[c][k] + flast * x[k];
                 pin(sz[c][k]);
             }
         }

@@ -528,3 +528,24 @@ def test_cached_replays_of_rounded_checkpoints(dtype):
         for i, (a, b) in enumerate(zip(*got)):
             assert torch.equal(a, b), (mb, i, segments)
     assert True in planned
+
+
+@pytest.mark.parametrize("nz,nx,npml,nshot", [(12, 42, 0, 3), (65, 60, 0, 2), (257, 60, 4, 3), (320, 203, 20, 24)])
+def test_subnormal_images(nz, nx, npml, nshot):
+    """Data so small that the images are subnormal: the same bits."""
+    torch = require_gpu()
+    w = synth.small((nz - 2 * npml, nx - 2 * npml), nt=14, npml=npml, seed=nz, nshot=nshot)
+    for s in range(nshot):               # about the last rows, whose half nodes are their own
+        w.rec[s][:, 0] = nz - 2 * npml - 1 - np.arange(len(w.rec[s])) % 3
+        w.src[s] = (nz - 2 * npml - 2, w.src[s][1])
+    got = []
+    for resident in (0, 3):
+        ctx = _context(torch, w, resident, ckpt_every=5)
+        d = ctx.born(to_dev(torch, w.dm))
+        top = float(ctx.adjoint(d).abs().max())
+        got.append([ctx.adjoint(d * (s / top)) for s in (1e-36, 1e-38, 1e-40, 1e-42)])
+        assert 0.0 < float(got[-1][-2].abs().max()) < 1.2e-38
+        assert ctx.resident()["last"] == (resident > 0)
+        ctx.close()
+    for i, (a, b) in enumerate(zip(*got)):
+        assert torch.equal(a.view(torch.int32), b.view(torch.int32)), (i, int((a != b).sum()))
