@@ -1615,7 +1615,7 @@ lsrtm_status plan(lsrtm_ctx* c) {
     };
     // The resident kernels store a column's replay rows in whole waves.
     const auto seg_of = [&](const Window& W, bool res) { return res ? res_segn(W.npts, W.N[1], bz) : W.npts; };
-    const auto size_plan = [&](bool res) {
+    const auto size_plan = [&](bool res, int least_k) {
         Sizing z;
         // points of the largest group and of all shots, and their replay buffers'
         long long grp_pts = 0, grp_seg = 0, all_seg = 0;
@@ -1634,6 +1634,12 @@ lsrtm_status plan(lsrtm_ctx* c) {
                 all_seg += seg;
             }
         };
+        const auto need_of = [&](int kk) -> long long {
+            const int ns = (nt + kk - 1) / kk;
+            const double ck_mem = z.ckg ? (double)z.G * max_ck : (double)ck_per_shot_sum;
+            return fixed + grp_pts * (nbg + nsc + 2) * 4LL + (long long)kk * (grp_seg * (nd + 1) * 4) +
+                   (long long)((ns - 1) * ck_mem) + (long long)ns * nshot * (1 + nd) * 4;
+        };
         for (int mode = c->opt_ckg ? 1 : 0; mode < 2 && !z.fits; ++mode) {
             z.ckg = mode == 1;
             z.G = G0;
@@ -1647,9 +1653,7 @@ lsrtm_status plan(lsrtm_ctx* c) {
                     const double kk = std::sqrt((double)nt * ck_mem / (double)std::max(1LL, seg_step));
                     z.k = (int)std::max(1.0, std::min((double)nt, std::round(kk)));
                 }
-                const int nseg = (nt + z.k - 1) / z.k;
-                z.need = fixed + grp_pts * (nbg + nsc + 2) * 4LL + (long long)z.k * seg_step +
-                         (long long)((nseg - 1) * ck_mem) + (long long)nseg * nshot * (1 + nd) * 4;
+                z.need = need_of(z.k);
                 if (z.need <= budget) {
                     z.fits = true;
                     break;
@@ -1672,13 +1676,7 @@ lsrtm_status plan(lsrtm_ctx* c) {
         // cache holds no less.
         const bool lengthen = res && c->g.ckpt_dtype == 0;
         if ((c->opt_rcache_mb > 0 || lengthen) && !c->fused && !z.ckg && c->g.ckpt_every <= 0) {
-            const long long seg_step = grp_seg * (nd + 1) * 4;   // replay buffer bytes per step
             const long long step_all = all_seg * (nd + 1) * 4;   // cache bytes per step, all groups
-            auto need_of = [&](int kk) -> long long {
-                const int ns = (nt + kk - 1) / kk;
-                return fixed + grp_pts * (nbg + nsc + 2) * 4LL + (long long)kk * seg_step +
-                       (long long)((ns - 1) * (double)ck_per_shot_sum) + (long long)ns * nshot * (1 + nd) * 4;
-            };
             auto held = [&](int kk) -> long long {   // steps of every group the cache would hold
                 const long long nk = need_of(kk);
                 if (nk > budget) return -1;
@@ -1706,13 +1704,18 @@ lsrtm_status plan(lsrtm_ctx* c) {
                 z.need = need_of(z.k);
             }
         }
+        if (least_k > z.k) {
+            z.k = least_k;
+            z.need = need_of(z.k);
+            z.fits = z.need <= budget;
+        }
         return z;
     };
     // What fits is decided without the resident kernels' larger replay buffer
     // (1.1 times at 280 padded rows, 2 to 4 times below 65): they are taken where
     // that buffer fits the budget too, with the same checkpoint layout, for the
     // kinds of calls that are estimated to be faster on them.
-    Sizing z = size_plan(false);
+    Sizing z = size_plan(false, 0);
     if (!z.fits)
         FAIL(c, LSRTM_ENOMEM, "memory plan needs %.2f GB, budget %.2f GB", z.need / 1e9, budget / 1e9);
     ResPicks picks;
@@ -1731,7 +1734,7 @@ lsrtm_status plan(lsrtm_ctx* c) {
             r.need += more * z.k * (nd + 1) * 4;
             r.fits = r.need <= budget;
         } else {
-            r = size_plan(true);
+            r = size_plan(true, 0);
         }
         // Born passes after 16-bit checkpoints have the rounding of the segments that
         // the cache holds, which therefore stay as many
@@ -1758,6 +1761,11 @@ lsrtm_status plan(lsrtm_ctx* c) {
             for (int pass : {PASS_FORWARD, PASS_BORN, PASS_MIGRATION}) {
                 c->res_pass[pass] = c->opt_res == 3 || res[pass] <= 0.95 * str[pass];
                 if (c->res_pass[pass]) c->res_bz = bz;
+            }
+            // calls that stay on the streaming kernels write no more checkpoints than without the others
+            if (c->res_bz && r.k < z.k && c->opt_rcache_mb <= 0 && !(c->res_pass[PASS_FORWARD] && c->res_pass[PASS_BORN] && c->res_pass[PASS_MIGRATION])) {
+                const Sizing longer = size_plan(true, z.k);
+                if (longer.fits && longer.sizes == r.sizes && longer.ckg == r.ckg) r = longer;
             }
             if (c->res_bz) z = r;
         }

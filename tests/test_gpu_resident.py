@@ -406,7 +406,7 @@ def test_route_by_estimate(shape, expect, opts):
     nz, nx, npml, nshot, nt = shape
     w = synth.small((nz - 2 * npml, nx - 2 * npml), nt=nt, npml=npml, seed=nz, nshot=nshot, nrec=30)
     dm = to_dev(torch, w.dm)
-    got = []
+    got, every = [], []
     for resident in (1, 0):
         ctx = _context(torch, w, None if resident else 0, mem_budget_mb=30000, **opts)
         out, route = [], []
@@ -416,11 +416,14 @@ def test_route_by_estimate(shape, expect, opts):
             route.append(ctx.resident()["last"])
         assert tuple(route) == ((*expect, *expect[1:], expect[0]) if resident else (False,) * 6)
         assert ctx.resident()["planned"] == (bool(resident) and any(expect))
+        every.append(ctx.sizes()["ckpt_every"])
         x, mis = ctx.cgnr(out[1], 1)
         got.append(out + [x, torch.tensor(mis)])
         ctx.close()
     for i, (a, b) in enumerate(zip(*got)):
         assert torch.equal(a, b), i
+    # calls that stay streaming write no more checkpoints for the others' sake
+    assert opts or all(expect) or every[0] >= every[1]
 
 
 def test_autotune_times_the_kernels_of_the_passes(tmp_path, monkeypatch):
