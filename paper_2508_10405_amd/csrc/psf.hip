@@ -213,10 +213,6 @@ __global__ void __launch_bounds__(SPLIT * NTHREADS) k_psf_t(Psf2Args a, const fl
         for (int p = 0; p < NB; ++p) xs[p * pz * px + e] = in ? x[p * a.N + jz + (long long)a.n[0] * jx] : 0.f;
     }
     __syncthreads();
-    if (bad >= a.packing) {
-        gather_piece(a, x, y, 1, sz.x, lz, sx.x, lx);
-        return;
-    }
     const long long win = (long long)D * D * NB * NB;
     const float* P[4];
 #pragma unroll
@@ -283,6 +279,10 @@ __global__ void __launch_bounds__(SPLIT * NTHREADS) k_psf_t(Psf2Args a, const fl
                 }
         if (SPLIT > 1) __syncthreads();
     }
+    if (bad >= a.packing) {
+        __syncthreads();                                     // over the outputs just stored
+        gather_piece(a, x, y, 1, sz.x, lz, sx.x, lx);
+    }
 }
 
 // y = H x: a block serves a piece of outputs, two rows of z per thread, and
@@ -299,10 +299,7 @@ __global__ void __launch_bounds__(64 * PSF_WAVES) k_psf_f(Psf2Args a, const floa
     const int4 sz = a.fz[blockIdx.x % a.nfz], sx = a.fx[blockIdx.x / a.nfz];   // (start, length, corners first .. last)
     const int lz = sz.y, lx = sx.y, np = (lz + 1) / 2;
     const int *tz = a.tab + 3 * a.off[0], *tx = a.tab + 3 * a.off[1];
-    if (*a.bad >= a.packing) {
-        gather_piece(a, x, y, 0, sz.x, lz, sx.x, lx);
-        return;
-    }
+    const int bad = *a.bad;
     float acc[CH][NB][2] = {};
     // points a corner serves on an axis
     auto lo = [&](int k) { return k == 0 ? 0 : W + (k - 1) * a.s + 1; };
@@ -362,6 +359,10 @@ __global__ void __launch_bounds__(64 * PSF_WAVES) k_psf_f(Psf2Args a, const floa
         for (int e = 0; e < CH * NB * 2; ++e)
             lds[((wave - 1) * CH * NB * 2 + e) * 64 + lane] = acc[e / (2 * NB)][e / 2 % NB][e % 2];
     __syncthreads();
+    if (bad >= a.packing) {
+        gather_piece(a, x, y, 0, sz.x, lz, sx.x, lx);
+        return;
+    }
     if (wave > 0) return;
 #pragma unroll
     for (int ch = 0; ch < CH; ++ch) {
