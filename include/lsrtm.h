@@ -124,7 +124,10 @@ enum {
                                        those segments, and later 2D Born passes
                                        run only the scattered phases there,
                                        reading the background from it.  Results
-                                       are bitwise the same.  Two-phase steps with checkpoints
+                                       are bitwise the same (after 16-bit
+                                       checkpoints those Born passes take their
+                                       rounding over from the cached segments).
+                                       Two-phase steps with checkpoints
                                        for the whole plan only; 0 = off
                                        (default).  Re-plans when changed.       */
     LSRTM_OPT_GRAPH_CACHE = 12,     /* most pass graphs kept (least recently
