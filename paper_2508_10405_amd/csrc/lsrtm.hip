@@ -1051,14 +1051,14 @@ lsrtm_status run_passes(lsrtm_ctx* c, int pass, F body) {
         c->res_on = resident;
         if (!resident) CHK(tile_ready(c));
         // The two schedules keep the replay cache in layouts of their own.  The
-        // migrations fill it.  Born passes on the other schedule do without it,
-        // except after 16-bit checkpoints, whose rounding they have from there.
+        // migrations fill it.  A Born pass that has to leave their schedule does
+        // without it, except after 16-bit checkpoints, whose rounding it has from there.
         if (c->rc_m > 0 && c->rc_res != resident) {
-            if (pass == PASS_MIGRATION) {
+            if (pass == PASS_BORN && c->g.ckpt_dtype != 0 && c->ckpt_valid) {
+                CHK(refill_cache(c));
+            } else if (pass == PASS_MIGRATION) {
                 for (auto& gr : c->groups) gr.rc_valid = false;
                 c->rc_res = resident;
-            } else if (pass == PASS_BORN && c->g.ckpt_dtype != 0) {
-                CHK(refill_cache(c));
             }
         }
         return body();
@@ -1746,15 +1746,15 @@ lsrtm_status plan(lsrtm_ctx* c) {
             const int nseg = (nt + q.k - 1) / q.k;
             return std::max(0LL, std::min<long long>(nseg, cap / (seg * q.k * (nd + 1) * 4)));
         };
-        const long long held16 = c->g.ckpt_dtype != 0 ? cached(z, false) : 0;
-        const bool same16 = c->g.ckpt_dtype == 0 || cached(r, true) == held16;
+        const long long held = cached(r, true);
+        const bool same16 = c->g.ckpt_dtype == 0 || held == cached(z, false);
         if (r.fits && r.ckg == z.ckg && same16 && res_pick(c, r.sizes, bz, c->res_cus, cuts, picks)) {
             double res[3], str[3];
             for (int pass : {PASS_FORWARD, PASS_BORN, PASS_MIGRATION}) {
                 res[pass] = resident_us(c, pass, r, bz, picks);
                 str[pass] = streaming_us(c, pass, z);
             }
-            if (held16 > 0) {        // one layout for both, or every call would fill the cache anew
+            if (held > 0) {          // one layout, that both can read
                 res[PASS_BORN] = res[PASS_MIGRATION] = res[PASS_BORN] + res[PASS_MIGRATION];
                 str[PASS_BORN] = str[PASS_MIGRATION] = str[PASS_BORN] + str[PASS_MIGRATION];
             }

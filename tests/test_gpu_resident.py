@@ -385,11 +385,13 @@ def test_plans_without_the_resident_layout():
         ref.close()
 
 
-# (padded nz, padded nx, npml, shots, steps), whether forward, Born, migration take the resident kernels
+# (padded nz, padded nx, npml, shots, steps), whether forward, Born, migration take the resident kernels; with a replay
+# cache Born passes and migrations, which share it, go together
 ROUTES = [
     ((8, 240, 0, 256, 100), (False, False, False)),      # 4 of 64 lanes, 256 shots
     ((28, 757, 10, 64, 100), (False, False, False)),
-    ((40, 260, 10, 256, 100), (False, True, False)),
+    ((40, 260, 10, 256, 100), (False, True, False)),     # together 0.98 of the streaming estimate
+    ((28, 80, 6, 32, 12), (True, False, True)),          # together 0.83
     ((64, 280, 20, 64, 12), (False, False, False)),      # a short march
     ((28, 260, 10, 4, 100), (True, True, True)),         # few shots
     ((140, 240, 20, 1, 1000), (True, True, True)),
@@ -404,6 +406,10 @@ def test_route_by_estimate(shape, expect, opts):
     on mixed routes share checkpoints and cached replays rightly."""
     torch = require_gpu()
     nz, nx, npml, nshot, nt = shape
+    if shape[0] == 28 and nshot == 32:
+        opts = dict(opts, ckpt_every=20)                 # one segment
+    if "replay_cache_mb" in opts and expect[1] != expect[2]:
+        expect = (expect[0],) + (shape[0] == 28,) * 2
     w = synth.small((nz - 2 * npml, nx - 2 * npml), nt=nt, npml=npml, seed=nz, nshot=nshot, nrec=30)
     dm = to_dev(torch, w.dm)
     got, every = [], []
@@ -423,7 +429,7 @@ def test_route_by_estimate(shape, expect, opts):
     for i, (a, b) in enumerate(zip(*got)):
         assert torch.equal(a, b), i
     # calls that stay streaming write no more checkpoints for the others' sake
-    assert opts or all(expect) or every[0] >= every[1]
+    assert "replay_cache_mb" in opts or all(expect) or every[0] >= every[1]
 
 
 def test_autotune_times_the_kernels_of_the_passes(tmp_path, monkeypatch):
@@ -476,9 +482,11 @@ def test_born_passes_keep_off_the_other_layout():
     ctx.close()
 
 
-def test_mixed_plans_share_no_layout():
-    """Migrations resident, Born passes streaming (32 small shots, 12 steps in
-    one segment): Born passes do without the replays that the migrations keep."""
+def test_calls_that_share_a_cache_go_together():
+    """Born passes and migrations of a plan with a replay cache take the same
+    kernels, also where the estimate has one of them faster on the others (32
+    small shots, 12 steps in one segment): every Born pass after a migration
+    reads the cached replays."""
     torch = require_gpu()
     w = synth.small((16, 68), nt=12, npml=6, seed=14, nshot=32, nrec=20)
     dm = to_dev(torch, w.dm)
@@ -491,7 +499,7 @@ def test_mixed_plans_share_no_layout():
                      lambda: ctx.born(dm)):
             out.append(call())
             route.append(ctx.resident()["last"])
-        assert route == ([False, True, False, True, False] if resident is None else [False] * 5)
+        assert route == [resident is None] * 5
         got.append(out)
         ctx.close()
     for i, (a, b) in enumerate(zip(*got)):
