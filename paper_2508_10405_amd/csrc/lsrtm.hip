@@ -1149,21 +1149,30 @@ lsrtm_status prep_model_windows(lsrtm_ctx* c) {
 }
 
 // Slabs of an axis of nx padded columns (the ones that reach a strip are as
-// wide as their body allows): first column and whether in the strips, and the
-// slab of every column.
+// wide as their body allows): first column and whether in the strips.
 struct ResCut {
+    int nx = 0;
     std::vector<std::pair<int, bool>> slabs;
-    std::vector<int> of;
+    // the slab of every column, made when it is first asked for
+    const std::vector<int>& of() const {
+        if (of_.empty()) {
+            of_.resize(nx);
+            for (size_t b = 0; b < slabs.size(); ++b)
+                std::fill(of_.begin() + slabs[b].first, b + 1 < slabs.size() ? of_.begin() + slabs[b + 1].first : of_.end(), (int)b);
+        }
+        return of_;
+    }
+
+  private:
+    mutable std::vector<int> of_;
 };
 ResCut res_cut(int nx, int npml, int cx) {
     ResCut r;
-    r.of.resize(nx);
+    r.nx = nx;
     for (int x = 0; x < nx;) {
         const bool inner = x >= npml && x + RES_WAVES * cx <= nx - npml - 1;
-        const int x1 = std::min(nx, x + RES_WAVES * (inner ? cx : res_cx_edge(cx)));
-        for (int i = x; i < x1; ++i) r.of[i] = (int)r.slabs.size();
         r.slabs.push_back({x, !inner});
-        x = x1;
+        x += RES_WAVES * (inner ? cx : res_cx_edge(cx));
     }
     return r;
 }
@@ -1228,6 +1237,22 @@ bool res_pick(const lsrtm_ctx* c, const std::vector<int>& sizes, int bz, int ncu
         int blocks, recs, nodes;
     };
     std::vector<std::array<Fit, RES_CX_MAX + 1>> fit(c->nshot);
+    // most receivers (adjoint: nodes) of a workgroup that its LDS holds, -1 if not even none
+    int room[R_KINDS][RES_CX_MAX + 1], least[RES_CX_MAX + 1];
+    double step[R_KINDS][RES_CX_MAX + 1];
+    for (int cx = 1; cx <= RES_CX_MAX; ++cx) {
+        least[cx] = INT_MAX;
+        for (int kind = 0; kind < R_KINDS; ++kind) {
+            int lo = -1, hi = (int)(RES_LDS / 4);
+            while (lo + 1 < hi) {
+                const int mid = lo + (hi - lo) / 2;
+                (res_lds_bytes(kind, bz, cx, mid) <= RES_LDS ? lo : hi) = mid;
+            }
+            room[kind][cx] = lo;
+            if (kind != R_SEG) least[cx] = std::min(least[cx], lo);
+            step[kind][cx] = res_step_us(kind, bz * cx);
+        }
+    }
     std::vector<int> cols, count, distinct;
     for (int s = 0; s < c->nshot; ++s) {
         const ShotInfo& sh = c->shots[s];
@@ -1240,25 +1265,23 @@ bool res_pick(const lsrtm_ctx* c, const std::vector<int>& sizes, int bz, int ncu
             f.blocks = (int)cut.slabs.size();
             // counted only where all of the shot's on one slab would not fit
             f.recs = f.nodes = sh.nrec;
-            bool any = true;
-            for (int kind = 0; kind < R_KINDS; ++kind) any = any && res_lds_bytes(kind, bz, cx, kind == R_SEG ? 0 : sh.nrec) <= RES_LDS;
-            if (any) continue;
+            if (sh.nrec <= least[cx]) continue;
             if (cols.empty()) {
                 cols.resize(sh.nrec);
                 for (int r = 0; r < sh.nrec; ++r) cols[r] = sh.rec_lin[r] / ldz;
             }
             count.assign(cut.slabs.size(), 0);
-            for (int x : cols) ++count[cut.of[x]];
+            for (int x : cols) ++count[cut.of()[x]];
             f.recs = f.nodes = *std::max_element(count.begin(), count.end());
             // receivers that share nodes are told apart only where it matters
-            if (res_lds_bytes(R_ADJ, bz, cx, f.nodes) > RES_LDS) {
+            if (f.nodes > room[R_ADJ][cx]) {
                 if (distinct.empty()) {
                     distinct = sh.rec_lin;
                     std::sort(distinct.begin(), distinct.end());
                     distinct.erase(std::unique(distinct.begin(), distinct.end()), distinct.end());
                 }
                 count.assign(cut.slabs.size(), 0);
-                for (int i : distinct) ++count[cut.of[i / ldz]];
+                for (int i : distinct) ++count[cut.of()[i / ldz]];
                 f.nodes = *std::max_element(count.begin(), count.end());
             }
         }
@@ -1279,8 +1302,8 @@ bool res_pick(const lsrtm_ctx* c, const std::vector<int>& sizes, int bz, int ncu
                         const Fit& f = fit[s0 + e][cx];
                         blocks += f.blocks;
                         most = std::max(most, kind == R_SEG ? 0 : kind == R_ADJ ? f.nodes : f.recs);
-                        if (blocks > ncu || res_lds_bytes(kind, bz, cx, most) > RES_LDS) break;
-                        const double t = res_step_us(kind, bz * cx) + best[e + 1];
+                        if (blocks > ncu || most > room[kind][cx]) break;
+                        const double t = step[kind][cx] + best[e + 1];
                         if (t < best[i]) {
                             best[i] = t;
                             pick[i] = {i, e + 1 - i, cx};
@@ -1396,7 +1419,7 @@ lsrtm_status plan_resident(lsrtm_ctx* c, const ResCuts& cuts, const ResPicks& pi
                             blocks.push_back({s, sl[b].first,
                                               (b > 0 ? 1 : 0) | (b + 1 < sl.size() ? 2 : 0) | (sl[b].second ? 4 : 0), 0});
                     }
-                    const auto block_of = [&](int s, int x) { return base[s - P.first] + cut_of(s, L.cx).of[x]; };
+                    const auto block_of = [&](int s, int x) { return base[s - P.first] + cut_of(s, L.cx).of()[x]; };
                     L.nblocks = (int)blocks.size();
                     if (records) {
                         const auto r0 = from(P.first), r1 = from(end);
@@ -1457,10 +1480,12 @@ lsrtm_status plan_resident(lsrtm_ctx* c, const ResCuts& cuts, const ResPicks& pi
     }
     c->res_ctln = (int)((2 * c->nseg + 4) * rounds + 1);
     c->res_exn = exn;
-    // without room for these the passes stay on the streaming kernels
-    if (dalloc_t(c, &c->res_tab, tab.size(), true) != LSRTM_OK || dalloc_t(c, &c->res_ex, exn, true) != LSRTM_OK ||
-        dalloc_t(c, &c->res_ctl, c->res_ctln, true) != LSRTM_OK)
-        return LSRTM_OK;
+    // tables, exchange words and arrival counts in one block; without room for it
+    // the passes stay on the streaming kernels
+    const size_t ex_at = (tab.size() + 255) / 256 * 256, ctl_at = ex_at + exn * sizeof(*c->res_ex);
+    if (dalloc_t(c, &c->res_tab, ctl_at + c->res_ctln * sizeof(int), true) != LSRTM_OK) return LSRTM_OK;
+    c->res_ex = reinterpret_cast<unsigned long long*>(c->res_tab + ex_at);
+    c->res_ctl = reinterpret_cast<int*>(c->res_tab + ctl_at);
     HIPCHK(c, hipMemcpy(c->res_tab, tab.data(), tab.size(), hipMemcpyHostToDevice));
     c->res_ok = true;
     return LSRTM_OK;
@@ -1762,6 +1787,8 @@ lsrtm_status plan(lsrtm_ctx* c) {
                 c->res_pass[pass] = c->opt_res == 3 || res[pass] <= 0.95 * str[pass];
                 if (c->res_pass[pass]) c->res_bz = bz;
             }
+            // a cache that streaming passes alone read is not padded for a forward call's sake
+            if (c->opt_rcache_mb > 0 && !c->res_pass[PASS_BORN] && !c->res_pass[PASS_MIGRATION]) c->res_bz = 0;
             // calls that stay on the streaming kernels write no more checkpoints than without the others
             if (c->res_bz && r.k < z.k && c->opt_rcache_mb <= 0 && !(c->res_pass[PASS_FORWARD] && c->res_pass[PASS_BORN] && c->res_pass[PASS_MIGRATION])) {
                 const Sizing longer = size_plan(true, z.k);
